@@ -316,6 +316,65 @@ __device__ __forceinline__ bool touch_line(const void* ptr, int t, int extent, i
   return true;
 }
 
+// ---- epilogue helpers (shared with the persistent kernel) ------------------------------------
+// The fused elementwise function is act(alpha * acc + bias[n]).  A lane's columns are the same in
+// every 32-row band, so its TN * 4 groups of four bias values are fetched once per tile, all at
+// once and without branches (columns past N take the values of column 0 and are not stored).
+// Fetched one group at a time where it is used, each load under its own lane mask, the bias cost
+// a serial chain of TM * TN * 4 memory latencies: 4096 x 3072 x 768 bf16 with bias and ReLU took
+// 29.9 us against 21.2 us without them.
+template <int TN, class HW>
+__device__ __forceinline__ void load_bias(const Params& p, int n0, int lane, f32x4 (&bv)[TN * 4])
+{
+  if (p.bias == nullptr) {
+#pragma unroll
+    for (int g = 0; g < TN * 4; g++) bv[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    return;
+  }
+#pragma unroll
+  for (int g = 0; g < TN * 4; g++) {
+    const int n = n0 + 8 * g + 4 * (lane >> 5);
+    bv[g] = HW::global_load_f32x4(p.bias + (n < p.N ? n : 0));
+  }
+}
+
+// Converts the 32-row band j of the accumulators to the output type and parks it in LDS at
+// `ebase` (row stride RS bytes).  act(): t < floor ? 0 : t with floor = 0 (ReLU) or -infinity.
+template <class OT, int RS, class HW, int TN, int TM>
+__device__ __forceinline__ void park_band(const Params& p, f32x16 (&acc)[TN][TM], int j, uint32_t ebase,
+                                          int lane, bool fused, const f32x4 (&bv)[TN * 4])
+{
+  typedef OT ot4 __attribute__((ext_vector_type(4)));
+  const uint32_t row = ebase + (lane & 31) * RS + 4 * (lane >> 5) * (int)sizeof(OT);
+  auto put = [&](int i, int vq, f32x4 v) __attribute__((always_inline)) {
+    const ot4 h = {HW::template cvt<OT>(v[0]), HW::template cvt<OT>(v[1]),
+                   HW::template cvt<OT>(v[2]), HW::template cvt<OT>(v[3])};
+    HW::lds_write(row + (i * 32 + 8 * vq) * (int)sizeof(OT), h);
+  };
+  if (fused) {
+    const float floor = p.act == 1 ? 0.f : -__builtin_inff();
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int vq = 0; vq < 4; vq++) {
+        f32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const float t = acc[i][j][4 * vq + e] * p.alpha + bv[i * 4 + vq][e];
+          v[e] = t < floor ? 0.f : t;
+        }
+        put(i, vq, v);
+      }
+  } else {
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int vq = 0; vq < 4; vq++)
+        put(i, vq, f32x4{acc[i][j][4 * vq + 0], acc[i][j][4 * vq + 1], acc[i][j][4 * vq + 2],
+                         acc[i][j][4 * vq + 3]});
+  }
+}
+
 template <class C, class HW>
 __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
 {
@@ -747,6 +806,9 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
       if constexpr (S >= 2) stage_end();
     }
   }
+  const bool fused = p.alpha != 1.0f || p.bias != nullptr || p.act != 0;
+  f32x4 bv[TN * 4];
+  if (fused) load_bias<TN, HW>(p, tn * BN + wn * WN, lane, bv);   // in flight during the drain
   HW::template wait_vm<0>();   // drain the zero-fill loads of the ring's tail before the ring is reused
   HW::wait_lds();
   HW::block_barrier();   // every wave has finished reading the ring
@@ -762,34 +824,13 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
     constexpr int RS = WN * OB + 16;                 // LDS row stride of the band
     constexpr int LPR = WN * OB / 16;                // lanes per row when reading back
     constexpr int RPI = 64 / LPR;                    // rows per read instruction
-    typedef OT ot4 __attribute__((ext_vector_type(4)));
     const uint32_t ebase = lds0 + (uint32_t)wave * C::EPI_WAVE_BYTES;
     const int m0 = tm * BM + wm * WM, n0 = tn * BN + wn * WN;
     char* Cb = (char*)p.C + (long)batch * p.strideC * OB;
     if constexpr (C::SK) Cb += (long)HW::block_z() * p.zstrideC * OB;
-    const bool fused = p.alpha != 1.0f || p.bias != nullptr || p.act != 0;
 #pragma unroll
     for (int j = 0; j < TM; j++) {
-#pragma unroll
-      for (int i = 0; i < TN; i++)
-#pragma unroll
-        for (int vq = 0; vq < 4; vq++) {
-          f32x4 v = {acc[i][j][4 * vq + 0], acc[i][j][4 * vq + 1], acc[i][j][4 * vq + 2],
-                     acc[i][j][4 * vq + 3]};
-          if (fused) {   // f(.) on the accumulators (paper Sec. 3.2: fused into the consumer)
-            const int n = n0 + i * 32 + 8 * vq + 4 * (lane >> 5);
-            f32x4 b = {0.f, 0.f, 0.f, 0.f};
-            if (p.bias != nullptr && n < p.N) b = HW::global_load_f32x4(p.bias + n);
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-              float t = v[e] * p.alpha + b[e];
-              v[e] = (p.act == 1 && t < 0.f) ? 0.f : t;
-            }
-          }
-          const ot4 h = {HW::template cvt<OT>(v[0]), HW::template cvt<OT>(v[1]),
-                         HW::template cvt<OT>(v[2]), HW::template cvt<OT>(v[3])};
-          HW::lds_write(ebase + (lane & 31) * RS + (i * 32 + 8 * vq + 4 * (lane >> 5)) * OB, h);
-        }
+      park_band<OT, RS, HW>(p, acc, j, ebase, lane, fused, bv);
       // a row is LPR lanes long; when that does not divide 64 (a wave tile 96 wide) the last
       // lanes of an instruction idle and the last instruction covers fewer rows
       constexpr bool EVEN = 64 % LPR == 0 && 32 % RPI == 0;

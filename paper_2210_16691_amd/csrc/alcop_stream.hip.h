@@ -239,37 +239,19 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
       // ---- epilogue of a tile (Table 1, epilogue term), overlapped with the producers' loads of
       // the following tiles: convert, transpose one 32-row band at a time through this wave's own
       // staging area, store whole 128-byte lines
+      f32x4 bv[TN * 4];
+      if (fused) load_bias<TN, HW>(p, tn * BN + wn * WN, lane, bv);
       auto epilogue = [&](auto zero) __attribute__((always_inline)) {
         using OT = decltype(zero);
         constexpr int OBY = sizeof(OT);
         constexpr int RS = WN * OBY + 16;
         constexpr int LPR = WN * OBY / 16;
         constexpr int RPI = 64 / LPR;
-        typedef OT ot4 __attribute__((ext_vector_type(4)));
         const int m0 = tm * BM + wm * WM, n0 = tn * BN + wn * WN;
         char* Cb = (char*)p.C + (long)batch * p.strideC * OBY;
 #pragma unroll
         for (int jj = 0; jj < TM; jj++) {
-#pragma unroll
-          for (int i = 0; i < TN; i++)
-#pragma unroll
-            for (int vq = 0; vq < 4; vq++) {
-              f32x4 v = {acc[i][jj][4 * vq + 0], acc[i][jj][4 * vq + 1], acc[i][jj][4 * vq + 2],
-                         acc[i][jj][4 * vq + 3]};
-              if (fused) {
-                const int n = n0 + i * 32 + 8 * vq + 4 * (lane >> 5);
-                f32x4 bv = {0.f, 0.f, 0.f, 0.f};
-                if (p.bias != nullptr && n < p.N) bv = HW::global_load_f32x4(p.bias + n);
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                  float t = v[e] * p.alpha + bv[e];
-                  v[e] = (p.act == 1 && t < 0.f) ? 0.f : t;
-                }
-              }
-              const ot4 h = {HW::template cvt<OT>(v[0]), HW::template cvt<OT>(v[1]),
-                             HW::template cvt<OT>(v[2]), HW::template cvt<OT>(v[3])};
-              HW::lds_write(ebase + (lane & 31) * RS + (i * 32 + 8 * vq + 4 * (lane >> 5)) * OBY, h);
-            }
+          park_band<OT, RS, HW>(p, acc, jj, ebase, lane, fused, bv);
           // a row is LPR lanes long; when that does not divide 64 (a wave tile 96 wide) the last
           // lanes of an instruction idle and the last instruction covers fewer rows
           constexpr bool EVEN = 64 % LPR == 0 && 32 % RPI == 0;
