@@ -220,13 +220,12 @@ int alcop_conv2d_igemm_dilated(const void* x, const void* w, void* y, int N, int
  * Operands the pipelined loops cannot take as they are (paper Sec. 4.2: a pipeline stage is
  * filled by asynchronous copies; here they move 16-byte chunks, hence the alignment rules of
  * alcop_gemm): N or K not a multiple of 8, M not a multiple of 8 with transA, leading dimensions,
- * batch strides or base addresses that are not 16-byte aligned.  A, B (and the bias) are first
- * copied into `workspace` with every extent rounded up to 8 elements and the tails zero-filled,
- * the product is computed there by the ordinary kernels (same schedules, same k order; the extra
- * k terms are exact zeros, so every valid element equals what an aligned call on the same values
- * returns), and the valid M x N part is copied to C element by element; bytes of C outside the
- * valid elements (row padding) are not touched.  Three small copy kernels besides the product:
- * meant for odd shapes, not for speed.
+ * batch strides or base addresses that are not 16-byte aligned.  Those of A, B (and the bias) that
+ * break the rules are copied into `workspace`, all in one launch, with every extent rounded up to
+ * 8 elements and the tails zero-filled; the ordinary kernels compute the product there (same
+ * schedules, same k order; the extra k terms are exact zeros, so every valid element equals what an
+ * aligned call on the same values returns) and store the valid M x N part straight to C; bytes of C
+ * outside the valid elements (row padding) are not touched.  One small copy kernel besides the product.
  *   A, B, C: DEVICE pointers aligned to their element size; lda, ldb, ldc, strides in elements,
  *     any value allowed by the shape (lda >= K or M, ...); batch = 1 with strides 0 is a GEMM.
  *   ep: host, may be NULL; ep->bias: DEVICE pointer to N fp32 values, 4-byte aligned.
@@ -246,11 +245,12 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
 
 /*
  * The same for a convolution whose channel counts are not multiples of 8 (an RGB stem: C = 3) or
- * whose tensors are not 16-byte aligned: x (NHWC) is copied to C rounded up to 8 channels, the
- * weights ([R][S][C][K]) to C and K rounded up, the convolution runs on the padded tensors
- * (zero channels add exact zeros) and the K valid channels of every output pixel are copied to
- * y (NPQK, dense).  Geometry, dilation and ep as for alcop_conv2d_igemm_dilated; sched: a
- * schedule for the padded problem or NULL.  workspace: at least
+ * whose tensors are not 16-byte aligned: x (NHWC) and the weights ([R][S][C][K]) are copied to an
+ * image of 16-byte chunks (C rounded up to 8 channels, or, with a NULL schedule and few channels,
+ * several pixels or a whole filter row per chunk: fewer zeros to multiply), the convolution runs on
+ * the padded tensors (the padding adds exact zeros) and the K valid channels of every output pixel
+ * are stored to y (NPQK, dense).  Geometry, dilation and ep as for alcop_conv2d_igemm_dilated;
+ * sched: a schedule for the problem padded to C and K rounded up to 8, or NULL.  workspace: at least
  * alcop_conv2d_unaligned_workspace_bytes(...) bytes, otherwise as above.
  */
 size_t alcop_conv2d_unaligned_workspace_bytes(int N, int H, int W, int C, int K, int R, int S,

@@ -57,6 +57,9 @@ struct Call {
   // conv geometry
   int cN, cH, cW, cC, cK, cR, cS, csh, csw, cph, cpw, cP, cQ;
   int cdh, cdw;   // dilation
+  int cPix;       // elements between pixels of x if not cC (0)
+  // C without 16-byte chunks: its valid rows and columns if not M and N (0), any element alignment
+  int Mv, Nv, c_any;
   // fused epilogue
   float alpha;
   const void* bias;
@@ -245,21 +248,22 @@ int check_call(const Call& c)
   if (!c.A || !c.B || !c.C) return ALCOP_ERR_NULL;
   int rc = check_problem(problem_of(c));
   if (rc) return rc;
-  if (!aligned16(c.A) || !aligned16(c.B) || !aligned16(c.C)) return ALCOP_ERR_ALIGN;
+  if (!aligned16(c.A) || !aligned16(c.B) || (!c.c_any && !aligned16(c.C))) return ALCOP_ERR_ALIGN;
   if (c.bias && !aligned16(c.bias)) return ALCOP_ERR_ALIGN;
   if (c.act != 0 && c.act != 1) return ALCOP_ERR_UNSUPPORTED;
   if (c.op == ALCOP_OP_CONV2D) {
     if (c.cR <= 0 || c.cS <= 0 || c.csh <= 0 || c.csw <= 0 || c.cph < 0 || c.cpw < 0 ||
         c.cP <= 0 || c.cQ <= 0 || c.cC % 8 != 0)
       return ALCOP_ERR_SHAPE;
-    const double xbytes = 2.0 * c.cN * c.cH * c.cW * c.cC;
+    const double xbytes = 2.0 * c.cN * c.cH * c.cW * (c.cPix ? c.cPix : c.cC);
     if (xbytes >= 2147483648.0) return ALCOP_ERR_SIZE;
     return ALCOP_OK;
   }
-  if ((c.lda | c.ldb | c.ldc) & 7) return ALCOP_ERR_ALIGN;
-  if (c.batch > 1 && ((c.strideA | c.strideB | c.strideC) & 7)) return ALCOP_ERR_ALIGN;
+  if ((c.lda | c.ldb | (c.c_any ? 0 : c.ldc)) & 7) return ALCOP_ERR_ALIGN;
+  if (c.batch > 1 && ((c.strideA | c.strideB | (c.c_any ? 0 : c.strideC)) & 7)) return ALCOP_ERR_ALIGN;
   if (c.strideA < 0 || c.strideB < 0 || c.strideC < 0) return ALCOP_ERR_SHAPE;
-  if (c.lda < (c.transA ? c.M : c.K) || c.ldb < (c.transB ? c.K : c.N) || c.ldc < c.N)
+  if (c.lda < (c.transA ? c.M : c.K) || c.ldb < (c.transB ? c.K : c.N) ||
+      c.ldc < (c.c_any ? c.Nv : c.N))
     return ALCOP_ERR_SHAPE;
   if (c.lda >= (1L << 30) || c.ldb >= (1L << 30) || c.ldc >= (1L << 30)) return ALCOP_ERR_SIZE;
   return ALCOP_OK;
@@ -288,7 +292,7 @@ struct Patch {
 };
 int patch_of(const Call& c, const alcop_sched& s, const KernelEntry* e, Patch* out)
 {
-  if (c.op != ALCOP_OP_CONV2D || c.csh != 1 || c.csw != 1 || c.cdh != 1 || c.cdw != 1)
+  if (c.op != ALCOP_OP_CONV2D || c.csh != 1 || c.csw != 1 || c.cdh != 1 || c.cdw != 1 || c.cPix != 0)
     return ALCOP_ERR_SCHED;
   Patch pt;
   pt.wp = c.cW + 2 * c.cpw;                                    // row length of the padded image
@@ -362,6 +366,9 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
   p.strideB = c.strideB;
   p.strideC = c.strideC;
   p.out_dtype = (int)c.out;
+  p.Mv = c.Mv ? c.Mv : c.M;
+  p.Nv = c.Nv ? c.Nv : c.N;
+  p.c_any = c.c_any;
   p.ntm = (c.M + s.bm - 1) / s.bm;
   p.ntn = (c.N + s.bn - 1) / s.bn;
   p.raster = s.raster;
@@ -390,7 +397,8 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
     p.cpw = c.cpw;
     p.cdh = c.cdh;
     p.cdw = c.cdw;
-    p.a_span = (unsigned)(2L * c.cN * c.cH * c.cW * c.cC);
+    p.cPix = c.cPix ? c.cPix : c.cC;
+    p.a_span = (unsigned)(2L * c.cN * c.cH * c.cW * p.cPix);
     if (e->am == 3) {
       Patch pt;
       if (patch_of(c, s, e, &pt) != ALCOP_OK) return ALCOP_ERR_SCHED;
@@ -794,41 +802,114 @@ size_t unaligned_layout(double a_elems, double b_elems, double c_elems, long n8,
   return off[3] + r256(4.0 * (double)n8);
 }
 
-PackParams pack2d(const void* src, void* dst, int rows, int cols, long s_batch, long s_row, int rows_d,
-                  int cols_d, long d_batch, long d_row, int esize)
-{
-  PackParams p;
-  p.src = src;
-  p.dst = dst;
-  p.rows = rows;
-  p.cols = cols;
-  p.s_batch = s_batch;
-  p.s_row = s_row;
-  p.rows_d = rows_d;
-  p.cols_d = cols_d;
-  p.d_batch = d_batch;
-  p.d_row = d_row;
-  p.esize = esize;
-  return p;
-}
-
 bool elem_aligned(const void* p, int esize) { return (reinterpret_cast<uintptr_t>(p) & (uintptr_t)(esize - 1)) == 0; }
 
-// Padded bias (N8 floats, zero tail) if the epilogue has one; fills the inner call's epilogue.
-int pack_epilogue(const alcop_epilogue* ep, int N, char* ws_bias, Call* inner, hipStream_t st)
+// Collects the segments of a call's one pack launch.
+struct Packer {
+  PackParams p;
+  unsigned blocks = 0;
+  bool too_big = false;
+  Packer() { std::memset(&p, 0, sizeof(p)); }
+
+  // rows_d rows of cpr chunks per batch entry, dense at dst
+  PackSeg& add(int kind, const void* src, void* dst, int batch, long rows_d, long cpr, int esize)
+  {
+    PackSeg& g = p.seg[p.nseg++];
+    const double chunks = (double)batch * rows_d * cpr;
+    if (chunks >= 2147483648.0) too_big = true;
+    g.src = src;
+    g.dst = dst;
+    g.kind = kind;
+    g.esize = esize;
+    g.first = blocks;
+    g.chunks = too_big ? 0 : (uint32_t)chunks;
+    g.cpr = FastDiv::of((uint32_t)cpr);
+    g.rows_d = FastDiv::of((uint32_t)rows_d);
+    g.rg = FastDiv::of(1);
+    blocks += (g.chunks + PACK_THREADS - 1) / PACK_THREADS;
+    return g;
+  }
+  // batch matrices of rows x cols (cols contiguous, pitch s_row) -> rows_d x cols_d
+  void matrix(const void* src, void* dst, int batch, int rows, int cols, long s_batch, long s_row, int rows_d,
+              int cols_d, int esize)
+  {
+    PackSeg& g = add(PACK_MAT, src, dst, batch, rows_d, cols_d / (16 / esize), esize);
+    g.rg = FastDiv::of((uint32_t)rows_d);
+    g.nq = 1;
+    g.nm = rows;
+    g.cols = cols;
+    g.s_batch = s_batch;
+    g.s_row = s_row;
+  }
+  int launch(hipStream_t st) const
+  {
+    if (too_big) return ALCOP_ERR_SIZE;
+    if (p.nseg == 0) return ALCOP_OK;
+    return launch_pack(p, blocks, st) == hipSuccess ? ALCOP_OK : ALCOP_ERR_LAUNCH;
+  }
+};
+
+// The fused epilogue of the inner call; a bias the kernels cannot read as it is (four values at a
+// time, up to the padded N) joins the pack launch.
+int pack_epilogue(const alcop_epilogue* ep, int N, char* ws_bias, Call* inner, Packer* pk)
 {
   if (!ep) return ALCOP_OK;
   inner->alpha = ep->alpha;
   inner->act = ep->act;
   if (ep->act != 0 && ep->act != 1) return ALCOP_ERR_UNSUPPORTED;
-  if (ep->bias) {
-    if (!elem_aligned(ep->bias, 4)) return ALCOP_ERR_ALIGN;
-    const int n8 = (int)r8(N);
-    if (launch_pack(pack2d(ep->bias, ws_bias, 1, N, 0, 0, 1, n8, 0, n8, 4), 1, st) != hipSuccess)
-      return ALCOP_ERR_LAUNCH;
-    inner->bias = ws_bias;
-  }
+  if (!ep->bias) return ALCOP_OK;
+  if (!elem_aligned(ep->bias, 4)) return ALCOP_ERR_ALIGN;
+  inner->bias = ep->bias;
+  if (aligned16(ep->bias) && N % 8 == 0) return ALCOP_OK;
+  pk->matrix(ep->bias, ws_bias, 1, 1, N, 0, N, 1, (int)r8(N), 4);
+  inner->bias = ws_bias;
   return ALCOP_OK;
+}
+
+// How a convolution whose channel count is not a multiple of 8 is laid out for the gather.
+//   pixel form   C padded to 8 channels: R * S taps of 8 channels.
+//   pair form    C <= 4 and horizontal stride a multiple of px = 8 / Cg pixels (Cg = 1, 2, 4 >= C):
+//                the left padding is made explicit, px pixels share a 16-byte chunk, and since every
+//                window starts on a chunk its whole filter row is ceil(S / px) consecutive chunks.
+//                The gather sees a filter S = 1 wide with that many channels, whose windows overlap.
+//   window form  one window per output column: the S * C elements of a filter row, padded to 8.
+// The pixel form multiplies 8 / C times as much padding as data: a 7 x 7 stem on RGB reduces over
+// 392 elements instead of 147 (pair form: 224).  Picked by bytes: the image is written and read
+// once at about 4 TB/s, the gather moves M * K elements from L2 to LDS at about 15 TB/s.
+struct XForm {
+  int kind;               // PACK_PIX or PACK_WIN
+  int cg, px, chunks;     // pixel, pair: elements per pixel, pixels per chunk; chunks per filter row (pair)
+  int width;              // columns of the image the gather sees
+  int pix;                // elements between them
+  int chans, taps;        // channels per tap, taps per filter row
+  int stride, pad;        // horizontal stride and padding left for the gather
+  bool padded;            // left padding is part of the image
+};
+
+XForm choose_xform(int N, int H, int W, int C, int R, int S, int sw, int pw, int dw, long Q, long M, double x_room)
+{
+  const int c8 = (int)r8(C);
+  const XForm plain{PACK_PIX, c8, 1, 0, W, c8, c8, S, sw, pw, false};
+  auto bytes = [&](const XForm& f) { return 2.0 * N * H * f.width * f.pix; };
+  auto cost = [&](const XForm& f) { return 2.0 * bytes(f) / 4e12 + 2.0 * M * R * f.taps * f.chans / 15e12; };
+  XForm best = plain;
+  if (C % 8 == 0 || dw != 1) return plain;
+  auto consider = [&](const XForm& f) {
+    if (f.width < 1 || bytes(f) >= 2147483648.0 || r256(bytes(f)) > x_room) return;
+    if (cost(f) < cost(best)) best = f;
+  };
+  if (C <= 4) {
+    const int cg = C <= 1 ? 1 : C <= 2 ? 2 : 4, px = 8 / cg;
+    if (sw % px == 0) {
+      const int ch = (S + px - 1) / px;
+      const long last = (Q - 1) * (sw / px) + ch;          // chunks a row must have
+      if (last < 0x3fffffff)
+        consider(XForm{PACK_PIX, cg, px, ch, (int)last, 8, 8 * ch, 1, sw / px, 0, true});
+    }
+  }
+  if ((double)S * C < 65536.0 && Q < 0x3fffffff)
+    consider(XForm{PACK_WIN, 0, 0, 0, (int)Q, (int)r8((long)S * C), (int)r8((long)S * C), 1, 1, 0, true});
+  return best;
 }
 
 }  // namespace
@@ -1122,25 +1203,31 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
   if (need == 0 || workspace_bytes < need) return ALCOP_ERR_SIZE;
   char* ws = (char*)workspace;
   hipStream_t st = (hipStream_t)hip_stream;
-  // padded operands, each batch entry a dense matrix
-  const int a_rows = transA ? K : M, a_cols = transA ? M : K, a_rd = transA ? k8 : m8, a_cd = transA ? m8 : k8;
+  // An operand is used where it lies if its chunks are whole and aligned; otherwise it is padded
+  // into the workspace, each batch entry a dense matrix.  Rows of A (stored M x K) need no padding.
+  auto in_place = [&](const void* p, long ld, long stride, int rows, int cols) {
+    return aligned16(p) && ld % 8 == 0 && (batch == 1 || stride % 8 == 0) && cols % 8 == 0 && K % 8 == 0 &&
+           2.0 * ((double)rows * ld) < 2147483648.0;
+  };
+  const int a_rows = transA ? K : M, a_cols = transA ? M : K, a_rd = transA ? k8 : M, a_cd = transA ? m8 : k8;
   const int b_rows = transB ? N : K, b_cols = transB ? K : N, b_rd = transB ? n8 : k8, b_cd = transB ? k8 : n8;
-  Call c = gemm_call(batch > 1 ? ALCOP_OP_BMM : ALCOP_OP_GEMM, ws + off[0], ws + off[1], ws + off[2],
-                     batch, m8, n8, k8, a_cd, b_cd, n8, (long)m8 * k8, (long)k8 * n8, (long)m8 * n8,
-                     transA, transB, in, out);
-  int rc = pack_epilogue(ep, N, ws + off[3], &c, st);
+  const bool a_ok = in_place(A, lda, strideA, a_rows, a_cols);
+  const bool b_ok = in_place(B, ldb, strideB, b_rows, b_cols) && N % 8 == 0;
+  Call c = gemm_call(batch > 1 ? ALCOP_OP_BMM : ALCOP_OP_GEMM, a_ok ? A : ws + off[0], b_ok ? B : ws + off[1], C,
+                     batch, transA ? m8 : M, n8, k8, a_ok ? lda : a_cd, b_ok ? ldb : b_cd, ldc,
+                     a_ok ? strideA : (long)a_rd * a_cd, b_ok ? strideB : (long)b_rd * b_cd, strideC, transA,
+                     transB, in, out);
+  c.Mv = M;
+  c.Nv = N;
+  c.c_any = !(aligned16(C) && N % 8 == 0 && ldc % 8 == 0 && (batch == 1 || strideC % 8 == 0));
+  Packer pk;
+  int rc = pack_epilogue(ep, N, ws + off[3], &c, &pk);
   if (rc) return rc;
-  if (launch_pack(pack2d(A, ws + off[0], a_rows, a_cols, strideA, lda, a_rd, a_cd, (long)m8 * k8, a_cd, 2),
-                  batch, st) != hipSuccess ||
-      launch_pack(pack2d(B, ws + off[1], b_rows, b_cols, strideB, ldb, b_rd, b_cd, (long)k8 * n8, b_cd, 2),
-                  batch, st) != hipSuccess)
-    return ALCOP_ERR_LAUNCH;
-  rc = run(c, sched, hip_stream);
+  if (!a_ok) pk.matrix(A, ws + off[0], batch, a_rows, a_cols, strideA, lda, a_rd, a_cd, 2);
+  if (!b_ok) pk.matrix(B, ws + off[1], batch, b_rows, b_cols, strideB, ldb, b_rd, b_cd, 2);
+  rc = pk.launch(st);
   if (rc) return rc;
-  if (launch_unpack(pack2d(ws + off[2], C, M, N, (long)m8 * n8, n8, m8, n8, strideC, ldc, osz), batch, st) !=
-      hipSuccess)
-    return ALCOP_ERR_LAUNCH;
-  return ALCOP_OK;
+  return run(c, sched, hip_stream);
 }
 
 // Output extent of the convolution, or false if the arguments do not describe one.
@@ -1194,23 +1281,72 @@ int alcop_conv2d_igemm_unaligned(const void* x, const void* w, void* y, int N, i
   if (need == 0 || workspace_bytes < need) return ALCOP_ERR_SIZE;
   char* ws = (char*)workspace;
   hipStream_t st = (hipStream_t)hip_stream;
+  // the image the gather sees; an explicit schedule is one for the pixel form
+  const bool x_ok = aligned16(x) && C % 8 == 0, w_ok = aligned16(w) && C % 8 == 0 && K % 8 == 0;
+  const double x_room = (double)(need - r256(2.0 * R * S * c8 * k8) - r256(4.0 * k8));
+  const bool automatic = !sched || sched->bm == 0;
+  const XForm f = automatic ? choose_xform(N, H, W, C, R, S, stride_w, pad_w, dil_w, Q, outputs, x_room)
+                            : choose_xform(N, H, W, c8, R, S, stride_w, pad_w, dil_w, Q, outputs, 0.0);
+  const size_t w_off = f.padded ? r256(2.0 * N * H * f.width * f.pix) : off[1];
+  const size_t b_off = f.padded ? w_off + r256(2.0 * R * f.chans * k8) : off[3];
+  if (b_off + r256(4.0 * k8) > need) return ALCOP_ERR_SIZE;   // cannot happen: forms are chosen to fit
   Call c;
-  int rc = conv_call(&c, ws + off[0], ws + off[1], ws + off[2], N, H, W, c8, k8, R, S, stride_h, stride_w,
+  int rc = conv_call(&c, x_ok ? x : ws, w_ok ? w : ws + w_off, y, N, H, W, c8, k8, R, S, stride_h, stride_w,
                      pad_h, pad_w, in, out, 0, dil_h, dil_w);
   if (rc) return rc;
-  rc = pack_epilogue(ep, K, ws + off[3], &c, st);
+  c.Nv = K;
+  c.ldc = K;
+  c.c_any = !(aligned16(y) && K % 8 == 0);
+  if (f.padded) {
+    c.K = R * f.chans;
+    c.lda = c.K;
+    c.cW = f.width;
+    c.cC = f.chans;
+    c.cPix = f.pix;
+    c.cS = 1;
+    c.csw = f.stride;
+    c.cpw = 0;
+  }
+  Packer pk;
+  rc = pack_epilogue(ep, K, ws + b_off, &c, &pk);
   if (rc) return rc;
-  // x: pixels x C -> pixels x C8; w: (R*S) matrices of C x K -> C8 x K8
-  if (launch_pack(pack2d(x, ws + off[0], (int)pixels, C, 0, C, (int)pixels, c8, 0, c8, 2), 1, st) != hipSuccess ||
-      launch_pack(pack2d(w, ws + off[1], C, K, (long)C * K, K, c8, k8, (long)c8 * k8, k8, 2), R * S, st) !=
-          hipSuccess)
-    return ALCOP_ERR_LAUNCH;
-  rc = run(c, sched, hip_stream);
+  if (!x_ok) {
+    PackSeg& g = pk.add(f.kind, x, ws, 1, f.padded ? (long)N * H : pixels, f.padded ? (long)f.width * f.pix / 8 : c8 / 8, 2);
+    g.s_row = f.padded ? (long)W * C : C;
+    if (!f.padded) {            // pixels x C -> pixels x C8: a plain matrix
+      g.kind = PACK_MAT;
+      g.rg = g.rows_d;
+      g.nq = 1;
+      g.nm = (int)pixels;
+      g.cols = C;
+    } else {
+      g.rg = FastDiv::of((uint32_t)(f.pix / 8));
+      g.width = W;
+      g.chans = C;
+      g.pad = pad_w;
+      g.cg = f.cg;
+      g.stride = stride_w;
+      g.win = S * C;
+    }
+  }
+  if (!w_ok) {
+    if (!f.padded) {            // (R*S) matrices of C x K -> C8 x K8
+      pk.matrix(w, ws + w_off, R * S, C, K, (long)C * K, K, c8, k8, 2);
+    } else {                    // R matrices of S * C rows, in groups of Cg (pair form) or dense
+      PackSeg& g = pk.add(PACK_MAT, w, ws + w_off, R, f.chans, k8 / 8, 2);
+      const bool pair = f.kind == PACK_PIX;
+      g.rg = FastDiv::of((uint32_t)(pair ? f.cg : f.chans));
+      g.nq = pair ? S : 1;
+      g.nm = pair ? C : S * C;
+      g.cols = K;
+      g.s_batch = (long)S * C * K;
+      g.s_grp = (long)C * K;
+      g.s_row = K;
+    }
+  }
+  rc = pk.launch(st);
   if (rc) return rc;
-  if (launch_unpack(pack2d(ws + off[2], y, (int)outputs, K, 0, k8, (int)outputs, k8, 0, K, osz), 1, st) !=
-      hipSuccess)
-    return ALCOP_ERR_LAUNCH;
-  return ALCOP_OK;
+  return run(c, sched, hip_stream);
 }
 
 int alcop_sched_supported(const alcop_problem* prob, const alcop_sched* sched)

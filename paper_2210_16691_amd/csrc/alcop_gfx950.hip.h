@@ -120,7 +120,16 @@ struct Gfx950 {
   {
     return *(const f32x4*)ptr;
   }
-  // element-wise accesses of the pack / unpack kernels (any element-aligned address)
+  // accesses at any element-aligned address: the pack kernel and the epilogue of products whose C
+  // is not made of 16-byte chunks
+  typedef u32x4 u32x4_any __attribute__((aligned(2)));
+  __device__ static __forceinline__ u32x4 global_load16_any(const void* ptr) { return *(const u32x4_any*)ptr; }
+  __device__ static __forceinline__ void global_store16_any(void* ptr, u32x4 v)
+  {
+    __builtin_nontemporal_store(v, (u32x4_any*)ptr);
+  }
+  // 16-byte store whose line stays in the caches: the next kernel reads it
+  __device__ static __forceinline__ void global_store16_keep(void* ptr, u32x4 v) { *(u32x4*)ptr = v; }
   __device__ static __forceinline__ uint16_t global_load_u16(const void* ptr) { return *(const uint16_t*)ptr; }
   __device__ static __forceinline__ uint32_t global_load_u32(const void* ptr) { return *(const uint32_t*)ptr; }
   __device__ static __forceinline__ void global_store_u16(void* ptr, uint16_t v) { *(uint16_t*)ptr = v; }

@@ -54,10 +54,15 @@ struct Params {
   int lda, ldb, ldc;           // elements (host guarantees the byte spans fit 31 bits)
   long strideA, strideB, strideC;
   int out_dtype;               // 0 f16, 1 bf16, 2 f32
+  // rows and columns of C that exist (M and N unless the operands are zero-padded images), and
+  // whether C's rows or its columns' extent are not 16-byte aligned
+  int Mv, Nv, c_any;
   int ntm, ntn;                // tile counts
   int raster, group_m;         // block -> tile order
   // convolution geometry (AM != 0): x is NHWC, A rows are (img, p, q)
   int cH, cW, cC, cP, cQ, cS, csh, csw, cph, cpw;
+  int cPix;                    // elements between neighbouring pixels of x: cC, or less where the
+                               // channels of a tap span several pixels (windows that overlap)
   int cdh, cdw;                // dilation: filter tap (r, s) reads row ih0 + r * cdh, column iw0 + s * cdw
   unsigned a_span, b_span;     // conv: bytes of x; unused otherwise
   // third pipeline level (HBM -> L2): every wave touches lines of k-tile kt + pf_dist when it
@@ -375,6 +380,34 @@ __device__ __forceinline__ void park_band(const Params& p, f32x16 (&acc)[TN][TM]
   }
 }
 
+// Stores one 16-byte chunk of a row of C, columns n .. of it.  C's rows start at multiples of 16
+// bytes and hold whole chunks, or (c_any) anywhere: then a chunk goes out at its element-aligned
+// address, and the row's last, partial chunk element by element.  A copy of C through an aligned
+// image cost more than the product it followed (51 MB of a 7x7 stem: 37 us).
+template <class OT, class HW>
+__device__ __forceinline__ void store_chunk(const Params& p, char* dst, int n, u32x4 v)
+{
+  if (!p.c_any) {
+    if (n < p.N) HW::global_store16(dst, v);
+    return;
+  }
+  constexpr int PER = 16 / (int)sizeof(OT);
+  if (n + PER <= p.Nv) {
+    HW::global_store16_any(dst, v);
+  } else {
+#pragma unroll 1
+    for (; n < p.Nv; n++, dst += sizeof(OT)) {     // the low element of v, then v shifted down by it
+      if constexpr (sizeof(OT) == 2) {
+        HW::global_store_u16(dst, (uint16_t)v[0]);
+        v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
+      } else {
+        HW::global_store_u32(dst, v[0]);
+        v = u32x4{v[1], v[2], v[3], 0u};
+      }
+    }
+  }
+}
+
 template <class C, class HW>
 __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
 {
@@ -495,7 +528,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
       const int pp = pq / p.cQ, qq = pq - pp * p.cQ;
       ih0[i] = (m < p.M) ? pp * p.csh - p.cph : -0x40000000;
       iw0[i] = qq * p.csw - p.cpw;
-      coff[i] = (uint32_t)((((img * p.cH + (pp * p.csh - p.cph)) * p.cW) + iw0[i]) * p.cC * 2 +
+      coff[i] = (uint32_t)((((img * p.cH + (pp * p.csh - p.cph)) * p.cW) + iw0[i]) * p.cPix * 2 +
                            (C::AM == 2 ? 0 : c * 16));
     }
   }
@@ -546,7 +579,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
     if constexpr (C::AM == 0)
       st_ka = st_live ? (uint32_t)kt * la.kstep : 0x80000000u;
     else if constexpr (C::AM != 3)
-      st_tap = (uint32_t)(((crd * p.cW + csd) * p.cC + cc0) * 2);
+      st_tap = (uint32_t)(((crd * p.cW + csd) * p.cPix + cc0) * 2);
     if constexpr (C::AM == 2) a_in_k = kt * BK + a_k8 < Kb;
     st_kb = st_live ? (uint32_t)kt * lb.kstep : 0x80000000u;
   };
@@ -847,7 +880,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
         const u32x4 v = HW::lds_read16(ebase + r * RS + c16 * 16);
         int m = m0 + j * 32 + r;
         const int n = n0 + c16 * (16 / OB);
-        bool row_ok = m < p.M;
+        bool row_ok = m < p.Mv;
         if constexpr (C::AM == 3) {
           // position of the padded output space -> output pixel; columns >= Q are not stored
           const int jj = p_j0 + wm * WM + j * 32 + r;
@@ -855,8 +888,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
           row_ok = pp < p.cP && qq < p.cQ;
           m = (p_img * p.cP + pp) * p.cQ + qq;
         }
-        if (lane_ok && row_ok && n < p.N)
-          HW::global_store16(Cb + ((long)m * p.ldc + n) * OB, v);
+        if (lane_ok && row_ok) store_chunk<OT, HW>(p, Cb + ((long)m * p.ldc + n) * OB, n, v);
       }
     }
   };

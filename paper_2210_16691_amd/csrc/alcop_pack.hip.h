@@ -2,11 +2,17 @@
 // multiple of 8, row pitches or base addresses that are not 16-byte aligned, a channel count such
 // as 3.  The loops move 16-byte chunks (paper Sec. 4.2: the asynchronous copies of a pipeline
 // stage; here one buffer_load_dwordx4 ... lds per lane), so such operands are first copied into a
-// workspace with every extent rounded up to 8 elements and the tail zero-filled, the product is
-// computed there by the ordinary kernels, and the valid part of the result is copied out.
-// Zero padding leaves every valid output element unchanged: the extra k terms are exact zeros.
+// workspace with every extent rounded up to 8 elements and the tail zero-filled, and the ordinary
+// kernels compute the product there; their epilogue stores the valid part of the result straight
+// to C (Params::c_any).  Zero padding leaves every valid output element unchanged: the extra k
+// terms are exact zeros.
 //
-// Like the main loops, the two kernels take the hardware operations from a policy class.
+// ONE launch copies all operands of a call (A and B, or x and w, and the bias): a call on odd
+// sizes costs two launches.  With a launch per operand and a copy of C behind the product it was
+// five, which is what a small product of that kind took its time for (1021 x 1531 x 767 bf16:
+// 24.9 us, of which the product 6.9).
+//
+// Like the main loops, the kernel takes the hardware operations from a policy class.
 #pragma once
 #include <stdint.h>
 
@@ -14,70 +20,121 @@
 
 namespace alcop {
 
-struct PackParams {
+// n / d for n < 2^31 without a divide: q = (n + mulhi(n, mul)) >> shift.
+struct FastDiv {
+  uint32_t d, mul, shift;
+  static FastDiv of(uint32_t d)
+  {
+    FastDiv f;
+    f.d = d;
+    f.shift = 0;
+    while ((1ull << f.shift) < d) f.shift++;
+    f.mul = (uint32_t)(((1ull << 32) * ((1ull << f.shift) - d)) / d + 1);
+    return f;
+  }
+  __device__ __forceinline__ uint32_t div(uint32_t n) const
+  {
+    return (uint32_t)(((uint64_t)n * mul) >> 32) + n >> shift;
+  }
+};
+
+// What a segment's 16-byte chunks hold.
+enum {
+  PACK_MAT = 0,   // a matrix: rows of `cols` elements, zero beyond; rows may come in groups of rg
+                  // of which the first nm (and the first nq groups) exist in the source
+  PACK_PIX = 1,   // an image row as pixels of cg elements (a power of two <= 8): `chans` channels
+                  // of a pixel and zeros; `pad` zero pixels before the first
+  PACK_WIN = 2,   // an image row as one window of cu elements per output column: the `win` elements
+                  // its filter row covers (all taps and channels, contiguous in the source)
+};
+
+struct PackSeg {
   const void* src;
   void* dst;
-  int rows, cols;        // extent of the valid data (both kernels)
-  long s_batch, s_row;   // source strides in elements; grid.y = batch entry
-  int rows_d, cols_d;    // extent of the padded image: pack writes all of it, unpack reads the
-                         // valid part of it; cols_d * esize is a multiple of 16
-  long d_batch, d_row;   // destination strides in elements
-  int esize;             // bytes per element: 2 or 4
+  int kind, esize;        // bytes per element: 2, or 4 (PACK_MAT only)
+  uint32_t first;         // first block of this segment
+  uint32_t chunks;        // 16-byte chunks in all: batch * rows_d * cpr
+  FastDiv cpr, rows_d;    // chunks per destination row; destination rows per batch entry
+  FastDiv rg;             // PACK_MAT: rows per group; PACK_WIN: chunks per window
+  long s_batch, s_grp, s_row;   // source strides in elements: batch entry, row group, row
+  int nq, nm, cols;       // PACK_MAT: valid groups, rows of a group, columns
+  int width, chans;       // PACK_PIX / PACK_WIN: pixels of a source row, channels
+  int pad, cg, stride;    // ... zero pixels on the left; elements per pixel; columns per output
+  int win;
 };
 
 constexpr int PACK_THREADS = 256;
+constexpr int PACK_SEGS = 3;
 
-// dst[b][r][c] = r < rows && c < cols ? src[b][r][c] : 0 for r < rows_d, c < cols_d.  The source
-// needs element alignment only (element-wise loads); the destination rows are 16-byte aligned and
-// one thread writes one 16-byte chunk.  grid.x covers rows_d * cols_d * esize / 16 threads.
+struct PackParams {
+  PackSeg seg[PACK_SEGS];
+  int nseg;
+};
+
+// Elements [lo, hi) of the eight (four) at s that exist; the others are zero.
 template <class HW>
-__global__ void __launch_bounds__(PACK_THREADS) alcop_pack(const PackParams p)
+__device__ __forceinline__ u32x4 load_chunk(const char* s, int esize, int lo, int hi)
 {
-  const int per = 16 / p.esize, cpr = p.cols_d / per;
-  const long idx = (long)HW::block_x() * PACK_THREADS + HW::wave_id() * 64 + HW::lane_id();
-  if (idx >= (long)p.rows_d * cpr) return;
-  const int r = (int)(idx / cpr), c0 = (int)(idx - (long)r * cpr) * per;
-  const long b = (long)HW::block_y();
+  const int per = 16 / esize;
+  if (lo <= 0 && hi >= per) return HW::global_load16_any(s);
   u32x4 v = {0u, 0u, 0u, 0u};
-  if (r < p.rows) {
-    const char* s = (const char*)p.src + (b * p.s_batch + (long)r * p.s_row + c0) * p.esize;
-    if (p.esize == 2) {
-#pragma unroll
-      for (int e = 0; e < 8; e++)
-        if (c0 + e < p.cols) v[e >> 1] |= (uint32_t)HW::global_load_u16(s + 2 * e) << (16 * (e & 1));
-    } else {
-#pragma unroll
-      for (int e = 0; e < 4; e++)
-        if (c0 + e < p.cols) v[e] = HW::global_load_u32(s + 4 * e);
-    }
-  }
-  HW::global_store16((char*)p.dst + (b * p.d_batch + (long)r * p.d_row + c0) * p.esize, v);
-}
-
-// dst[b][r][c] = src[b][r][c] for r < rows, c < cols: the source is a padded image (16-byte
-// aligned rows, one 16-byte load per thread), the destination needs element alignment only.
-// grid.x covers rows * cols_d * esize / 16 threads.
-template <class HW>
-__global__ void __launch_bounds__(PACK_THREADS) alcop_unpack(const PackParams p)
-{
-  const int per = 16 / p.esize, cpr = p.cols_d / per;
-  const long idx = (long)HW::block_x() * PACK_THREADS + HW::wave_id() * 64 + HW::lane_id();
-  if (idx >= (long)p.rows * cpr) return;
-  const int r = (int)(idx / cpr), c0 = (int)(idx - (long)r * cpr) * per;
-  if (c0 >= p.cols) return;
-  const long b = (long)HW::block_y();
-  const char* s = (const char*)p.src + (b * p.s_batch + (long)r * p.s_row + c0) * p.esize;
-  const u32x4 v = __builtin_bit_cast(u32x4, HW::global_load_f32x4((const float*)s));
-  char* d = (char*)p.dst + (b * p.d_batch + (long)r * p.d_row + c0) * p.esize;
-  if (p.esize == 2) {
+  if (esize == 2) {
 #pragma unroll
     for (int e = 0; e < 8; e++)
-      if (c0 + e < p.cols) HW::global_store_u16(d + 2 * e, (uint16_t)(v[e >> 1] >> (16 * (e & 1))));
+      if (e >= lo && e < hi) v[e >> 1] |= (uint32_t)HW::global_load_u16(s + 2 * e) << (16 * (e & 1));
   } else {
 #pragma unroll
     for (int e = 0; e < 4; e++)
-      if (c0 + e < p.cols) HW::global_store_u32(d + 4 * e, v[e]);
+      if (e >= lo && e < hi) v[e] = HW::global_load_u32(s + 4 * e);
   }
+  return v;
+}
+
+// One thread writes one 16-byte chunk of one segment; the destinations are dense images.  Sources
+// need element alignment only.
+template <class HW>
+__global__ void __launch_bounds__(PACK_THREADS) alcop_pack(const PackParams p)
+{
+  const uint32_t bx = HW::block_x();
+  int k = 0;
+  if (p.nseg > 1 && bx >= p.seg[1].first) k = 1;
+  if (p.nseg > 2 && bx >= p.seg[2].first) k = 2;
+  const PackSeg& g = p.seg[k];
+  const uint32_t idx = (bx - g.first) * PACK_THREADS + (uint32_t)(HW::wave_id() * 64 + HW::lane_id());
+  if (idx >= g.chunks) return;
+  const uint32_t rr = g.cpr.div(idx);
+  const uint32_t c = idx - rr * g.cpr.d;
+  const uint32_t b = g.rows_d.div(rr);
+  const uint32_t r = rr - b * g.rows_d.d;
+  u32x4 v = {0u, 0u, 0u, 0u};
+  if (g.kind == PACK_MAT) {
+    const uint32_t q = g.rg.div(r);
+    const uint32_t m = r - q * g.rg.d;
+    if ((int)q < g.nq && (int)m < g.nm) {
+      const int c0 = (int)c * (16 / g.esize);
+      const long off = (long)b * g.s_batch + (long)q * g.s_grp + (long)m * g.s_row + c0;
+      v = load_chunk<HW>((const char*)g.src + off * g.esize, g.esize, 0, g.cols - c0);
+    }
+  } else if (g.kind == PACK_WIN) {
+    const uint32_t q = g.rg.div(c);
+    const int e0 = (int)(c - q * g.rg.d) * 8;
+    const int f = ((int)q * g.stride - g.pad) * g.chans + e0;         // element of the image row
+    const int end = g.width * g.chans - f;                            // elements left in the row
+    const int hi = (g.win - e0) < end ? (g.win - e0) : end;
+    v = load_chunk<HW>((const char*)g.src + ((long)r * g.s_row + f) * 2, 2, -f, hi);
+  } else {
+    const int px = 8 / g.cg;
+    const long row = (long)r * g.s_row;
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      const int ch = e & (g.cg - 1);
+      const int iw = (int)c * px + (int)((uint32_t)e / (uint32_t)g.cg) - g.pad;
+      if (ch < g.chans && (unsigned)iw < (unsigned)g.width)
+        v[e >> 1] |= (uint32_t)HW::global_load_u16((const char*)g.src + (row + (long)iw * g.chans + ch) * 2)
+                     << (16 * (e & 1));
+    }
+  }
+  HW::global_store16_keep((char*)g.dst + (size_t)idx * 16, v);
 }
 
 }  // namespace alcop

@@ -159,7 +159,7 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
           const int pp = pq / p.cQ, qq = pq - pp * p.cQ;
           ih0[i] = (m < p.M) ? pp * p.csh - p.cph : -0x40000000;
           iw0[i] = qq * p.csw - p.cpw;
-          coff[i] = (uint32_t)((((img * p.cH + (pp * p.csh - p.cph)) * p.cW) + iw0[i]) * p.cC * 2 + c * 16);
+          coff[i] = (uint32_t)((((img * p.cH + (pp * p.csh - p.cph)) * p.cW) + iw0[i]) * p.cPix * 2 + c * 16);
         }
         cs = cc0 = crd = csd = 0;
       }
@@ -179,7 +179,7 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
       const uint32_t voffA = voA | (tail ? tmA : 0u), voffB = voB | (tail ? tmB : 0u);
       const uint32_t ka = live ? (uint32_t)ikt * ksA : 0x80000000u;
       const uint32_t kb = live ? (uint32_t)ikt * ksB : 0x80000000u;
-      const uint32_t tap = (uint32_t)(((crd * p.cW + csd) * p.cC + cc0) * 2);
+      const uint32_t tap = (uint32_t)(((crd * p.cW + csd) * p.cPix + cc0) * 2);
 #pragma unroll
       for (int i = 0; i < NLA; i++) {
         if constexpr (C::AM == 0) {
@@ -268,7 +268,7 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
             const u32x4 v = HW::lds_read16(ebase + r * RS + c16 * 16);
             const int m = m0 + jj * 32 + r;
             const int n = n0 + c16 * (16 / OBY);
-            if (lane_ok && m < p.M && n < p.N) HW::global_store16(Cb + ((long)m * p.ldc + n) * OBY, v);
+            if (lane_ok && m < p.Mv) store_chunk<OT, HW>(p, Cb + ((long)m * p.ldc + n) * OBY, n, v);
           }
         }
       };

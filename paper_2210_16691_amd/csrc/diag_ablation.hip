@@ -185,8 +185,8 @@ int alcop_diag_time(int config, int drop, const void* A, const void* B, void* C,
   p.A = A;
   p.B = B;
   p.C = C;
-  p.M = M;
-  p.N = N;
+  p.M = p.Mv = M;
+  p.N = p.Nv = N;
   p.K = K;
   p.lda = K;
   p.ldb = N;

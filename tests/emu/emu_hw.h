@@ -492,6 +492,26 @@ struct Emu {
       fail("global load outside every operand (thread %d)", blk()->cur);
     return v;
   }
+  // 16-byte accesses at element-aligned addresses
+  static u32x4 global_load16_any(const void* ptr)
+  {
+    u32x4 v = {0, 0, 0, 0};
+    if ((uintptr_t)ptr % 2) fail("16-byte load from an odd address (thread %d)", blk()->cur);
+    if (in_buffer(ptr, 16, false))
+      memcpy(&v, ptr, 16);
+    else
+      fail("global load outside every operand (thread %d)", blk()->cur);
+    return v;
+  }
+  static void global_store16_any(void* ptr, u32x4 v)
+  {
+    if ((uintptr_t)ptr % 2) fail("16-byte store to an odd address (thread %d)", blk()->cur);
+    if (in_buffer(ptr, 16, true))
+      memcpy(ptr, &v, 16);
+    else
+      fail("global store outside the output: block %u,%u thread %d", blk()->bx, blk()->by, blk()->cur);
+  }
+  static void global_store16_keep(void* ptr, u32x4 v) { global_store16(ptr, v); }
   template <class T>
   static T global_load_elem(const void* ptr)
   {
