@@ -1,7 +1,8 @@
 """MI355X-native load-compute-pipelined GEMM / BMM / implicit-GEMM conv2d (ALCOP, arXiv 2210.16691).
 
-Thin ctypes binding over ``libalcop.so`` (C ABI declared in ``include/alcop.h``).  Argument
-marshalling only: every step of the hot path runs in the HIP kernels.  PyTorch is used for device
+Thin binding over ``libalcop.so`` (C ABI declared in ``include/alcop.h``).  Argument marshalling
+only (the hot entry points' in C++, the rest with ctypes): every step of the hot path runs in the
+HIP kernels.  PyTorch is used for device
 memory and streams.  There is no CPU fallback: if the shared library is missing, importing the
 binding's functions raises.
 """
@@ -70,6 +71,8 @@ class Problem(ctypes.Structure):
 
 
 _lib = None
+_marshal = None          # C++ marshalling of the hot entry points (csrc/py_binding.cpp) ...
+_marshal_lib = None      # ... and the library its calls go to
 
 
 def _declare(L: ctypes.CDLL) -> ctypes.CDLL:
@@ -157,11 +160,18 @@ def _declare(L: ctypes.CDLL) -> ctypes.CDLL:
 
 def lib() -> ctypes.CDLL:
     """Loads libalcop.so (built by ``python -m paper_2210_16691_amd.build``); fails loudly if absent."""
-    global _lib
+    global _lib, _marshal, _marshal_lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise ImportError("libalcop.so is not built: run `python -m paper_2210_16691_amd.build`")
-        _lib = _declare(ctypes.CDLL(LIB_PATH))
+        L = _declare(ctypes.CDLL(LIB_PATH))
+        import torch  # noqa: F401  (the module below links against it)
+
+        from . import _binding as m
+        m.init(*[ctypes.cast(f, ctypes.c_void_p).value for f in
+                 (L.alcop_gemm_fused, L.alcop_bmm_fused, L.alcop_bmm_unaligned, L.alcop_conv2d_igemm_dilated,
+                  L.alcop_conv2d_igemm_unaligned)])
+        _lib, _marshal, _marshal_lib = L, m, L
     return _lib
 
 
@@ -274,6 +284,12 @@ def _conv_shapes(x, w, y, stride, pad, krsc=False, bias=None, dilation=(1, 1)):
 def alcop_gemm(A, B, C, sched=None, transB=False, stream=None, transA=False):
     """C[M,N] = A . B  (A is [M,K], or [K,M] if transA; B is [K,N], or [N,K] if transB).  Tensors
     are 2-D CUDA tensors whose last dimension is contiguous; C's dtype selects the output type."""
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.mm(A, B, C, transA, transB, sched, stream) if A.dim() == 2 else None
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_gemm")
+            return C
     if A.dim() != 2:
         raise ValueError("alcop_gemm takes 2-D tensors")
     _, M, N, K = _mm_shapes(A, B, C, transA, transB)
@@ -286,6 +302,12 @@ def alcop_gemm(A, B, C, sched=None, transB=False, stream=None, transA=False):
 
 def alcop_bmm(A, B, C, sched=None, transB=False, stream=None, transA=False):
     """Batched: A [b,M,K] (or [b,K,M] if transA), B [b,K,N] (or [b,N,K] if transB), C [b,M,N]."""
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.mm(A, B, C, transA, transB, sched, stream) if A.dim() == 3 else None
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_bmm")
+            return C
     if A.dim() != 3:
         raise ValueError("alcop_bmm takes 3-D tensors")
     b, M, N, K = _mm_shapes(A, B, C, transA, transB)
@@ -302,6 +324,12 @@ def _epilogue(alpha, bias, act):
 
 def alcop_gemm_fused(A, B, C, alpha=1.0, bias=None, act=0, sched=None, transB=False, stream=None):
     """C = act(alpha * A.B + bias[j]); bias is an fp32 CUDA vector of N values or None; act 1 = ReLU."""
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.mm(A, B, C, False, transB, sched, stream, alpha, bias, act) if A.dim() == 2 else None
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_gemm_fused")
+            return C
     if A.dim() != 2:
         raise ValueError("alcop_gemm_fused takes 2-D tensors")
     _, M, N, K = _mm_shapes(A, B, C, False, transB, bias)
@@ -314,6 +342,12 @@ def alcop_gemm_fused(A, B, C, alpha=1.0, bias=None, act=0, sched=None, transB=Fa
 
 
 def alcop_bmm_fused(A, B, C, alpha=1.0, bias=None, act=0, sched=None, transB=False, stream=None):
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.mm(A, B, C, False, transB, sched, stream, alpha, bias, act) if A.dim() == 3 else None
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_bmm_fused")
+            return C
     if A.dim() != 3:
         raise ValueError("alcop_bmm_fused takes 3-D tensors")
     b, M, N, K = _mm_shapes(A, B, C, False, transB, bias)
@@ -328,6 +362,12 @@ def alcop_bmm_fused(A, B, C, alpha=1.0, bias=None, act=0, sched=None, transB=Fal
 
 def alcop_conv2d_igemm(x, w, y, stride=(1, 1), pad=(0, 0), sched=None, stream=None):
     """x NHWC [N,H,W,C], w RSCK [R,S,C,K], y NPQK [N,P,Q,K]; all contiguous."""
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.conv(x, w, y, stride, pad, (1, 1), False, sched, stream, 1.0, None, 0)
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_conv2d_igemm")
+            return y
     N, H, W, Cc, K, R, S = _conv_shapes(x, w, y, stride, pad)
     rc = lib().alcop_conv2d_igemm(_ptr(x), _ptr(w), _ptr(y), N, H, W, Cc, K, R, S,
                                   stride[0], stride[1], pad[0], pad[1],
@@ -417,6 +457,12 @@ def alcop_splitk_auto(prob: "Problem", split: int = 0):
 def alcop_conv2d_igemm_fused(x, w, y, stride=(1, 1), pad=(0, 0), alpha=1.0, bias=None, act=0,
                              krsc=False, sched=None, stream=None):
     """y = act(alpha * conv(x, w) + bias[k]); w is RSCK [R,S,C,K], or KRSC [K,R,S,C] if krsc."""
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.conv(x, w, y, stride, pad, (1, 1), krsc, sched, stream, alpha, bias, act)
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_conv2d_igemm_fused")
+            return y
     N, H, W, Cc, K, R, S = _conv_shapes(x, w, y, stride, pad, krsc, bias)
     e = _epilogue(alpha, bias, act)
     rc = lib().alcop_conv2d_igemm_fused(_ptr(x), _ptr(w), _ptr(y), N, H, W, Cc, K, R, S,
@@ -431,6 +477,12 @@ def alcop_conv2d_igemm_dilated(x, w, y, stride=(1, 1), pad=(0, 0), dilation=(1, 
                                act=0, krsc=False, sched=None, stream=None):
     """y = act(alpha * conv(x, w) + bias[k]) with filter taps dilation[0] rows / dilation[1] columns
     apart; w is RSCK [R,S,C,K], or KRSC [K,R,S,C] if krsc."""
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.conv(x, w, y, stride, pad, dilation, krsc, sched, stream, alpha, bias, act)
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_conv2d_igemm_dilated")
+            return y
     N, H, W, Cc, K, R, S = _conv_shapes(x, w, y, stride, pad, krsc, bias, dilation)
     e = _epilogue(alpha, bias, act)
     rc = lib().alcop_conv2d_igemm_dilated(_ptr(x), _ptr(w), _ptr(y), N, H, W, Cc, K, R, S,
@@ -450,6 +502,12 @@ def alcop_bmm_unaligned(A, B, C, workspace, alpha=1.0, bias=None, act=0, sched=N
     """C = act(alpha * A.B + bias[j]) for operands of any extent and element-aligned placement
     (2-D: a GEMM; 3-D: batched); they are padded into `workspace` (a CUDA byte tensor of at least
     alcop_unaligned_workspace_bytes(...) bytes) and multiplied there."""
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.mm_any(A, B, C, workspace, alpha, bias, act, sched, transA, transB, stream)
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_bmm_unaligned")
+            return C
     b, M, N, K = _mm_shapes(A, B, C, transA, transB, bias)
     _same_place(A, workspace)
     if not workspace.is_contiguous():
@@ -476,6 +534,12 @@ def alcop_conv2d_igemm_unaligned(x, w, y, workspace, stride=(1, 1), pad=(0, 0), 
                                  bias=None, act=0, sched=None, stream=None):
     """y = act(alpha * conv(x, w) + bias[k]) for any channel counts (x NHWC, w RSCK, y NPQK); the
     tensors are padded to 8 channels in `workspace` and convolved there."""
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.conv_any(x, w, y, workspace, stride, pad, dilation, alpha, bias, act, sched, stream)
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_conv2d_igemm_unaligned")
+            return y
     N, H, W, Cc, K, R, S = _conv_shapes(x, w, y, stride, pad, False, bias, dilation)
     _same_place(x, workspace)
     if not workspace.is_contiguous():
@@ -492,6 +556,12 @@ def alcop_conv2d_igemm_unaligned(x, w, y, workspace, stride=(1, 1), pad=(0, 0), 
 
 def alcop_conv2d_igemm_krsc(x, w, y, stride=(1, 1), pad=(0, 0), sched=None, stream=None):
     """x NHWC [N,H,W,C], w KRSC [K,R,S,C], y NPQK [N,P,Q,K]; all contiguous."""
+    if _marshal_lib is _lib is not None:
+        rc = _marshal.conv(x, w, y, stride, pad, (1, 1), True, sched, stream, 1.0, None, 0)
+        if rc is not None:
+            if rc:
+                raise AlcopError(rc, "alcop_conv2d_igemm_krsc")
+            return y
     N, H, W, Cc, K, R, S = _conv_shapes(x, w, y, stride, pad, krsc=True)
     rc = lib().alcop_conv2d_igemm_krsc(_ptr(x), _ptr(w), _ptr(y), N, H, W, Cc, K, R, S,
                                        stride[0], stride[1], pad[0], pad[1],

@@ -21,6 +21,9 @@ OBJDIR = os.path.join(ROOT, "_build", "alcop")
 LIB = os.path.join(HERE, "libalcop.so")
 DIAG_LIB = os.path.join(HERE, "libalcop_diag.so")     # measurement aid: csrc/diag_*.hip
 
+MARSHAL_SRC = os.path.join(CSRC, "py_binding.cpp")    # argument marshalling of the Python binding
+MARSHAL_LIB = os.path.join(HERE, "_binding.so")
+
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
@@ -32,7 +35,7 @@ FLAGS = [
 
 def sources():
     hip = [f for f in glob.glob(os.path.join(CSRC, "*.hip")) if not os.path.basename(f).startswith("diag_")]
-    return sorted(hip + glob.glob(os.path.join(CSRC, "*.cpp")))
+    return sorted(hip + [f for f in glob.glob(os.path.join(CSRC, "*.cpp")) if f != MARSHAL_SRC])
 
 
 def diag_sources():
@@ -67,12 +70,33 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def build_marshal(force: bool = False) -> str:
+    """The binding's marshalling module: host code only, against the installed PyTorch's headers."""
+    header = os.path.join(ROOT, "include", "alcop.h")
+    if not force and os.path.exists(MARSHAL_LIB) and \
+            os.path.getmtime(MARSHAL_LIB) >= max(os.path.getmtime(MARSHAL_SRC), os.path.getmtime(header)):
+        return MARSHAL_LIB
+    import sysconfig
+
+    import torch
+    t = os.path.dirname(torch.__file__)
+    subprocess.check_call(
+        [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+         "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+         "-I" + os.path.join(t, "include"), "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"),
+         "-I/opt/rocm/include", "-I" + sysconfig.get_paths()["include"], MARSHAL_SRC, "-o", MARSHAL_LIB,
+         "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"])
+    return MARSHAL_LIB
+
+
 def build(jobs: int = 8, force: bool = False) -> str:
     os.makedirs(OBJDIR, exist_ok=True)
     srcs = sources()
     dsrcs = diag_sources()
     with cf.ThreadPoolExecutor(max_workers=max(1, min(jobs, 16))) as ex:
+        marshal = ex.submit(build_marshal, force)
         allobjs = list(ex.map(lambda s: _compile(s, force), srcs + dsrcs))
+        marshal.result()
     objs, dobjs = allobjs[:len(srcs)], allobjs[len(srcs):]
     for lib, obs in ((LIB, objs), (DIAG_LIB, dobjs)):
         if obs and (force or not os.path.exists(lib) or any(os.path.getmtime(o) > os.path.getmtime(lib) for o in obs)):

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstdio>
 #include <cstdint>
 #include <cstdlib>
@@ -10,6 +11,7 @@
 #include <map>
 #include <mutex>
 #include <tuple>
+#include <unordered_map>
 #include <vector>
 
 #include "../../include/alcop.h"
@@ -95,17 +97,32 @@ int a_mode(const alcop_problem& p, int bk, int variant)
   return (bk > 0 && p.conv_C % bk == 0) ? 1 : 2;
 }
 
+// What names a kernel: operand type and layouts, loader, split-K switch, tile, pipelining, kind.
+using EntryKey = std::array<int, 15>;
+struct EntryHash {
+  size_t operator()(const EntryKey& k) const
+  {
+    size_t h = 0;
+    for (int v : k) h = h * 1000003u + (size_t)v;
+    return h;
+  }
+};
+
+// Every call looks its kernel up; a walk over the thousand table entries was most of the host
+// time a call spent outside the launch.
 const KernelEntry* find_entry(const alcop_problem& p, const alcop_sched& s, int sk)
 {
-  const int am = a_mode(p, s.bk, s.variant);
-  for (const KernelEntry& e : registry())
-    if (e.sk == sk && e.dt == (int)p.in && e.bl == (p.transB ? 1 : 0) && e.al == (p.transA ? 1 : 0) &&
-        e.am == am && e.bm == s.bm &&
-        e.bn == s.bn && e.bk == s.bk && e.wm == s.wm && e.wn == s.wn && e.stages == s.stages &&
-        e.reg_stages == s.reg_stages && e.fuse == (s.fuse_inner ? 1 : 0) &&
-        e.pf == (s.l2_prefetch > 0 ? 1 : 0) && e.st == (s.variant == 2 ? 1 : 0))
-      return &e;
-  return nullptr;
+  static const std::unordered_map<EntryKey, const KernelEntry*, EntryHash> index = [] {
+    std::unordered_map<EntryKey, const KernelEntry*, EntryHash> m;
+    for (const KernelEntry& e : registry())
+      m.emplace(EntryKey{e.sk, e.dt, e.bl, e.al, e.am, e.bm, e.bn, e.bk, e.wm, e.wn, e.stages, e.reg_stages,
+                         e.fuse, e.pf, e.st}, &e);    // of equal keys the first stays
+    return m;
+  }();
+  const auto it = index.find(EntryKey{sk, (int)p.in, p.transB ? 1 : 0, p.transA ? 1 : 0, a_mode(p, s.bk, s.variant),
+                                      s.bm, s.bn, s.bk, s.wm, s.wn, s.stages, s.reg_stages, s.fuse_inner ? 1 : 0,
+                                      s.l2_prefetch > 0 ? 1 : 0, s.variant == 2 ? 1 : 0});
+  return it == index.end() ? nullptr : it->second;
 }
 
 int check_problem(const alcop_problem& p)

@@ -34,7 +34,7 @@ struct FastDiv {
   }
   __device__ __forceinline__ uint32_t div(uint32_t n) const
   {
-    return (uint32_t)(((uint64_t)n * mul) >> 32) + n >> shift;
+    return ((uint32_t)(((uint64_t)n * mul) >> 32) + n) >> shift;
   }
 };
 
