@@ -100,6 +100,12 @@ typedef struct {
                       /* number of blocks is one or two per compute unit (by LDS), at most    */
                       /* the number of tiles; the environment variable ALCOP_STREAM_BLOCKS    */
                       /* (a positive integer, read at every launch) overrides it              */
+                      /* 3 = the waves of a block split the reduction axis (any operator): every */
+                      /* wave owns the whole bm x bn tile (16x16, 16x32, 32x32, 32x64; wm = bm, */
+                      /* wn = bn) and a slice of K with a ring of its own, and the waves' fp32   */
+                      /* tiles are added in wave order at the end.  For outputs with few tiles.  */
+                      /* bk = 64, reg_stages = 1, fuse_inner = 0, l2_prefetch = 0.  Deterministic, */
+                      /* not bit-identical to the other kernels (another order of the k sum)       */
 } alcop_sched;
 
 /* Problem description used by the model / tuner / feasibility entry points. */
@@ -374,8 +380,8 @@ int alcop_sched_space(const alcop_problem* prob /* host */, alcop_sched* out /* 
 
 /*
  * The kernels outside the default space built for the problem.  They run when a caller names
- * them or asks the tuner for them (alcop_tune with variants = 1); a NULL / zero schedule never
- * resolves to one unless the tuner chose it.  They are
+ * them or asks the tuner for them (alcop_tune with variants = 1); the static model never picks
+ * one on its own (the library's pick may be of variant 3, see alcop_sched_auto).  They are
  *   - the schedule variant 1, whose feasibility depends on more than the
  *     problem description: for a convolution the variant with the input patch resident in LDS,
  *     which also needs stride 1 and a patch that fits the LDS (alcop_sched_supported only checks
@@ -383,7 +389,9 @@ int alcop_sched_space(const alcop_problem* prob /* host */, alcop_sched* out /* 
  *   - the kernels with bk = 128: half as many block-wide synchronisations per unit of work, but
  *     two stages of a 128 x 128 tile already fill 128 KB of LDS;
  *   - the persistent kernels whose consumers run the deep register pipeline (variant 2 with
- *     reg_stages = 4): measured no faster than reg_stages = 2 on any shape tried.
+ *     reg_stages = 4): measured no faster than reg_stages = 2 on any shape tried;
+ *   - the kernels whose waves split the reduction axis (variant 3), which the static model does not
+ *     describe: it takes their small tiles for tiles of one wave.
  */
 int alcop_sched_variants(const alcop_problem* prob /* host */, alcop_sched* out /* host */, int cap);
 
@@ -466,8 +474,10 @@ int alcop_sched_ranked(const alcop_problem* prob /* host */, int model, int vari
 
 /*
  * The schedule a NULL / zero schedule argument resolves to for this problem: the entry of the
- * tuning cache if there is one (written by alcop_tune or alcop_cache_load), else the feasible
- * schedule with the lowest predicted latency under model 0.  Host only, launches nothing.
+ * tuning cache if there is one (written by alcop_tune or alcop_cache_load), else the library's
+ * pick: the lowest of the measured costs of a few kernels (csrc/alcop_dispatch.h), or, where those
+ * are within 3 % of it or do not cover the problem, the feasible schedule with the lowest predicted
+ * latency under model 0.  Host only, launches nothing.
  */
 int alcop_sched_auto(const alcop_problem* prob /* host */, alcop_sched* out /* host */);
 

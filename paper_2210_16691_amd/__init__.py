@@ -608,7 +608,7 @@ def alcop_sched_ranked(prob: Problem, model: int = 0, variants: bool = False, to
 
 
 def alcop_sched_auto(prob: Problem) -> Sched:
-    """The schedule a None schedule resolves to (tuning cache, else the model's top-1)."""
+    """The schedule a None schedule resolves to (tuning cache, else the library's pick)."""
     s = Sched()
     _check(lib().alcop_sched_auto(ctypes.byref(prob), ctypes.byref(s)), "alcop_sched_auto")
     return s

@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "../../include/alcop.h"
+#include "alcop_dispatch.h"
 #include "alcop_model.h"
 #include "alcop_registry.h"
 
@@ -39,6 +40,8 @@ const std::vector<KernelEntry>& registry()
     register_wide(t);
     register_pf(t);
     register_stream(t);
+    register_ksplit(t);
+    register_ksplit_conv(t);
     register_splitk_gemm(t);
     register_splitk_conv(t);
     return t;
@@ -121,7 +124,8 @@ const KernelEntry* find_entry(const alcop_problem& p, const alcop_sched& s, int 
   }();
   const auto it = index.find(EntryKey{sk, (int)p.in, p.transB ? 1 : 0, p.transA ? 1 : 0, a_mode(p, s.bk, s.variant),
                                       s.bm, s.bn, s.bk, s.wm, s.wn, s.stages, s.reg_stages, s.fuse_inner ? 1 : 0,
-                                      s.l2_prefetch > 0 ? 1 : 0, s.variant == 2 ? 1 : 0});
+                                      s.l2_prefetch > 0 ? 1 : 0,
+                                      s.variant == 2 ? 1 : s.variant == 3 ? 2 : 0});
   return it == index.end() ? nullptr : it->second;
 }
 
@@ -155,7 +159,10 @@ int check_sched(const alcop_problem& p, const alcop_sched& s, const KernelEntry*
   if (s.raster != 0 && s.raster != 1) return ALCOP_ERR_SCHED;
   if (s.l2_prefetch < 0 || s.l2_prefetch > 64 || (s.l2_prefetch > 0 && s.raster != 1))
     return ALCOP_ERR_SCHED;
-  if (s.variant != 0 && s.variant != 2 &&
+  // variant 3, the waves of a block split the reduction axis: one register stage, no L2 touches, no
+  // split-K
+  if (s.variant == 3 && (s.reg_stages != 1 || s.l2_prefetch != 0 || sk != 0)) return ALCOP_ERR_SCHED;
+  if (s.variant != 0 && s.variant != 2 && s.variant != 3 &&
       !(s.variant == 1 && p.op == ALCOP_OP_CONV2D && !p.transB && p.conv_C == s.bk && sk == 0))
     return ALCOP_ERR_SCHED;
   // variant 2, the persistent producer / consumer kernels: two register stages (fused across
@@ -186,7 +193,7 @@ int default_l2_prefetch(int bk) { return 256 / bk; }
 // feasibility depends on the call, not only on the problem description) and the kernels with a
 // k-tile of 128 (two stages of a 128 x 128 tile fill the LDS: a trade the tuner should measure),
 // and the persistent kernels with the consumers' deep register pipeline (no faster where measured).
-bool opt_in(const KernelEntry& e) { return e.am == 3 || e.bk == 128 || (e.st && e.reg_stages == 4); }
+bool opt_in(const KernelEntry& e) { return e.am == 3 || e.bk == 128 || (e.st == 1 && e.reg_stages == 4) || e.st == 2; }
 
 // variants: 0 = the default kernels; 1 = also the opt-in kernels; 2 = only those.
 std::vector<alcop_sched> space_of(const alcop_problem& p, int sk = 0, int variants = 0)
@@ -200,14 +207,14 @@ std::vector<alcop_sched> space_of(const alcop_problem& p, int sk = 0, int varian
     {
       // a kernel with the third (HBM -> L2) level is offered with that level on
       v.push_back(alcop_sched{e.bm, e.bn, e.bk, e.wm, e.wn, e.stages, e.reg_stages, e.fuse, 1,
-                              e.pf ? default_l2_prefetch(e.bk) : 0, e.am == 3 ? 1 : (e.st ? 2 : 0)});
+                              e.pf ? default_l2_prefetch(e.bk) : 0, e.am == 3 ? 1 : e.st == 1 ? 2 : e.st == 2 ? 3 : 0});
     }
   return v;
 }
 
 using CacheKey = std::tuple<int, int, int, int, int, int, int, int, int, int>;
 std::mutex g_cache_mu;
-std::map<CacheKey, alcop_sched> g_cache;   // problem -> chosen schedule (tuned or model top-1)
+std::map<CacheKey, alcop_sched> g_cache;   // problem -> chosen schedule (tuned or the library's pick)
 
 CacheKey key_of(const alcop_problem& p)
 {
@@ -236,7 +243,32 @@ int model_pick(const alcop_problem& p, alcop_sched* out)
   return have ? ALCOP_OK : ALCOP_ERR_SCHED;
 }
 
-// What a NULL / zero schedule resolves to: the tuning cache, else the model's pick.
+// The library's own pick: the cheapest by measured cost (alcop_dispatch.h).  A near tie (3 %) goes to
+// the model's pick, and so do problems the measurements do not cover.
+int library_pick(const alcop_problem& p, alcop_sched* out)
+{
+  alcop_sched model;
+  const int rc = model_pick(p, &model);
+  const MeasuredCost *best = nullptr, *of_model = nullptr;
+  double best_us = 0;
+  for (const MeasuredCost& m : kMeasured) {
+    if (!measured_applies(p, m) || check_sched(p, m.s, nullptr) != ALCOP_OK) continue;
+    const double us = measured_us(p, m);
+    if (!best || us < best_us) {
+      best = &m;
+      best_us = us;
+    }
+    if (rc == ALCOP_OK && std::memcmp(&m.s, &model, sizeof(model)) == 0) of_model = &m;
+  }
+  if (best && !(of_model && measured_us(p, *of_model) <= 1.03 * best_us)) {
+    *out = best->s;
+    return ALCOP_OK;
+  }
+  *out = model;
+  return rc;
+}
+
+// What a NULL / zero schedule resolves to: the tuning cache, else the library's pick.
 int auto_sched(const alcop_problem& p, alcop_sched* out)
 {
   // a tuning cache named by the environment is merged in once, before the first lookup
@@ -253,7 +285,7 @@ int auto_sched(const alcop_problem& p, alcop_sched* out)
       return ALCOP_OK;
     }
   }
-  const int rc = model_pick(p, out);
+  const int rc = library_pick(p, out);
   if (rc) return rc;
   std::lock_guard<std::mutex> lk(g_cache_mu);
   g_cache[key_of(p)] = *out;
@@ -428,7 +460,7 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
     }
   }
   dim3 grid((unsigned)(p.ntm * p.ntn), (unsigned)c.batch, 1);
-  if (e->st) {
+  if (e->st == 1) {
     // persistent blocks: as many as stay resident (by LDS, at most two per compute unit), never
     // more than there are tiles; ALCOP_STREAM_BLOCKS overrides the count (a tuning and test knob)
     const long total = (long)p.ntm * p.ntn * c.batch;

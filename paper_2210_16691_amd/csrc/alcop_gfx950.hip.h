@@ -6,6 +6,8 @@
 //                                 descriptor's num_records writes zeros and fetches nothing
 //   ds_read_b64_tr_b16            per 16-lane group: lane i receives, as element e, element i%4
 //                                 of the 8 bytes addressed by lane 4e + i/4 (four 4x4 transposes)
+//   v_mfma_f32_16x16x32_{f16,bf16}  X lane l = row l%16, k = 8*(l/16)..+7; Y likewise by column;
+//                                 D lane l = column l%16, rows 4*(l/16)..+3
 //   v_mfma_f32_32x32x16_{f16,bf16}  X lane l = row l%32, k = 8*(l/32)..+7; Y likewise by column;
 //                                 D lane l = column l%32, rows 8*(v/4) + 4*(l/32) + v%4
 // The direct-to-LDS loads and the waits are inline asm on purpose: the compiler treats a builtin
@@ -96,6 +98,17 @@ struct Gfx950 {
                                                      __builtin_bit_cast(bf16x8, y), acc, 0, 0, 0);
   }
 
+  template <int DT>
+  __device__ static __forceinline__ f32x4 mma16(u32x4 x, u32x4 y, f32x4 acc)
+  {
+    if constexpr (DT == 0)
+      return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x),
+                                                    __builtin_bit_cast(f16x8, y), acc, 0, 0, 0);
+    else
+      return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x),
+                                                     __builtin_bit_cast(bf16x8, y), acc, 0, 0, 0);
+  }
+
   __device__ static __forceinline__ u32x4 lds_read16(uint32_t addr)
   {
     return *(const ALCOP_LDS u32x4*)(uintptr_t)addr;
@@ -134,6 +147,12 @@ struct Gfx950 {
   __device__ static __forceinline__ uint32_t global_load_u32(const void* ptr) { return *(const uint32_t*)ptr; }
   __device__ static __forceinline__ void global_store_u16(void* ptr, uint16_t v) { *(uint16_t*)ptr = v; }
   __device__ static __forceinline__ void global_store_u32(void* ptr, uint32_t v) { *(uint32_t*)ptr = v; }
+  // aligned store of a scalar or a short vector
+  template <class V>
+  __device__ static __forceinline__ void global_store(void* ptr, V v)
+  {
+    __builtin_nontemporal_store(v, (V*)ptr);
+  }
   // fp32 -> output element, round to nearest even
   template <class OT>
   __device__ static __forceinline__ OT cvt(float v)

@@ -60,6 +60,11 @@ void add_stream(std::vector<KernelEntry>& t)
   add_stream<DT, BM, BN, BK, WM, WN, 2, BL, AM, 0, 0>(T);        \
   add_stream<DT, BM, BN, BK, WM, WN, 3, BL, AM, 0, 0>(T);        \
   add_stream<DT, BM, BN, BK, WM, WN, 4, BL, AM, 0, 0>(T);
+// the pipelinings that measured best across the f16 shapes, k-tile 64, for the other layouts and bf16
+#define ALCOP_STREAM_KEY(T, DT, BM, BN, WM, WN, BL, AM, AL)      \
+  add_stream<DT, BM, BN, 64, WM, WN, 2, BL, AM, AL, 0>(T);       \
+  add_stream<DT, BM, BN, 64, WM, WN, 3, BL, AM, AL, 0>(T);       \
+  add_stream<DT, BM, BN, 64, WM, WN, 3, BL, AM, AL, 1>(T);
 // the consumers' deep register pipeline (k-tile 64): measured no faster than the two above on any
 // configuration, so these stay outside the default schedule space (alcop_sched_variants)
 #define ALCOP_STREAM_DEEP(T, DT, BM, BN, WM, WN, BL, AM)         \

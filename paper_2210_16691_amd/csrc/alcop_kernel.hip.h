@@ -321,6 +321,27 @@ __device__ __forceinline__ bool touch_line(const void* ptr, int t, int extent, i
   return true;
 }
 
+// Block -> tile (paper Sec. 1: inter-tile parallelism; the order only affects L2 reuse).
+__device__ __forceinline__ void tile_of_block(const Params& p, int lid, int& tm, int& tn)
+{
+  const int nblk = p.ntm * p.ntn;
+  if (p.raster == 1) {
+    // blocks are dealt to the 8 XCDs round robin: XCD x takes the x-th of 8 nearly equal runs of tiles
+    const int x = lid & 7, rem8 = nblk & 7;
+    lid = x * (nblk >> 3) + (x < rem8 ? x : rem8) + (lid >> 3);
+    const int width = p.group_m * p.ntn;
+    const int g = lid / width;
+    const int first = g * p.group_m;
+    const int gsz = (p.ntm - first) < p.group_m ? (p.ntm - first) : p.group_m;
+    const int rem = lid - g * width;
+    tm = first + rem % gsz;
+    tn = rem / gsz;
+  } else {
+    tm = lid / p.ntn;
+    tn = lid - tm * p.ntn;
+  }
+}
+
 // ---- epilogue helpers (shared with the persistent kernel) ------------------------------------
 // The fused elementwise function is act(alpha * acc + bias[n]).  A lane's columns are the same in
 // every 32-row band, so its TN * 4 groups of four bias values are fetched once per tile, all at
@@ -422,23 +443,8 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
   const int wm = wave % C::WAVES_M, wn = wave / C::WAVES_M;
   const int batch = HW::block_y();
 
-  // ---- block -> tile (paper Sec. 1: inter-tile parallelism; the order only affects L2 reuse)
-  int lid = HW::block_x();
-  const int nblk = p.ntm * p.ntn;
   int tm, tn;
-  if (p.raster == 1) {
-    if ((nblk & 7) == 0) lid = (lid & 7) * (nblk >> 3) + (lid >> 3);   // blocks of one XCD adjacent
-    const int width = p.group_m * p.ntn;
-    const int g = lid / width;
-    const int first = g * p.group_m;
-    const int gsz = (p.ntm - first) < p.group_m ? (p.ntm - first) : p.group_m;
-    const int rem = lid - g * width;
-    tm = first + rem % gsz;
-    tn = rem / gsz;
-  } else {
-    tm = lid / p.ntn;
-    tn = lid - tm * p.ntn;
-  }
+  tile_of_block(p, HW::block_x(), tm, tn);
   // the k range of this block: all of K, or one slice of it (split-K; slices are whole k-tiles)
   int k0 = 0, Kb = p.K;
   if constexpr (C::SK) {

@@ -13,7 +13,8 @@ struct KernelEntry {
   int dt, bm, bn, bk, wm, wn, stages, reg_stages, fuse, bl, am, al;
   int sk;   // 1: split-K variant (grid.z slices of the reduction axis, fp32 partial tiles)
   int pf;   // 1: the kernel has the HBM -> L2 touch level (schedules with l2_prefetch > 0)
-  int st;   // 1: persistent producer / consumer kernel (schedule variant 2)
+  int st;   // 1: persistent producer / consumer kernel (schedule variant 2); 2: the waves of a block
+            // split the reduction axis (schedule variant 3)
   int lds_bytes, threads, loads_per_stage;
   int patch_off;   // am == 3: LDS offset of the input patch (its size is per call)
   hipError_t (*launch)(const Params&, dim3, hipStream_t);
@@ -38,6 +39,8 @@ void register_deep(std::vector<KernelEntry>&);
 void register_wide(std::vector<KernelEntry>&);
 void register_pf(std::vector<KernelEntry>&);
 void register_stream(std::vector<KernelEntry>&);
+void register_ksplit(std::vector<KernelEntry>&);
+void register_ksplit_conv(std::vector<KernelEntry>&);
 void register_splitk_gemm(std::vector<KernelEntry>&);
 void register_splitk_conv(std::vector<KernelEntry>&);
 

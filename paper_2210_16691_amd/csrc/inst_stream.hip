@@ -5,6 +5,7 @@
 namespace alcop {
 void register_stream_nk(std::vector<KernelEntry>& t);
 void register_stream_conv(std::vector<KernelEntry>& t);
+void register_stream_more(std::vector<KernelEntry>& t);
 void register_stream(std::vector<KernelEntry>& t)
 {
   // fp16, B stored K x N
@@ -16,5 +17,6 @@ void register_stream(std::vector<KernelEntry>& t)
   ALCOP_STREAM_DEEP(t, 0, 128, 64, 64, 32, 0, 0)
   register_stream_nk(t);
   register_stream_conv(t);
+  register_stream_more(t);
 }
 }  // namespace alcop

@@ -50,6 +50,7 @@
 
 #include "alcop_kernel.hip.h"
 #include "alcop_stream.hip.h"
+#include "alcop_ksplit.hip.h"
 
 namespace emu {
 
@@ -392,6 +393,7 @@ struct Emu {
   {
     if (cfg().mutation == 4) return;
     reads_done();
+    wave_sync();                   // a wave's lanes wait together: all of its reads are over
   }
   static void block_barrier()
   {
@@ -418,6 +420,36 @@ struct Emu {
       float s = acc[v];
       for (int k = 0; k < 16; k++) {
         const u32x4 xr = W.X[par][i + 32 * (k >> 3)], yr = W.Y[par][j + 32 * (k >> 3)];
+        const int e = k & 7;
+        const uint16_t xb = (uint16_t)(xr[e >> 1] >> (16 * (e & 1)));
+        const uint16_t yb = (uint16_t)(yr[e >> 1] >> (16 * (e & 1)));
+        const float xf = DT == 0 ? f16_to_float(xb) : bf16_to_float(xb);
+        const float yf = DT == 0 ? f16_to_float(yb) : bf16_to_float(yb);
+        s += xf * yf;
+      }
+      acc[v] = s;
+    }
+    return acc;
+  }
+
+  template <int DT>
+  static f32x4 mma16(u32x4 x, u32x4 y, f32x4 acc)
+  {
+    Block& b = *blk();
+    const int l = b.cur & 63;
+    Lane& L = b.lanes[b.cur];
+    Wave& W = b.waves[b.cur >> 6];
+    const int par = L.mma_par;
+    L.mma_par ^= 1;
+    W.X[par][l] = x;
+    W.Y[par][l] = y;
+    wave_sync();
+    const int j = l & 15;
+    for (int v = 0; v < 4; v++) {
+      const int i = 4 * (l >> 4) + v;
+      float s = acc[v];
+      for (int k = 0; k < 32; k++) {
+        const u32x4 xr = W.X[par][i + 16 * (k >> 3)], yr = W.Y[par][j + 16 * (k >> 3)];
         const int e = k & 7;
         const uint16_t xb = (uint16_t)(xr[e >> 1] >> (16 * (e & 1)));
         const uint16_t yb = (uint16_t)(yr[e >> 1] >> (16 * (e & 1)));
@@ -512,6 +544,16 @@ struct Emu {
       fail("global store outside the output: block %u,%u thread %d", blk()->bx, blk()->by, blk()->cur);
   }
   static void global_store16_keep(void* ptr, u32x4 v) { global_store16(ptr, v); }
+  template <class V>
+  static void global_store(void* ptr, V v)
+  {
+    Block& b = *blk();
+    if ((uintptr_t)ptr % sizeof(V)) fail("global store to an unaligned address (thread %d)", b.cur);
+    if (in_buffer(ptr, sizeof(V), true))
+      memcpy(ptr, &v, sizeof(V));
+    else
+      fail("global store outside the output: block %u,%u thread %d", b.bx, b.by, b.cur);
+  }
   template <class T>
   static T global_load_elem(const void* ptr)
   {
@@ -646,6 +688,12 @@ template <class C>
 void stream_entry(const void* p)
 {
   alcop::alcop_stream<C, Emu>(*(const alcop::Params*)p);
+}
+
+template <class C>
+void ksplit_entry(const void* p)
+{
+  alcop::alcop_ksplit<C, Emu>(*(const alcop::Params*)p);
 }
 
 }  // namespace emu

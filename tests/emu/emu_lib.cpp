@@ -42,6 +42,21 @@ void add_stream(std::vector<KernelEntry>& t)
                           &launch_emulated_stream<C>});
 }
 
+template <class C>
+hipError_t launch_emulated_ksplit(const Params& p, dim3 grid, hipStream_t)
+{
+  emu::run_grid(&emu::ksplit_entry<C>, &p, C::NT, C::LDS_BYTES, grid.x, grid.y, grid.z);
+  return hipSuccess;
+}
+
+template <int DT, int BM, int BN, int NW, int S, int BL, int AM, int AL = 0>
+void add_ksplit(std::vector<KernelEntry>& t)
+{
+  using C = WCfg<DT, BM, BN, NW, S, BL, AM, AL>;
+  t.push_back(KernelEntry{DT, BM, BN, 64, BM, BN, S, 1, 0, BL, AM, AL, 0, 0, 2, C::LDS_BYTES, C::NT, C::L, 0,
+                          &launch_emulated_ksplit<C>});
+}
+
 #if EMU_PART == 0
 void emu_part_0(std::vector<KernelEntry>& t)
 {
@@ -230,6 +245,26 @@ void register_deep(std::vector<KernelEntry>&) {}
 void register_wide(std::vector<KernelEntry>&) {}
 void register_pf(std::vector<KernelEntry>&) {}
 void register_stream(std::vector<KernelEntry>&) {}
+void register_ksplit(std::vector<KernelEntry>& t)
+{
+  // the waves of a block split the reduction axis (schedule variant 3)
+  add_ksplit<0, 16, 16, 8, 2, 0, 0>(t);
+  add_ksplit<0, 16, 16, 8, 2, 1, 0>(t);
+  add_ksplit<0, 16, 32, 8, 2, 0, 0>(t);
+  add_ksplit<1, 16, 32, 8, 2, 1, 0>(t);
+  add_ksplit<0, 32, 32, 8, 2, 0, 0>(t);
+  add_ksplit<0, 32, 32, 8, 2, 1, 0, 1>(t);
+  add_ksplit<1, 16, 16, 8, 2, 0, 0, 1>(t);
+  add_ksplit<0, 32, 64, 4, 2, 0, 0>(t);
+  add_ksplit<1, 32, 64, 4, 2, 1, 0, 1>(t);
+}
+void register_ksplit_conv(std::vector<KernelEntry>& t)
+{
+  add_ksplit<0, 16, 16, 8, 2, 0, 1>(t);
+  add_ksplit<0, 32, 32, 8, 2, 1, 1>(t);
+  add_ksplit<0, 32, 32, 8, 2, 0, 2>(t);
+  add_ksplit<1, 32, 64, 4, 2, 1, 2>(t);
+}
 
 static void reduce_entry(const void* p)
 {
