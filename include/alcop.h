@@ -106,6 +106,12 @@ typedef struct {
                       /* tiles are added in wave order at the end.  For outputs with few tiles.  */
                       /* bk = 64, reg_stages = 1, fuse_inner = 0, l2_prefetch = 0.  Deterministic, */
                       /* not bit-identical to the other kernels (another order of the k sum)       */
+                      /* 4 = convolution with the input patch resident in LDS for any channel    */
+                      /* count, stride, dilation and weight layout: bm x bn = 256x64, 128x128,    */
+                      /* 128x64, 64x128 or 64x64, bk = wm = wn = 64, reg_stages = 2, fuse_inner =  */
+                      /* 1, l2_prefetch = 0; a patch that does not fit the LDS returns              */
+                      /* ALCOP_ERR_SCHED.  The tiles below 256x64 and 128x128 split each stage of   */
+                      /* K among waves (deterministic, another order of the k sum)                  */
 } alcop_sched;
 
 /* Problem description used by the model / tuner / feasibility entry points. */
@@ -391,7 +397,9 @@ int alcop_sched_space(const alcop_problem* prob /* host */, alcop_sched* out /* 
  *   - the persistent kernels whose consumers run the deep register pipeline (variant 2 with
  *     reg_stages = 4): measured no faster than reg_stages = 2 on any shape tried;
  *   - the kernels whose waves split the reduction axis (variant 3), which the static model does not
- *     describe: it takes their small tiles for tiles of one wave.
+ *     describe: it takes their small tiles for tiles of one wave;
+ *   - the convolutions with a resident patch for any geometry (variant 4); as for variant 1, the
+ *     launch or the tuner checks that the patch of a call fits.
  */
 int alcop_sched_variants(const alcop_problem* prob /* host */, alcop_sched* out /* host */, int cap);
 

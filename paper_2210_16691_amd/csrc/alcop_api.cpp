@@ -18,6 +18,7 @@
 #include "alcop_dispatch.h"
 #include "alcop_model.h"
 #include "alcop_registry.h"
+#include "alcop_convres.hip.h"
 
 namespace alcop {
 
@@ -42,6 +43,8 @@ const std::vector<KernelEntry>& registry()
     register_stream(t);
     register_ksplit(t);
     register_ksplit_conv(t);
+    register_convres_rsck(t);
+    register_convres_krsc(t);
     register_splitk_gemm(t);
     register_splitk_conv(t);
     return t;
@@ -92,11 +95,13 @@ alcop_problem problem_of(const Call& c)
 // Loader of the A operand a problem needs with k-tile bk: 0 = matrix; 1 = convolution gather
 // whose k-tiles lie inside one filter tap (bk divides the channel count); 2 = gather for any
 // channel count that is a multiple of 8.
-// 3 = schedule variant 1 of a convolution: the input patch stays in LDS (bk equals the channel count).
+// 3 = schedule variant 1 of a convolution: the input patch stays in LDS (bk equals the channel count);
+// 4 = variant 4: the same for any channel count, stride and dilation.
 int a_mode(const alcop_problem& p, int bk, int variant)
 {
   if (p.op != ALCOP_OP_CONV2D) return 0;
   if (variant == 1) return 3;
+  if (variant == 4) return 4;
   return (bk > 0 && p.conv_C % bk == 0) ? 1 : 2;
 }
 
@@ -125,7 +130,7 @@ const KernelEntry* find_entry(const alcop_problem& p, const alcop_sched& s, int 
   const auto it = index.find(EntryKey{sk, (int)p.in, p.transB ? 1 : 0, p.transA ? 1 : 0, a_mode(p, s.bk, s.variant),
                                       s.bm, s.bn, s.bk, s.wm, s.wn, s.stages, s.reg_stages, s.fuse_inner ? 1 : 0,
                                       s.l2_prefetch > 0 ? 1 : 0,
-                                      s.variant == 2 ? 1 : s.variant == 3 ? 2 : 0});
+                                      s.variant == 2 ? 1 : s.variant == 3 ? 2 : s.variant == 4 ? 3 : 0});
   return it == index.end() ? nullptr : it->second;
 }
 
@@ -162,7 +167,9 @@ int check_sched(const alcop_problem& p, const alcop_sched& s, const KernelEntry*
   // variant 3, the waves of a block split the reduction axis: one register stage, no L2 touches, no
   // split-K
   if (s.variant == 3 && (s.reg_stages != 1 || s.l2_prefetch != 0 || sk != 0)) return ALCOP_ERR_SCHED;
-  if (s.variant != 0 && s.variant != 2 && s.variant != 3 &&
+  // variant 4, the resident patch for any geometry: whether the patch fits depends on the call
+  if (s.variant == 4 && (p.op != ALCOP_OP_CONV2D || s.l2_prefetch != 0 || sk != 0)) return ALCOP_ERR_SCHED;
+  if (s.variant != 0 && s.variant != 2 && s.variant != 3 && s.variant != 4 &&
       !(s.variant == 1 && p.op == ALCOP_OP_CONV2D && !p.transB && p.conv_C == s.bk && sk == 0))
     return ALCOP_ERR_SCHED;
   // variant 2, the persistent producer / consumer kernels: two register stages (fused across
@@ -193,7 +200,7 @@ int default_l2_prefetch(int bk) { return 256 / bk; }
 // feasibility depends on the call, not only on the problem description) and the kernels with a
 // k-tile of 128 (two stages of a 128 x 128 tile fill the LDS: a trade the tuner should measure),
 // and the persistent kernels with the consumers' deep register pipeline (no faster where measured).
-bool opt_in(const KernelEntry& e) { return e.am == 3 || e.bk == 128 || (e.st == 1 && e.reg_stages == 4) || e.st == 2; }
+bool opt_in(const KernelEntry& e) { return e.am >= 3 || e.bk == 128 || (e.st == 1 && e.reg_stages == 4) || e.st == 2; }
 
 // variants: 0 = the default kernels; 1 = also the opt-in kernels; 2 = only those.
 std::vector<alcop_sched> space_of(const alcop_problem& p, int sk = 0, int variants = 0)
@@ -202,12 +209,13 @@ std::vector<alcop_sched> space_of(const alcop_problem& p, int sk = 0, int varian
   for (const KernelEntry& e : registry())
     if (e.sk == sk && e.dt == (int)p.in && e.bl == (p.transB ? 1 : 0) &&
         e.al == (p.transA ? 1 : 0) &&
-        (e.am == 3 ? (p.op == ALCOP_OP_CONV2D && p.conv_C == e.bk) : e.am == a_mode(p, e.bk, 0)) &&
+        (e.am == 3 ? (p.op == ALCOP_OP_CONV2D && p.conv_C == e.bk)
+         : e.am == 4 ? p.op == ALCOP_OP_CONV2D : e.am == a_mode(p, e.bk, 0)) &&
         (variants == 1 || (variants == 2) == opt_in(e)))
     {
       // a kernel with the third (HBM -> L2) level is offered with that level on
       v.push_back(alcop_sched{e.bm, e.bn, e.bk, e.wm, e.wn, e.stages, e.reg_stages, e.fuse, 1,
-                              e.pf ? default_l2_prefetch(e.bk) : 0, e.am == 3 ? 1 : e.st == 1 ? 2 : e.st == 2 ? 3 : 0});
+                              e.pf ? default_l2_prefetch(e.bk) : 0, e.am == 3 ? 1 : e.am == 4 ? 4 : e.st == 1 ? 2 : e.st == 2 ? 3 : 0});
     }
   return v;
 }
@@ -357,10 +365,51 @@ int patch_of(const Call& c, const alcop_sched& s, const KernelEntry* e, Patch* o
   return ALCOP_OK;
 }
 
+// Geometry of the resident patch for any call (schedule variant 4), or an error: what must hold is
+// that the patch, the ring of weights and the chunk table fit the LDS.
+struct Resident {
+  int ws = 0, hs = 0, slots = 0, loads = 0, pitch = 0, chunks = 0, table = 0;
+};
+int resident_of(const Call& c, const alcop_sched& s, const KernelEntry* e, Resident* out)
+{
+  if (c.op != ALCOP_OP_CONV2D) return ALCOP_ERR_SCHED;
+  const bool overlap = c.cPix != 0 && c.cPix != c.cC;          // windows of cC / 8 one-chunk pixels
+  if (overlap && (c.cPix != 8 || c.cS != 1 || c.cpw != 0)) return ALCOP_ERR_SCHED;
+  Resident r;
+  const double rows = (double)c.cH + c.cph, cols = (double)c.cW + c.cpw;
+  if (rows * cols * (c.cN + 1.0) >= 1073741824.0 || c.cPix >= 65536 || c.cC >= 65536 || cols >= 16777216.0)
+    return ALCOP_ERR_SCHED;
+  r.ws = c.cW + c.cpw;
+  r.hs = c.cH + c.cph;
+  // positions from one output pixel to the next: csw, plus row_gap at the end of a row of C, plus
+  // img_gap at the end of an image; they must grow from the first pixel of a tile to its last
+  const double row_gap = (double)c.csh * r.ws - (double)c.cQ * c.csw;
+  const double img_gap = ((double)r.hs - (double)c.cP * c.csh) * r.ws;
+  if (c.csw + row_gap <= 0 || c.csw + row_gap + img_gap <= 0) return ALCOP_ERR_SCHED;
+  const long d = std::min(s.bm, c.M) - 1, pq = (long)c.cP * c.cQ;
+  const double span = (double)d * c.csw + (double)((d + c.cQ - 1) / c.cQ) * std::max(0.0, row_gap) +
+                      (double)((d + pq - 1) / pq) * std::max(0.0, img_gap);
+  const double halo = (c.cR - 1.0) * c.cdh * r.ws + (c.cS - 1.0) * c.cdw;
+  r.chunks = overlap ? 1 : c.cC / 8;
+  const int cp = overlap ? 1 : r.chunks | 1;                   // odd: see alcop_convres.hip.h
+  const double slots = (span + halo + 1 + (overlap ? c.cC / 8 - 1 : 0)) * cp;
+  if (slots > 160 * 64) return ALCOP_ERR_SCHED;                // more than the LDS holds
+  r.slots = (int)slots;
+  r.pitch = cp * 16;
+  r.loads = (r.slots + 1 + 255) / 256;                         // one slot of zeros at least
+  const int wk = 4 / ((s.bm / 64) * (s.bn / 64));
+  if (c.K > 1 << 20) return ALCOP_ERR_SCHED;
+  r.table = convres_table(c.K, wk);
+  if (convres_lds(e->patch_off, e->lds_bytes, r.loads, r.table) > 160 * 1024) return ALCOP_ERR_SCHED;
+  if (out) *out = r;
+  return ALCOP_OK;
+}
+
 // What a schedule needs from the call beyond the problem description.
 int call_feasible(const Call& c, const alcop_sched& s, const KernelEntry* e)
 {
   if (e->am == 3) return patch_of(c, s, e, nullptr);
+  if (e->am == 4) return resident_of(c, s, e, nullptr);
   return ALCOP_OK;
 }
 
@@ -457,6 +506,30 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
       p.patch_loads = pt.loads;
       p.ntm = pt.ntj * c.cN;                 // tiles of padded output positions, per image
       p.group_m = std::min(8, p.ntm);
+    }
+    if (e->am == 4) {
+      Resident r;
+      if (resident_of(c, s, e, &r) != ALCOP_OK) return ALCOP_ERR_SCHED;
+      p.rWs = r.ws;
+      p.rHs = r.hs;
+      p.rslots = r.slots;
+      p.rloads = r.loads;
+      p.rpitch = r.pitch;
+      p.rc8 = r.chunks;
+      p.rdS = c.cdw * r.pitch;
+      p.rdR = c.cdh * r.ws * r.pitch;
+      p.rtab = r.table;
+      const int cp = r.pitch / 16;
+      p.rstep_c = 256 % cp;
+      p.rstep_row = 256 / cp / r.ws;
+      p.rstep_col = 256 / cp % r.ws;
+      p.rQ = FastDiv::of((uint32_t)c.cQ);
+      p.rPQ = FastDiv::of((uint32_t)c.cP * (uint32_t)c.cQ);
+      p.rWsDiv = FastDiv::of((uint32_t)r.ws);
+      p.rImg = FastDiv::of((uint32_t)r.ws * (uint32_t)r.hs);
+      p.rCP = FastDiv::of((uint32_t)(r.pitch / 16));
+      p.rC8 = FastDiv::of((uint32_t)(c.cC / 8));
+      p.rS = FastDiv::of((uint32_t)c.cS);
     }
   }
   dim3 grid((unsigned)(p.ntm * p.ntn), (unsigned)c.batch, 1);

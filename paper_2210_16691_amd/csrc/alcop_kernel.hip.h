@@ -46,6 +46,24 @@
 
 namespace alcop {
 
+// n / d for n < 2^31 without a divide: q = (n + mulhi(n, mul)) >> shift.
+struct FastDiv {
+  uint32_t d, mul, shift;
+  static FastDiv of(uint32_t d)
+  {
+    FastDiv f;
+    f.d = d;
+    f.shift = 0;
+    while ((1ull << f.shift) < d) f.shift++;
+    f.mul = (uint32_t)(((1ull << 32) * ((1ull << f.shift) - d)) / d + 1);
+    return f;
+  }
+  __device__ __forceinline__ uint32_t div(uint32_t n) const
+  {
+    return ((uint32_t)(((uint64_t)n * mul) >> 32) + n) >> shift;
+  }
+};
+
 struct Params {
   const void* A;
   const void* B;
@@ -83,6 +101,13 @@ struct Params {
   // persistent producer / consumer kernels (alcop_stream.hip.h): blocks launched and batch count;
   // block b works on tiles b, b + sgrid, b + 2 sgrid, ... of the ntm * ntn * sbatch tiles
   int sgrid, sbatch;
+  // convolution kernels with a resident patch for any geometry (alcop_convres.hip.h): the images as
+  // rows of rWs positions, rHs rows each; the patch as rslots 16-byte slots (rloads block-wide
+  // loads), rpitch bytes per position of which rc8 chunks hold channels; chunks per tap cC / 8; the
+  // byte distance of neighbouring taps; entries of the chunk table
+  int rWs, rHs, rslots, rloads, rpitch, rc8, rdS, rdR, rtab;
+  int rstep_c, rstep_col, rstep_row;   // 256 slots further: chunks, columns, rows
+  FastDiv rQ, rPQ, rWsDiv, rImg, rCP, rC8, rS;
 };
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));

@@ -20,24 +20,6 @@
 
 namespace alcop {
 
-// n / d for n < 2^31 without a divide: q = (n + mulhi(n, mul)) >> shift.
-struct FastDiv {
-  uint32_t d, mul, shift;
-  static FastDiv of(uint32_t d)
-  {
-    FastDiv f;
-    f.d = d;
-    f.shift = 0;
-    while ((1ull << f.shift) < d) f.shift++;
-    f.mul = (uint32_t)(((1ull << 32) * ((1ull << f.shift) - d)) / d + 1);
-    return f;
-  }
-  __device__ __forceinline__ uint32_t div(uint32_t n) const
-  {
-    return ((uint32_t)(((uint64_t)n * mul) >> 32) + n) >> shift;
-  }
-};
-
 // What a segment's 16-byte chunks hold.
 enum {
   PACK_MAT = 0,   // a matrix: rows of `cols` elements, zero beyond; rows may come in groups of rg

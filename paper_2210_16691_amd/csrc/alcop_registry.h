@@ -14,9 +14,10 @@ struct KernelEntry {
   int sk;   // 1: split-K variant (grid.z slices of the reduction axis, fp32 partial tiles)
   int pf;   // 1: the kernel has the HBM -> L2 touch level (schedules with l2_prefetch > 0)
   int st;   // 1: persistent producer / consumer kernel (schedule variant 2); 2: the waves of a block
-            // split the reduction axis (schedule variant 3)
+            // split the reduction axis (schedule variant 3); 3: convolution with a resident patch for
+            // any geometry (schedule variant 4)
   int lds_bytes, threads, loads_per_stage;
-  int patch_off;   // am == 3: LDS offset of the input patch (its size is per call)
+  int patch_off;   // am == 3, 4: LDS offset of the input patch (its size is per call)
   hipError_t (*launch)(const Params&, dim3, hipStream_t);
   // what the first launch would do besides launching (the opt-in to the kernel's LDS size), so
   // that alcop_init can do it ahead of time; may be null
@@ -41,6 +42,8 @@ void register_pf(std::vector<KernelEntry>&);
 void register_stream(std::vector<KernelEntry>&);
 void register_ksplit(std::vector<KernelEntry>&);
 void register_ksplit_conv(std::vector<KernelEntry>&);
+void register_convres_rsck(std::vector<KernelEntry>&);
+void register_convres_krsc(std::vector<KernelEntry>&);
 void register_splitk_gemm(std::vector<KernelEntry>&);
 void register_splitk_conv(std::vector<KernelEntry>&);
 

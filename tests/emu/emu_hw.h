@@ -51,6 +51,7 @@
 #include "alcop_kernel.hip.h"
 #include "alcop_stream.hip.h"
 #include "alcop_ksplit.hip.h"
+#include "alcop_convres.hip.h"
 
 namespace emu {
 
@@ -475,6 +476,16 @@ struct Emu {
     }
     return v;
   }
+  static uint32_t lds_read4(uint32_t addr)
+  {
+    wave_sync();
+    uint32_t v = 0;
+    if (const unsigned char* p = lds_ptr(addr, 4, 4, "ds_read_b32")) {
+      memcpy(&v, p, 4);
+      note_read(addr, 4);
+    }
+    return v;
+  }
   static u32x2 lds_read_tr8(uint32_t addr)
   {
     Block& b = *blk();
@@ -694,6 +705,12 @@ template <class C>
 void ksplit_entry(const void* p)
 {
   alcop::alcop_ksplit<C, Emu>(*(const alcop::Params*)p);
+}
+
+template <class C>
+void convres_entry(const void* p)
+{
+  alcop::alcop_convres<C, Emu>(*(const alcop::Params*)p);
 }
 
 }  // namespace emu

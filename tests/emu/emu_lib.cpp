@@ -57,6 +57,22 @@ void add_ksplit(std::vector<KernelEntry>& t)
                           &launch_emulated_ksplit<C>});
 }
 
+template <class C>
+hipError_t launch_emulated_convres(const Params& p, dim3 grid, hipStream_t)
+{
+  emu::run_grid(&emu::convres_entry<C>, &p, C::NT, (uint32_t)convres_lds(C::RING_BYTES, C::MIN_LDS, p.rloads, p.rtab),
+                grid.x, grid.y, grid.z);
+  return hipSuccess;
+}
+
+template <int DT, int BM, int BN, int S, int BL>
+void add_convres(std::vector<KernelEntry>& t)
+{
+  using C = RCfg<DT, BM, BN, S, BL>;
+  t.push_back(KernelEntry{DT, BM, BN, 64, 64, 64, S, 2, 1, BL, 4, 0, 0, 0, 3, C::MIN_LDS, C::NT, C::L, C::RING_BYTES,
+                          &launch_emulated_convres<C>});
+}
+
 #if EMU_PART == 0
 void emu_part_0(std::vector<KernelEntry>& t)
 {
@@ -264,6 +280,23 @@ void register_ksplit_conv(std::vector<KernelEntry>& t)
   add_ksplit<0, 32, 32, 8, 2, 1, 1>(t);
   add_ksplit<0, 32, 32, 8, 2, 0, 2>(t);
   add_ksplit<1, 32, 64, 4, 2, 1, 2>(t);
+}
+
+void register_convres_rsck(std::vector<KernelEntry>& t)
+{
+  // the resident patch for any geometry (schedule variant 4)
+  add_convres<0, 256, 64, 3, 0>(t);
+  add_convres<0, 128, 128, 2, 0>(t);
+  add_convres<0, 128, 64, 3, 0>(t);
+  add_convres<1, 64, 128, 2, 0>(t);
+  add_convres<0, 64, 64, 2, 0>(t);
+}
+void register_convres_krsc(std::vector<KernelEntry>& t)
+{
+  add_convres<1, 256, 64, 2, 1>(t);
+  add_convres<0, 128, 128, 3, 1>(t);
+  add_convres<1, 128, 64, 2, 1>(t);
+  add_convres<0, 64, 64, 2, 1>(t);
 }
 
 static void reduce_entry(const void* p)
