@@ -485,7 +485,9 @@ int alcop_sched_ranked(const alcop_problem* prob /* host */, int model, int vari
  * tuning cache if there is one (written by alcop_tune or alcop_cache_load), else the library's
  * pick: the lowest of the measured costs of a few kernels (csrc/alcop_dispatch.h), or, where those
  * are within 3 % of it or do not cover the problem, the feasible schedule with the lowest predicted
- * latency under model 0.  Host only, launches nothing.
+ * latency under model 0.  A convolution call without a schedule also considers the kernels with a
+ * resident patch (variants 1 and 4), which depend on its image geometry and are left out here.
+ * Host only, launches nothing.
  */
 int alcop_sched_auto(const alcop_problem* prob /* host */, alcop_sched* out /* host */);
 

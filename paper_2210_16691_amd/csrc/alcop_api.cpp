@@ -222,7 +222,11 @@ std::vector<alcop_sched> space_of(const alcop_problem& p, int sk = 0, int varian
 
 using CacheKey = std::tuple<int, int, int, int, int, int, int, int, int, int>;
 std::mutex g_cache_mu;
-std::map<CacheKey, alcop_sched> g_cache;   // problem -> chosen schedule (tuned or the library's pick)
+struct CacheEntry {
+  alcop_sched s;
+  bool tuned;      // by alcop_tune or a cache file; else the library's pick
+};
+std::map<CacheKey, CacheEntry> g_cache;    // problem -> chosen schedule
 
 CacheKey key_of(const alcop_problem& p)
 {
@@ -251,6 +255,37 @@ int model_pick(const alcop_problem& p, alcop_sched* out)
   return have ? ALCOP_OK : ALCOP_ERR_SCHED;
 }
 
+// Replaces *out by the convolution kernel with the lowest measured cost.  Without a call (only the
+// problem is known) the kernels with a resident patch, whose feasibility depends on its geometry,
+// are left out.
+int resident_loads(const Call& c, const alcop_sched& s, const KernelEntry* e);
+double patch_row_tiles(const Call& c, const alcop_sched& s, const KernelEntry* e);
+void conv_pick(const alcop_problem& p, const Call* c, alcop_sched* out)
+{
+  double best = 0;
+  bool have = false;
+  for (const MeasuredConv& m : kMeasuredConv) {
+    const KernelEntry* e = nullptr;
+    if (m.am != a_mode(p, m.s.bk, m.s.variant) || !measured_conv_applies(p, m) ||
+        check_sched(p, m.s, &e) != ALCOP_OK)
+      continue;
+    double tiles = (p.M + m.s.bm - 1) / m.s.bm;
+    int loads = 0;
+    if (m.am >= 3) {
+      if (!c) continue;
+      if (m.am == 3) tiles = patch_row_tiles(*c, m.s, e);
+      if (m.am == 4) loads = resident_loads(*c, m.s, e);
+      if (tiles < 0 || loads < 0) continue;
+    }
+    const double us = measured_conv_us(p, m, tiles, loads);
+    if (!have || us < best) {
+      have = true;
+      best = us;
+      *out = m.s;
+    }
+  }
+}
+
 // The library's own pick: the cheapest by measured cost (alcop_dispatch.h).  A near tie (3 %) goes to
 // the model's pick, and so do problems the measurements do not cover.
 int library_pick(const alcop_problem& p, alcop_sched* out)
@@ -273,11 +308,11 @@ int library_pick(const alcop_problem& p, alcop_sched* out)
     return ALCOP_OK;
   }
   *out = model;
+  if (rc == ALCOP_OK && p.op == ALCOP_OP_CONV2D) conv_pick(p, nullptr, out);
   return rc;
 }
 
-// What a NULL / zero schedule resolves to: the tuning cache, else the library's pick.
-int auto_sched(const alcop_problem& p, alcop_sched* out)
+void load_env_cache()
 {
   // a tuning cache named by the environment is merged in once, before the first lookup
   static std::once_flag env_once;
@@ -285,18 +320,56 @@ int auto_sched(const alcop_problem& p, alcop_sched* out)
     const char* path = std::getenv("ALCOP_TUNE_CACHE");
     if (path && *path) (void)load_cache_file(path);
   });
+}
+
+// What a NULL / zero schedule resolves to: the tuning cache, else the library's pick.
+int auto_sched(const alcop_problem& p, alcop_sched* out)
+{
+  load_env_cache();
   {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     auto it = g_cache.find(key_of(p));
     if (it != g_cache.end()) {
-      *out = it->second;
+      *out = it->second.s;
       return ALCOP_OK;
     }
   }
   const int rc = library_pick(p, out);
   if (rc) return rc;
   std::lock_guard<std::mutex> lk(g_cache_mu);
-  g_cache[key_of(p)] = *out;
+  g_cache.emplace(key_of(p), CacheEntry{*out, false});
+  return ALCOP_OK;
+}
+
+// The same for a convolution call, whose image geometry decides which patch kernels can serve it: a
+// tuned schedule of the problem, else the pick for this geometry.
+using GeometryKey = std::array<int, 21>;
+std::map<GeometryKey, alcop_sched> g_conv_picks;       // under g_cache_mu
+constexpr size_t kConvPicks = 4096;
+int auto_conv_sched(const Call& c, const alcop_problem& p, alcop_sched* out)
+{
+  load_env_cache();
+  const GeometryKey key{p.M,   p.N,   p.K,   p.transB, (int)p.in, (int)p.out, p.conv_C, c.cN, c.cH, c.cW, c.cR,
+                        c.cS,  c.csh, c.csw, c.cph,    c.cpw,     c.cdh,      c.cdw,    c.cP, c.cQ, c.cPix};
+  {
+    std::lock_guard<std::mutex> lk(g_cache_mu);
+    const auto it = g_cache.find(key_of(p));
+    if (it != g_cache.end() && it->second.tuned) {
+      *out = it->second.s;
+      return ALCOP_OK;
+    }
+    const auto pick = g_conv_picks.find(key);
+    if (pick != g_conv_picks.end()) {
+      *out = pick->second;
+      return ALCOP_OK;
+    }
+  }
+  const int rc = auto_sched(p, out);         // refuses what no default kernel serves
+  if (rc) return rc;
+  conv_pick(p, &c, out);
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  if (g_conv_picks.size() >= kConvPicks) g_conv_picks.clear();
+  g_conv_picks[key] = *out;
   return ALCOP_OK;
 }
 
@@ -403,6 +476,17 @@ int resident_of(const Call& c, const alcop_sched& s, const KernelEntry* e, Resid
   if (convres_lds(e->patch_off, e->lds_bytes, r.loads, r.table) > 160 * 1024) return ALCOP_ERR_SCHED;
   if (out) *out = r;
   return ALCOP_OK;
+}
+
+int resident_loads(const Call& c, const alcop_sched& s, const KernelEntry* e)
+{
+  Resident r;
+  return resident_of(c, s, e, &r) == ALCOP_OK ? r.loads : -1;
+}
+double patch_row_tiles(const Call& c, const alcop_sched& s, const KernelEntry* e)
+{
+  Patch pt;
+  return patch_of(c, s, e, &pt) == ALCOP_OK ? (double)pt.ntj * c.cN : -1.0;
 }
 
 // What a schedule needs from the call beyond the problem description.
@@ -603,7 +687,7 @@ int run(const Call& c, const alcop_sched* sched, void* stream)
   alcop_sched s;
   const bool automatic = !sched || sched->bm == 0;
   if (automatic) {
-    rc = auto_sched(prob, &s);
+    rc = c.op == ALCOP_OP_CONV2D ? auto_conv_sched(c, prob, &s) : auto_sched(prob, &s);
     if (rc) return rc;
   } else {
     s = *sched;
@@ -616,9 +700,10 @@ int run(const Call& c, const alcop_sched* sched, void* stream)
   rc = call_feasible(c, s, e);
   if (rc && automatic && s.variant != 0) {
     // the cached schedule was tuned on a call with another geometry (the cache key is the
-    // problem description): fall back to the model's pick for this call
+    // problem description): fall back to the library's pick for this call
     rc = model_pick(prob, &s);
     if (rc) return rc;
+    conv_pick(prob, &c, &s);
     rc = check_sched(prob, s, &e);
     if (rc) return rc;
     rc = span_check(c, s);
@@ -1642,7 +1727,7 @@ int alcop_tune(const alcop_problem* prob, const void* A, const void* B, void* C,
   }
   if (trials_run) *trials_run = done;
   std::lock_guard<std::mutex> lk(g_cache_mu);
-  g_cache[key_of(p)] = *best;
+  g_cache[key_of(p)] = CacheEntry{*best, true};
   return ALCOP_OK;
 }
 
@@ -1697,7 +1782,7 @@ int alcop_cache_save(const char* path)
     std::lock_guard<std::mutex> lk(g_cache_mu);
     for (const auto& kv : g_cache) {
       const CacheKey& k = kv.first;
-      const alcop_sched& s = kv.second;
+      const alcop_sched& s = kv.second.s;
       // key order: op batch M N K transB in out conv_C transA
       std::fprintf(f, "%d %d %d %d %d %d %d %d %d %d : %d %d %d %d %d %d %d %d %d %d %d\n", std::get<0>(k),
                    std::get<1>(k), std::get<2>(k), std::get<3>(k), std::get<4>(k), std::get<9>(k),
@@ -1748,7 +1833,7 @@ int load_cache_file(const char* path)
     p.conv_C = cc;
     if (check_sched(p, s, nullptr) != ALCOP_OK) continue;   // not runnable here: ignore the entry
     std::lock_guard<std::mutex> lk(g_cache_mu);
-    g_cache[key_of(p)] = s;
+    g_cache[key_of(p)] = CacheEntry{s, true};
     n++;
   }
   std::fclose(f);

@@ -86,6 +86,52 @@ def test_non_finite_data_and_refusals():
         assert al.alcop_sched_supported(gemm, _sched((64, 64, 2))) == al.ERR_SCHED
 
 
+# one problem description (M = 128, K = 576, 64 channels), four geometries: what a patch kernel may
+# serve differs, so the library's pick must follow the call and not the problem
+SAME = [(2, 8, 8, 64, 72, 3, 3, (1, 1), (1, 1), (1, 1)), (2, 16, 16, 64, 72, 3, 3, (2, 2), (1, 1), (1, 1)),
+        (1, 2, 64, 64, 72, 3, 3, (1, 1), (1, 1), (1, 1)), (2, 8, 8, 64, 72, 3, 3, (1, 1), (2, 2), (2, 2))]
+
+
+@pytest.mark.parametrize("krsc", [0, 1])
+def test_default_pick_on_the_cpu_model(krsc):
+    for n, g in enumerate(SAME + GEOM + SAME[::-1]):
+        x, w, bias, ref = _case(g, "f16", krsc)
+        y = torch.full(ref.shape, float("nan"))
+        errs = emu.call(_run, x, w, y, g, bias, krsc, None, reads=[x, w, bias], writes=[y], policy=emu.POLICIES[n % 4])
+        assert not errs, (g, errs[:4])
+        assert np.array_equal(y.double().numpy(), ref), g
+
+
+def test_a_loaded_schedule_wins_over_the_pick(tmp_path):
+    # ... and one that this geometry cannot use gives way to the pick
+    g = SAME[1]
+    f = tmp_path / "cache"
+    f.write_text("2 1 128 72 576 0 0 0 2 64 : 128 64 64 64 32 2 2 0 1 0 1\n")
+    x, w, bias, ref = _case(g, "f16", 0)
+    with emu._swapped():
+        assert al.alcop_cache_load(str(f)) == 1
+        prob = al.problem(al.OP_CONV2D, 128, 72, 576, al.F16, al.F32, conv_C=64)
+        assert al.alcop_sched_auto(prob).variant == 1
+    for g in SAME[:2]:                             # stride 1 takes it, stride 2 cannot
+        x, w, bias, ref = _case(g, "f16", 0)
+        y = torch.full(ref.shape, float("nan"))
+        errs = emu.call(_run, x, w, y, g, bias, 0, None, reads=[x, w, bias], writes=[y])
+        assert not errs and np.array_equal(y.double().numpy(), ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dt,krsc", [("f16", 0), ("f16", 1), ("bf16", 0)])
+def test_default_pick_on_the_gpu(dt, krsc):
+    # few tiles, many, patches, odd channels: every kind of kernel the pick knows
+    for g in SAME + GEOM + [(8, 28, 28, 64, 64, 3, 3, (1, 1), (1, 1), (1, 1)), (3, 14, 14, 256, 192, 3, 3, (1, 1), (1, 1), (1, 1)),
+                            (2, 33, 31, 288, 64, 5, 5, (1, 1), (2, 2), (1, 1)), (16, 40, 40, 32, 136, 1, 1, (1, 1), (0, 0), (1, 1))]:
+        x, w, bias, ref = _case(g, dt, krsc)
+        y = torch.full(ref.shape, float("nan"), device="cuda")
+        _run(x.cuda(), w.cuda(), y, g, bias.cuda(), krsc, None)
+        torch.cuda.synchronize()
+        assert np.array_equal(y.cpu().double().numpy(), ref), g
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("krsc", [0, 1])
 @pytest.mark.parametrize("dt", ["f16", "bf16"])
