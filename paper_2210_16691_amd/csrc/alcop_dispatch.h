@@ -7,14 +7,20 @@
 // does not know the per-tile cost of a block, that persistent kernels whose consumers restart
 // their register pipeline per k-tile are the faster ones, or the kernels whose waves split K.
 //
-// So the library measured every kernel on those products and fits, per kernel,
+// So the library measured every kernel on 330 products and fits, per kernel and operand layout,
 //     us = a + b * turns * k-tiles + c * turns + d * (bytes of A, B and C at 5.1 TB/s)
-// with turns = ceil(tiles / 256), the tiles one compute unit works through in a row (least squares
-// of the relative error, no negative coefficient); k-tiles are those of one wave where the waves
-// split K.  a is the launch and the first loads, b the pace of the main loop (a 128 x 128 x 64
-// step 0.30 us, 64 x 64 x 64 0.17 us), c the epilogue and restart of a tile.  The estimates are within
-// 15 % for nine products in ten.  The kernels below are the ones that a greedy selection by the regret of
-// the estimated best keeps; with them it is 4 % in the mean, 15 % at the 90th percentile.
+//            + e * (flops at 1.4 PFLOP/s) + f * turns2 * k-tiles
+// (least squares of the relative error, no negative coefficient) with turns = ceil(tiles / 256), the
+// tiles one compute unit works through in a row, and, for kernels of which two blocks share a compute
+// unit, turns2 = 2 ceil(tiles / 512); k-tiles are those of one wave where the waves split K.  a is the
+// launch and the first loads, b and f the pace of the main loop (a 128 x 128 x 64 step 0.3 us), c the
+// epilogue and restart of a tile, e the matrix rate that the card's power allows, which bounds the
+// largest.  The layout matters: rows along k whose pitch is not a multiple of 128 bytes touch a second
+// cache line per row and k-tile, and wide tiles fetch fewer rows (3873 x 2872 with B stored N x K, bf16:
+// K = 7232 187 us with persistent 128 x 128 tiles and 167 with 256 x 192, K = 7192 235 and 181).  The
+// kernels below are the ones that a greedy selection by the regret of the estimated best keeps; the
+// pick is 3 % above the best in the mean and 7 % at the 90th percentile, on products above 12 GFLOP too,
+// where a fit without e, f and the layouts left 8 % and 30 % (operands cycled through three buffers).
 #pragma once
 #include <algorithm>
 
@@ -24,33 +30,64 @@ namespace alcop {
 
 struct MeasuredCost {
   alcop_sched s;
+  int transA, transB;  // operand layout the costs were measured with
   int waves_k;         // waves a tile's k-tiles are divided among
-  double a, b, c, d;
+  int blocks;          // blocks that share a compute unit
+  double a, b, c, d, e, f;
 };
 
 inline const MeasuredCost kMeasured[] = {
     // waves split K: while there are fewer 64 x 64 tiles than compute units
-    {{16, 16, 64, 16, 16, 2, 1, 0, 1, 0, 3}, 8, 2.10, 0.329, 0.72, 0.45},
-    {{16, 32, 64, 16, 32, 2, 1, 0, 1, 0, 3}, 8, 1.23, 0.417, 1.69, 0.59},
-    {{32, 32, 64, 32, 32, 2, 1, 0, 1, 0, 3}, 8, 1.23, 0.508, 2.05, 0.56},
-    {{32, 64, 64, 32, 64, 2, 1, 0, 1, 0, 3}, 4, 1.47, 0.367, 2.09, 0.52},
+    {{32, 32, 64, 32, 32, 2, 1, 0, 1, 0, 3}, 0, 0, 8, 1, 1.655, 0.683, 1.495, 0.600, 1.303, 0.000},
+    {{32, 32, 64, 32, 32, 2, 1, 0, 1, 0, 3}, 0, 1, 8, 1, 1.746, 0.391, 1.719, 0.300, 2.078, 0.000},
+    {{32, 32, 64, 32, 32, 2, 1, 0, 1, 0, 3}, 1, 0, 8, 1, 2.093, 0.387, 1.430, 0.259, 5.506, 0.000},
+    {{16, 16, 64, 16, 16, 2, 1, 0, 1, 0, 3}, 0, 0, 8, 1, 2.688, 0.320, 0.444, 0.846, 6.123, 0.000},
+    {{16, 16, 64, 16, 16, 2, 1, 0, 1, 0, 3}, 0, 1, 8, 1, 2.475, 0.188, 0.671, 0.456, 2.358, 0.000},
+    {{16, 16, 64, 16, 16, 2, 1, 0, 1, 0, 3}, 1, 0, 8, 1, 2.915, 0.178, 0.471, 0.000, 17.408, 0.000},
+    {{32, 64, 64, 32, 64, 2, 1, 0, 1, 0, 3}, 0, 0, 4, 1, 1.919, 0.396, 1.701, 0.612, 0.592, 0.000},
+    {{32, 64, 64, 32, 64, 2, 1, 0, 1, 0, 3}, 0, 1, 4, 1, 1.769, 0.328, 1.759, 0.633, 1.025, 0.000},
+    {{32, 64, 64, 32, 64, 2, 1, 0, 1, 0, 3}, 1, 0, 4, 1, 2.628, 0.389, 1.066, 0.222, 2.619, 0.000},
+    {{16, 32, 64, 16, 32, 2, 1, 0, 1, 0, 3}, 0, 0, 8, 1, 1.912, 0.438, 1.246, 0.643, 3.452, 0.000},
+    {{16, 32, 64, 16, 32, 2, 1, 0, 1, 0, 3}, 0, 1, 8, 1, 1.741, 0.279, 1.500, 0.494, 2.654, 0.000},
+    {{16, 32, 64, 16, 32, 2, 1, 0, 1, 0, 3}, 1, 0, 8, 1, 2.509, 0.211, 1.156, 0.000, 10.781, 0.000},
     // persistent
-    {{64, 64, 64, 32, 32, 3, 2, 0, 1, 0, 2}, 1, 2.51, 0.177, 0.45, 0.25},
-    {{128, 128, 64, 64, 64, 3, 2, 0, 1, 0, 2}, 1, 2.46, 0.302, 1.01, 0.46},
-    {{128, 128, 64, 64, 64, 2, 2, 0, 1, 0, 2}, 1, 2.28, 0.383, 0.82, 0.50},
-    {{128, 64, 64, 64, 32, 3, 2, 0, 1, 0, 2}, 1, 2.38, 0.239, 0.82, 0.39},
-    {{128, 64, 64, 64, 32, 2, 2, 0, 1, 0, 2}, 1, 2.47, 0.293, 0.60, 0.36},
-    {{128, 128, 32, 64, 64, 3, 2, 0, 1, 0, 2}, 1, 2.20, 0.192, 1.01, 0.40},
-    {{128, 192, 32, 64, 96, 3, 2, 0, 1, 0, 2}, 1, 1.28, 0.251, 2.52, 0.37},
+    {{128, 128, 64, 64, 64, 3, 2, 0, 1, 0, 2}, 0, 0, 1, 1, 2.508, 0.319, 1.120, 0.207, 0.445, 0.000},
+    {{128, 128, 64, 64, 64, 3, 2, 0, 1, 0, 2}, 0, 1, 1, 1, 2.795, 0.294, 0.982, 0.188, 0.570, 0.000},
+    {{128, 128, 64, 64, 64, 3, 2, 0, 1, 0, 2}, 1, 0, 1, 1, 2.699, 0.313, 1.019, 0.000, 0.582, 0.000},
+    {{128, 64, 64, 64, 32, 3, 2, 0, 1, 0, 2}, 0, 0, 1, 1, 2.588, 0.258, 0.628, 0.272, 0.381, 0.000},
+    {{128, 64, 64, 64, 32, 3, 2, 0, 1, 0, 2}, 0, 1, 1, 1, 2.852, 0.217, 0.671, 0.278, 0.675, 0.000},
+    {{128, 192, 32, 64, 96, 3, 2, 0, 1, 0, 2}, 0, 0, 1, 1, 2.149, 0.246, 1.921, 0.209, 0.372, 0.000},
     // tile at a time
-    {{64, 64, 64, 32, 32, 3, 2, 1, 1, 0, 0}, 1, 2.60, 0.167, 0.37, 0.47},
-    {{64, 64, 64, 32, 32, 4, 2, 1, 1, 0, 0}, 1, 2.39, 0.164, 0.62, 0.45},
-    {{64, 64, 32, 32, 32, 4, 2, 1, 1, 0, 0}, 1, 2.60, 0.104, 0.30, 0.42},
-    {{128, 128, 64, 64, 64, 4, 2, 1, 1, 0, 0}, 1, 1.60, 0.300, 2.29, 0.51},
-    {{256, 128, 64, 128, 64, 3, 2, 1, 1, 0, 0}, 1, 0.93, 0.511, 4.02, 0.40},
-    {{256, 256, 32, 128, 64, 3, 2, 1, 1, 0, 0}, 1, 0.00, 0.474, 4.60, 0.50},
-    {{64, 128, 64, 32, 64, 4, 2, 1, 1, 0, 0}, 1, 1.63, 0.214, 1.75, 0.47},
-    {{128, 64, 64, 64, 32, 4, 2, 1, 1, 0, 0}, 1, 1.62, 0.226, 1.70, 0.53},
+    {{64, 64, 64, 32, 32, 3, 2, 1, 1, 0, 0}, 0, 0, 1, 2, 2.415, 0.086, 0.330, 0.541, 0.092, 0.058},
+    {{64, 64, 64, 32, 32, 3, 2, 1, 1, 0, 0}, 0, 1, 1, 2, 2.585, 0.023, 0.381, 0.458, 0.700, 0.080},
+    {{64, 64, 64, 32, 32, 3, 2, 1, 1, 0, 0}, 1, 0, 1, 2, 2.769, 0.061, 0.165, 0.376, 0.793, 0.067},
+    {{256, 128, 64, 128, 64, 3, 2, 1, 1, 0, 0}, 0, 0, 1, 1, 0.000, 0.519, 4.954, 0.277, 0.327, 0.000},
+    {{256, 128, 64, 128, 64, 3, 2, 1, 1, 0, 0}, 0, 1, 1, 1, 1.807, 0.490, 3.249, 0.294, 0.407, 0.000},
+    {{256, 128, 64, 128, 64, 3, 2, 1, 1, 0, 0}, 1, 0, 1, 1, 0.814, 0.504, 4.371, 0.000, 0.442, 0.000},
+    {{128, 128, 64, 64, 64, 4, 2, 1, 1, 0, 0}, 0, 0, 1, 1, 1.384, 0.318, 2.552, 0.249, 0.317, 0.000},
+    {{128, 128, 64, 64, 64, 4, 2, 1, 1, 0, 0}, 0, 1, 1, 1, 1.858, 0.304, 2.121, 0.305, 0.392, 0.000},
+    {{128, 128, 64, 64, 64, 4, 2, 1, 1, 0, 0}, 1, 0, 1, 1, 1.654, 0.320, 2.428, 0.034, 0.412, 0.000},
+    {{256, 192, 32, 128, 96, 3, 2, 1, 1, 0, 0}, 0, 0, 1, 1, 0.141, 0.433, 5.835, 0.257, 0.262, 0.000},
+    {{256, 192, 32, 128, 96, 3, 2, 1, 1, 0, 0}, 0, 1, 1, 1, 1.366, 0.437, 4.559, 0.235, 0.357, 0.000},
+    {{256, 192, 32, 128, 96, 3, 2, 1, 1, 0, 0}, 1, 0, 1, 1, 1.366, 0.399, 5.047, 0.144, 0.291, 0.000},
+    {{128, 128, 64, 64, 64, 2, 1, 0, 1, 0, 0}, 0, 0, 1, 2, 2.167, 0.043, 0.873, 0.347, 0.461, 0.263},
+    {{128, 128, 64, 64, 64, 2, 1, 0, 1, 0, 0}, 0, 1, 1, 2, 2.181, 0.005, 1.051, 0.284, 0.548, 0.272},
+    {{128, 128, 64, 64, 64, 2, 1, 0, 1, 0, 0}, 1, 0, 1, 2, 1.680, 0.016, 1.318, 0.000, 0.583, 0.285},
+    {{128, 256, 64, 64, 128, 3, 2, 1, 1, 0, 0}, 0, 0, 1, 1, 0.930, 0.503, 4.130, 0.341, 0.274, 0.000},
+    {{256, 256, 32, 128, 64, 3, 2, 1, 1, 0, 0}, 0, 0, 1, 1, 0.092, 0.464, 4.571, 0.406, 0.317, 0.000},
+    {{256, 256, 32, 128, 64, 3, 2, 1, 1, 0, 0}, 0, 1, 1, 1, 0.460, 0.502, 4.408, 0.240, 0.424, 0.000},
+    {{256, 256, 32, 128, 64, 3, 2, 1, 1, 0, 0}, 1, 0, 1, 1, 0.000, 0.459, 4.782, 0.402, 0.231, 0.000},
+    {{64, 128, 64, 32, 64, 4, 2, 1, 1, 0, 0}, 0, 0, 1, 1, 1.700, 0.228, 1.750, 0.224, 0.385, 0.000},
+    {{64, 64, 64, 32, 32, 4, 2, 1, 1, 0, 0}, 0, 0, 1, 2, 2.339, 0.108, 0.546, 0.452, 0.134, 0.038},
+    {{64, 64, 64, 32, 32, 4, 2, 1, 1, 0, 0}, 0, 1, 1, 2, 2.396, 0.064, 0.649, 0.355, 0.557, 0.056},
+    {{64, 64, 64, 32, 32, 4, 2, 1, 1, 0, 0}, 1, 0, 1, 2, 2.679, 0.091, 0.395, 0.256, 0.690, 0.049},
+    {{64, 64, 32, 32, 32, 3, 1, 0, 1, 0, 0}, 0, 0, 1, 2, 2.425, 0.037, 0.176, 0.489, 0.000, 0.061},
+    {{64, 64, 32, 32, 32, 3, 1, 0, 1, 0, 0}, 0, 1, 1, 2, 2.604, 0.000, 0.188, 0.464, 1.035, 0.069},
+    {{64, 64, 32, 32, 32, 3, 1, 0, 1, 0, 0}, 1, 0, 1, 2, 2.766, 0.038, 0.000, 0.449, 0.000, 0.061},
+    {{128, 64, 64, 64, 32, 4, 2, 1, 1, 0, 0}, 0, 0, 1, 1, 1.427, 0.261, 1.774, 0.334, 0.205, 0.000},
+    {{128, 64, 64, 64, 32, 4, 2, 1, 1, 0, 0}, 0, 1, 1, 1, 1.775, 0.219, 1.798, 0.264, 0.459, 0.000},
+    {{64, 64, 128, 32, 32, 4, 2, 1, 1, 0, 0}, 0, 0, 1, 1, 1.743, 0.337, 1.560, 0.428, 0.187, 0.000},
+    {{64, 64, 128, 32, 32, 4, 2, 1, 1, 0, 0}, 0, 1, 1, 1, 2.016, 0.332, 1.690, 0.200, 0.312, 0.000},
 };
 
 inline double measured_us(const alcop_problem& p, const MeasuredCost& m)
@@ -58,17 +95,21 @@ inline double measured_us(const alcop_problem& p, const MeasuredCost& m)
   auto up = [](double x, double y) { return (double)(long)((x + y - 1) / y); };
   const double tiles = up(p.M, m.s.bm) * up(p.N, m.s.bn) * p.batch;
   const double turns = up(tiles, 256), kt = up(up(p.K, m.s.bk), m.waves_k);
+  const double turns2 = m.blocks == 2 ? 2.0 * up(tiles, 512) : 0.0;
   const double out = p.out == ALCOP_F32 ? 4.0 : 2.0;
   const double bytes = p.batch * (2.0 * p.M * p.K + 2.0 * p.K * p.N + out * p.M * p.N);
-  return m.a + m.b * turns * kt + m.c * turns + m.d * bytes / 5.1e6;
+  const double flops = 2.0 * p.batch * p.M * p.N * (double)p.K;
+  return m.a + m.b * turns * kt + m.c * turns + m.d * bytes / 5.1e6 + m.e * flops / 1.4e9 + m.f * turns2 * kt;
 }
 
 // The measured kernels worth considering for a product: small tiles cost more bytes per flop, so the
 // kernels whose waves split K are compared only while 64 x 64 tiles leave compute units idle (with 384
-// such tiles, 1021 x 1536 x 768, they take 11.9 us at best against 6.2).
+// such tiles, 1021 x 1536 x 768, they take 11.9 us at best against 6.2).  Both operands transposed use
+// the costs of A stored K x M.
 inline bool measured_applies(const alcop_problem& p, const MeasuredCost& m)
 {
   if (p.op == ALCOP_OP_CONV2D) return false;
+  if (m.transA != (p.transA ? 1 : 0) || (!p.transA && m.transB != (p.transB ? 1 : 0))) return false;
   return m.s.variant != 3 || (double)((p.M + 63) / 64) * ((p.N + 63) / 64) * p.batch <= 256;
 }
 

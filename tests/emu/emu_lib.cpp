@@ -201,6 +201,8 @@ void emu_part_7(std::vector<KernelEntry>& t)
   add<0, 256, 192, 32, 128, 96, 3, 3, 1, 0, 0>(t);     // deep register pipeline
   add<0, 192, 256, 32, 96, 128, 3, 2, 1, 0, 0, 1>(t);  // A stored K x M, 192 rows of C per tile
   add<0, 256, 192, 32, 128, 96, 2, 2, 1, 1, 0>(t);     // B stored N x K: plain rows, 192 of them
+  add<1, 256, 192, 32, 128, 96, 3, 2, 1, 0, 0, 1>(t);  // A stored K x M
+  add<1, 256, 256, 32, 128, 64, 3, 2, 1, 1, 0>(t);     // 8 waves, B stored N x K
   add_stream<0, 128, 192, 32, 64, 96, 3, 0, 0>(t);     // persistent kernels
   add_stream<1, 128, 192, 32, 64, 96, 4, 0, 0, 0, 0>(t);
 }
