@@ -119,6 +119,27 @@ def test_a_loaded_schedule_wins_over_the_pick(tmp_path):
         assert not errs and np.array_equal(y.double().numpy(), ref)
 
 
+@pytest.mark.parametrize("tile", [(256, 64, 3), (128, 128, 2), (128, 64, 3), (64, 64, 2)])
+def test_windows_that_overlap(tile, tmp_path, monkeypatch, capfd):
+    # an RGB image laid out as two pixels per chunk: the gather's pixels are 8 elements apart, its windows
+    # 32 elements long (224 deep with 7 filter rows); the schedule is loaded for that inner product
+    N, H, W, C, K, R, S, stride, pad = 2, 13, 14, 3, 64, 7, 7, (2, 2), (3, 3)
+    x, w = wl.small_ints((N, H, W, C), "f16", 9103), wl.small_ints((R, S, C, K), "f16", 9264)
+    ref = oracle.conv2d(wl.bits(x), wl.bits(w), oracle.F16, stride, pad)
+    f = tmp_path / "cache"
+    f.write_text("2 1 98 64 224 0 0 0 0 32 : %s\n" % " ".join(map(str, _sched(tile).key())))
+    y = torch.full(ref.shape, float("nan"), dtype=torch.float16)
+    ws = torch.empty(al.alcop_conv2d_unaligned_workspace_bytes(N, H, W, C, K, R, S, stride, pad, (1, 1), al.F16),
+                     dtype=torch.uint8)
+    monkeypatch.setenv("ALCOP_LOG", "1")
+    with emu._swapped():
+        assert al.alcop_cache_load(str(f)) == 1
+    errs = emu.call(al.alcop_conv2d_igemm_unaligned, x, w, y, ws, stride, pad, reads=[x, w], writes=[y, ws])
+    assert "variant 4" in capfd.readouterr().err
+    assert not errs, errs[:4]
+    assert np.array_equal(y.double().numpy(), ref)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("dt,krsc", [("f16", 0), ("f16", 1), ("bf16", 0)])
 def test_default_pick_on_the_gpu(dt, krsc):
