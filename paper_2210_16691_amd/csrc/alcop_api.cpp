@@ -66,6 +66,7 @@ struct Call {
   int cN, cH, cW, cC, cK, cR, cS, csh, csw, cph, cpw, cP, cQ;
   int cdh, cdw;   // dilation
   int cPix;       // elements between pixels of x if not cC (0)
+  int ragged;     // of the 8 elements of a window's last chunk, those inside the window (0: all)
   // C without 16-byte chunks: its valid rows and columns if not M and N (0), any element alignment
   int Mv, Nv, c_any;
   // fused epilogue
@@ -260,6 +261,7 @@ int model_pick(const alcop_problem& p, alcop_sched* out)
 // are left out.
 int resident_loads(const Call& c, const alcop_sched& s, const KernelEntry* e);
 double patch_row_tiles(const Call& c, const alcop_sched& s, const KernelEntry* e);
+bool ragged_ok(const Call& c, const KernelEntry* e);
 void conv_pick(const alcop_problem& p, const Call* c, alcop_sched* out)
 {
   double best = 0;
@@ -267,7 +269,7 @@ void conv_pick(const alcop_problem& p, const Call* c, alcop_sched* out)
   for (const MeasuredConv& m : kMeasuredConv) {
     const KernelEntry* e = nullptr;
     if (m.am != a_mode(p, m.s.bk, m.s.variant) || !measured_conv_applies(p, m) ||
-        check_sched(p, m.s, &e) != ALCOP_OK)
+        check_sched(p, m.s, &e) != ALCOP_OK || (c && !ragged_ok(*c, e)))
       continue;
     double tiles = (p.M + m.s.bm - 1) / m.s.bm;
     int loads = 0;
@@ -343,14 +345,15 @@ int auto_sched(const alcop_problem& p, alcop_sched* out)
 
 // The same for a convolution call, whose image geometry decides which patch kernels can serve it: a
 // tuned schedule of the problem, else the pick for this geometry.
-using GeometryKey = std::array<int, 21>;
+using GeometryKey = std::array<int, 22>;
 std::map<GeometryKey, alcop_sched> g_conv_picks;       // under g_cache_mu
 constexpr size_t kConvPicks = 4096;
 int auto_conv_sched(const Call& c, const alcop_problem& p, alcop_sched* out)
 {
   load_env_cache();
   const GeometryKey key{p.M,   p.N,   p.K,   p.transB, (int)p.in, (int)p.out, p.conv_C, c.cN, c.cH, c.cW, c.cR,
-                        c.cS,  c.csh, c.csw, c.cph,    c.cpw,     c.cdh,      c.cdw,    c.cP, c.cQ, c.cPix};
+                        c.cS,  c.csh, c.csw, c.cph,    c.cpw,     c.cdh,      c.cdw,    c.cP, c.cQ, c.cPix,
+                        c.ragged};
   {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     const auto it = g_cache.find(key_of(p));
@@ -478,6 +481,22 @@ int resident_of(const Call& c, const alcop_sched& s, const KernelEntry* e, Resid
   return ALCOP_OK;
 }
 
+// Windows that end inside a chunk: only the kernels with a resident patch clear what lies past them.
+bool ragged_ok(const Call& c, const KernelEntry* e) { return c.ragged == 0 || (e->am == 4 && e->bl == 0); }
+
+// Whether one of those kernels that the pick knows can serve such a call.
+bool ragged_fits(const Call& c)
+{
+  const alcop_problem p = problem_of(c);
+  for (const MeasuredConv& m : kMeasuredConv) {
+    const KernelEntry* e = nullptr;
+    if (m.am == 4 && check_sched(p, m.s, &e) == ALCOP_OK && ragged_ok(c, e) &&
+        resident_of(c, m.s, e, nullptr) == ALCOP_OK)
+      return true;
+  }
+  return false;
+}
+
 int resident_loads(const Call& c, const alcop_sched& s, const KernelEntry* e)
 {
   Resident r;
@@ -492,6 +511,7 @@ double patch_row_tiles(const Call& c, const alcop_sched& s, const KernelEntry* e
 // What a schedule needs from the call beyond the problem description.
 int call_feasible(const Call& c, const alcop_sched& s, const KernelEntry* e)
 {
+  if (!ragged_ok(c, e)) return ALCOP_ERR_SCHED;
   if (e->am == 3) return patch_of(c, s, e, nullptr);
   if (e->am == 4) return resident_of(c, s, e, nullptr);
   return ALCOP_OK;
@@ -614,6 +634,9 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
       p.rCP = FastDiv::of((uint32_t)(r.pitch / 16));
       p.rC8 = FastDiv::of((uint32_t)(c.cC / 8));
       p.rS = FastDiv::of((uint32_t)c.cS);
+      p.ragged = c.ragged != 0;
+      for (int e = 4; e < 8; e++)
+        if (e < c.ragged) p.rkeep[(e - 4) / 2] |= 0xffffu << (16 * (e & 1));
     }
   }
   dim3 grid((unsigned)(p.ntm * p.ntn), (unsigned)c.batch, 1);
@@ -698,7 +721,7 @@ int run(const Call& c, const alcop_sched* sched, void* stream)
   rc = span_check(c, s);
   if (rc) return rc;
   rc = call_feasible(c, s, e);
-  if (rc && automatic && s.variant != 0) {
+  if (rc && automatic) {
     // the cached schedule was tuned on a call with another geometry (the cache key is the
     // problem description): fall back to the library's pick for this call
     rc = model_pick(prob, &s);
@@ -1079,6 +1102,9 @@ int pack_epilogue(const alcop_epilogue* ep, int N, char* ws_bias, Call* inner, P
 //                the left padding is made explicit, px pixels share a 16-byte chunk, and since every
 //                window starts on a chunk its whole filter row is ceil(S / px) consecutive chunks.
 //                The gather sees a filter S = 1 wide with that many channels, whose windows overlap.
+//                If px does not divide S, the last chunk's pixels past the filter are data of other
+//                windows: only the kernels that clear them take the call (Call::ragged), and only
+//                where at least half of that chunk is the window's.
 //   window form  one window per output column: the S * C elements of a filter row, padded to 8.
 // The pixel form multiplies 8 / C times as much padding as data: a 7 x 7 stem on RGB reduces over
 // 392 elements instead of 147 (pair form: 224).  Picked by bytes: the image is written and read
@@ -1091,10 +1117,29 @@ struct XForm {
   int chans, taps;        // channels per tap, taps per filter row
   int stride, pad;        // horizontal stride and padding left for the gather
   bool padded;            // left padding is part of the image
+  int ragged = 0;         // pair: as in Call
 };
 
-XForm choose_xform(int N, int H, int W, int C, int R, int S, int sw, int pw, int dw, long Q, long M, double x_room)
+// The call on such an image, given the call on the pixel form.
+void apply_xform(const XForm& f, Call* c)
 {
+  if (!f.padded) return;
+  c->K = c->cR * f.chans;
+  c->lda = c->K;
+  c->cW = f.width;
+  c->cC = f.chans;
+  c->cPix = f.pix;
+  c->cS = 1;
+  c->csw = f.stride;
+  c->cpw = 0;
+  c->ragged = f.ragged;
+}
+
+// c: the call on the pixel form
+XForm choose_xform(const Call& c, int C, double x_room)
+{
+  const int N = c.cN, H = c.cH, W = c.cW, R = c.cR, S = c.cS, sw = c.csw, pw = c.cpw, dw = c.cdw;
+  const long Q = c.cQ, M = c.M;
   const int c8 = (int)r8(C);
   const XForm plain{PACK_PIX, c8, 1, 0, W, c8, c8, S, sw, pw, false};
   auto bytes = [&](const XForm& f) { return 2.0 * N * H * f.width * f.pix; };
@@ -1103,15 +1148,22 @@ XForm choose_xform(int N, int H, int W, int C, int R, int S, int sw, int pw, int
   if (C % 8 == 0 || dw != 1) return plain;
   auto consider = [&](const XForm& f) {
     if (f.width < 1 || bytes(f) >= 2147483648.0 || r256(bytes(f)) > x_room) return;
-    if (cost(f) < cost(best)) best = f;
+    if (cost(f) >= cost(best)) return;
+    if (f.ragged) {
+      Call t = c;
+      apply_xform(f, &t);
+      if (!ragged_fits(t)) return;
+    }
+    best = f;
   };
   if (C <= 4) {
     const int cg = C <= 1 ? 1 : C <= 2 ? 2 : 4, px = 8 / cg;
     if (sw % px == 0) {
       const int ch = (S + px - 1) / px;
       const long last = (Q - 1) * (sw / px) + ch;          // chunks a row must have
-      if (last < 0x3fffffff)
-        consider(XForm{PACK_PIX, cg, px, ch, (int)last, 8, 8 * ch, 1, sw / px, 0, true});
+      const int in = 8 - (ch * px - S) * cg;               // elements of the last chunk in the window
+      if (last < 0x3fffffff && in >= 4)
+        consider(XForm{PACK_PIX, cg, px, ch, (int)last, 8, 8 * ch, 1, sw / px, 0, true, in < 8 ? in : 0});
     }
   }
   if ((double)S * C < 65536.0 && Q < 0x3fffffff)
@@ -1492,28 +1544,19 @@ int alcop_conv2d_igemm_unaligned(const void* x, const void* w, void* y, int N, i
   const bool x_ok = aligned16(x) && C % 8 == 0, w_ok = aligned16(w) && C % 8 == 0 && K % 8 == 0;
   const double x_room = (double)(need - r256(2.0 * R * S * c8 * k8) - r256(4.0 * k8));
   const bool automatic = !sched || sched->bm == 0;
-  const XForm f = automatic ? choose_xform(N, H, W, C, R, S, stride_w, pad_w, dil_w, Q, outputs, x_room)
-                            : choose_xform(N, H, W, c8, R, S, stride_w, pad_w, dil_w, Q, outputs, 0.0);
+  Call c;
+  int rc = conv_call(&c, x, w, y, N, H, W, c8, k8, R, S, stride_h, stride_w, pad_h, pad_w, in, out, 0, dil_h, dil_w);
+  if (rc) return rc;
+  const XForm f = choose_xform(c, automatic ? C : c8, x_room);
   const size_t w_off = f.padded ? r256(2.0 * N * H * f.width * f.pix) : off[1];
   const size_t b_off = f.padded ? w_off + r256(2.0 * R * f.chans * k8) : off[3];
   if (b_off + r256(4.0 * k8) > need) return ALCOP_ERR_SIZE;   // cannot happen: forms are chosen to fit
-  Call c;
-  int rc = conv_call(&c, x_ok ? x : ws, w_ok ? w : ws + w_off, y, N, H, W, c8, k8, R, S, stride_h, stride_w,
-                     pad_h, pad_w, in, out, 0, dil_h, dil_w);
-  if (rc) return rc;
+  apply_xform(f, &c);
+  if (!x_ok) c.A = ws;
+  if (!w_ok) c.B = ws + w_off;
   c.Nv = K;
   c.ldc = K;
   c.c_any = !(aligned16(y) && K % 8 == 0);
-  if (f.padded) {
-    c.K = R * f.chans;
-    c.lda = c.K;
-    c.cW = f.width;
-    c.cC = f.chans;
-    c.cPix = f.pix;
-    c.cS = 1;
-    c.csw = f.stride;
-    c.cpw = 0;
-  }
   Packer pk;
   rc = pack_epilogue(ep, K, ws + b_off, &c, &pk);
   if (rc) return rc;

@@ -107,6 +107,10 @@ struct Params {
   // byte distance of neighbouring taps; entries of the chunk table
   int rWs, rHs, rslots, rloads, rpitch, rc8, rdS, rdR, rtab;
   int rstep_c, rstep_col, rstep_row;   // 256 slots further: chunks, columns, rows
+  // windows whose last chunk runs past the filter row: the bits of the chunk's third and fourth word
+  // that belong to the window (ragged: any do not)
+  int ragged;
+  uint32_t rkeep[2];
   FastDiv rQ, rPQ, rWsDiv, rImg, rCP, rC8, rS;
 };
 

@@ -57,10 +57,10 @@ void add_ksplit(std::vector<KernelEntry>& t)
                           &launch_emulated_ksplit<C>});
 }
 
-template <class C>
+template <class C, class D>
 hipError_t launch_emulated_convres(const Params& p, dim3 grid, hipStream_t)
 {
-  emu::run_grid(&emu::convres_entry<C>, &p, C::NT, (uint32_t)convres_lds(C::RING_BYTES, C::MIN_LDS, p.rloads, p.rtab),
+  emu::run_grid(p.ragged ? &emu::convres_entry<D> : &emu::convres_entry<C>, &p, C::NT, (uint32_t)convres_lds(C::RING_BYTES, C::MIN_LDS, p.rloads, p.rtab),
                 grid.x, grid.y, grid.z);
   return hipSuccess;
 }
@@ -69,8 +69,9 @@ template <int DT, int BM, int BN, int S, int BL>
 void add_convres(std::vector<KernelEntry>& t)
 {
   using C = RCfg<DT, BM, BN, S, BL>;
+  using D = RCfg<DT, BM, BN, S, BL, BL == 0>;
   t.push_back(KernelEntry{DT, BM, BN, 64, 64, 64, S, 2, 1, BL, 4, 0, 0, 0, 3, C::MIN_LDS, C::NT, C::L, C::RING_BYTES,
-                          &launch_emulated_convres<C>});
+                          &launch_emulated_convres<C, D>});
 }
 
 #if EMU_PART == 0
