@@ -233,11 +233,12 @@ int alcop_conv2d_igemm_dilated(const void* x, const void* w, void* y, int N, int
  * filled by asynchronous copies; here they move 16-byte chunks, hence the alignment rules of
  * alcop_gemm): N or K not a multiple of 8, M not a multiple of 8 with transA, leading dimensions,
  * batch strides or base addresses that are not 16-byte aligned.  Those of A, B (and the bias) that
- * break the rules are copied into `workspace`, all in one launch, with every extent rounded up to
- * 8 elements and the tails zero-filled; the ordinary kernels compute the product there (same
- * schedules, same k order; the extra k terms are exact zeros, so every valid element equals what an
- * aligned call on the same values returns) and store the valid M x N part straight to C; bytes of C
- * outside the valid elements (row padding) are not touched.  One small copy kernel besides the product.
+ * break the rules, or whose memory C shares (C may lie on any of them), are copied into
+ * `workspace`, all in one launch, with every extent rounded up to 8 elements and the tails
+ * zero-filled; the ordinary kernels compute the product there (same schedules, same k order; the
+ * extra k terms are exact zeros, so every valid element equals what an aligned call on the same
+ * values returns) and store the valid M x N part straight to C; bytes of C outside the valid
+ * elements (row padding) are not touched.  One small copy kernel besides the product.
  *   A, B, C: DEVICE pointers aligned to their element size; lda, ldb, ldc, strides in elements,
  *     any value allowed by the shape (lda >= K or M, ...); batch = 1 with strides 0 is a GEMM.
  *   ep: host, may be NULL; ep->bias: DEVICE pointer to N fp32 values, 4-byte aligned.

@@ -1034,6 +1034,13 @@ size_t unaligned_layout(double a_elems, double b_elems, double c_elems, long n8,
 
 bool elem_aligned(const void* p, int esize) { return (reinterpret_cast<uintptr_t>(p) & (uintptr_t)(esize - 1)) == 0; }
 
+// Whether two ranges of memory share bytes (addresses and sizes are exact as doubles, or far too large).
+bool meets(const void* p, double p_bytes, const void* q, double q_bytes)
+{
+  const double a = (double)reinterpret_cast<uintptr_t>(p), b = (double)reinterpret_cast<uintptr_t>(q);
+  return a < b + q_bytes && b < a + p_bytes;
+}
+
 // Collects the segments of a call's one pack launch.
 struct Packer {
   PackParams p;
@@ -1080,8 +1087,8 @@ struct Packer {
 };
 
 // The fused epilogue of the inner call; a bias the kernels cannot read as it is (four values at a
-// time, up to the padded N) joins the pack launch.
-int pack_epilogue(const alcop_epilogue* ep, int N, char* ws_bias, Call* inner, Packer* pk)
+// time, up to the padded N), or that the result overwrites, joins the pack launch.
+int pack_epilogue(const alcop_epilogue* ep, int N, char* ws_bias, double c_bytes, Call* inner, Packer* pk)
 {
   if (!ep) return ALCOP_OK;
   inner->alpha = ep->alpha;
@@ -1090,7 +1097,7 @@ int pack_epilogue(const alcop_epilogue* ep, int N, char* ws_bias, Call* inner, P
   if (!ep->bias) return ALCOP_OK;
   if (!elem_aligned(ep->bias, 4)) return ALCOP_ERR_ALIGN;
   inner->bias = ep->bias;
-  if (aligned16(ep->bias) && N % 8 == 0) return ALCOP_OK;
+  if (aligned16(ep->bias) && N % 8 == 0 && !meets(ep->bias, 4.0 * N, inner->C, c_bytes)) return ALCOP_OK;
   pk->matrix(ep->bias, ws_bias, 1, 1, N, 0, N, 1, (int)r8(N), 4);
   inner->bias = ws_bias;
   return ALCOP_OK;
@@ -1462,11 +1469,17 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
   if (need == 0 || workspace_bytes < need) return ALCOP_ERR_SIZE;
   char* ws = (char*)workspace;
   hipStream_t st = (hipStream_t)hip_stream;
-  // An operand is used where it lies if its chunks are whole and aligned; otherwise it is padded
-  // into the workspace, each batch entry a dense matrix.  Rows of A (stored M x K) need no padding.
+  // An operand is used where it lies if its chunks are whole and aligned and the result does not
+  // overwrite it; otherwise it is padded into the workspace, each batch entry a dense matrix.  Rows of
+  // A (stored M x K) need no padding.
+  auto bytes = [&](int esize, long ld, long stride, int rows, int cols) {
+    return esize * ((batch - 1.0) * stride + (rows - 1.0) * ld + cols);
+  };
+  const double c_bytes = bytes(osz, ldc, strideC, M, N);
   auto in_place = [&](const void* p, long ld, long stride, int rows, int cols) {
     return aligned16(p) && ld % 8 == 0 && (batch == 1 || stride % 8 == 0) && cols % 8 == 0 && K % 8 == 0 &&
-           2.0 * ((double)rows * ld) < 2147483648.0;
+           2.0 * ((double)rows * ld) < 2147483648.0 &&
+           !meets(p, bytes(2, ld, stride, rows, cols), C, c_bytes);
   };
   const int a_rows = transA ? K : M, a_cols = transA ? M : K, a_rd = transA ? k8 : M, a_cd = transA ? m8 : k8;
   const int b_rows = transB ? N : K, b_cols = transB ? K : N, b_rd = transB ? n8 : k8, b_cd = transB ? k8 : n8;
@@ -1480,7 +1493,7 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
   c.Nv = N;
   c.c_any = !(aligned16(C) && N % 8 == 0 && ldc % 8 == 0 && (batch == 1 || strideC % 8 == 0));
   Packer pk;
-  int rc = pack_epilogue(ep, N, ws + off[3], &c, &pk);
+  int rc = pack_epilogue(ep, N, ws + off[3], c_bytes, &c, &pk);
   if (rc) return rc;
   if (!a_ok) pk.matrix(A, ws + off[0], batch, a_rows, a_cols, strideA, lda, a_rd, a_cd, 2);
   if (!b_ok) pk.matrix(B, ws + off[1], batch, b_rows, b_cols, strideB, ldb, b_rd, b_cd, 2);
@@ -1540,8 +1553,11 @@ int alcop_conv2d_igemm_unaligned(const void* x, const void* w, void* y, int N, i
   if (need == 0 || workspace_bytes < need) return ALCOP_ERR_SIZE;
   char* ws = (char*)workspace;
   hipStream_t st = (hipStream_t)hip_stream;
+  // used where they lie: whole aligned chunks that the result does not overwrite
+  const double y_bytes = (double)osz * outputs * K;
+  const bool x_ok = aligned16(x) && C % 8 == 0 && !meets(x, 2.0 * pixels * C, y, y_bytes);
+  const bool w_ok = aligned16(w) && C % 8 == 0 && K % 8 == 0 && !meets(w, 2.0 * R * S * C * K, y, y_bytes);
   // the image the gather sees; an explicit schedule is one for the pixel form
-  const bool x_ok = aligned16(x) && C % 8 == 0, w_ok = aligned16(w) && C % 8 == 0 && K % 8 == 0;
   const double x_room = (double)(need - r256(2.0 * R * S * c8 * k8) - r256(4.0 * k8));
   const bool automatic = !sched || sched->bm == 0;
   Call c;
@@ -1558,7 +1574,7 @@ int alcop_conv2d_igemm_unaligned(const void* x, const void* w, void* y, int N, i
   c.ldc = K;
   c.c_any = !(aligned16(y) && K % 8 == 0);
   Packer pk;
-  rc = pack_epilogue(ep, K, ws + b_off, &c, &pk);
+  rc = pack_epilogue(ep, K, ws + b_off, y_bytes, &c, &pk);
   if (rc) return rc;
   if (!x_ok) {
     PackSeg& g = pk.add(f.kind, x, ws, 1, f.padded ? (long)N * H : pixels, f.padded ? (long)f.width * f.pix / 8 : c8 / 8, 2);

@@ -1,0 +1,107 @@
+"""The unaligned entry points read operands that need no padding where they lie.  What a copy of
+every operand used to guarantee must still hold, here on the CPU model of the hardware: the result
+may lie on an operand."""
+import numpy as np
+import pytest
+import torch
+
+import emu_util as emu
+import oracle
+import paper_2210_16691_amd as al
+import workloads as wl
+
+
+def _odd(t):
+    """A copy of t at an address that is a multiple of its element size only."""
+    v = torch.zeros(t.numel() + 1, dtype=t.dtype)[1:].view(t.shape)
+    return v.copy_(t)
+
+
+def _aligned(*shape, dtype=torch.float16):
+    n = int(np.prod(shape))
+    buf = torch.zeros(n + 64, dtype=dtype)
+    off = (-buf.data_ptr() % 64) // buf.element_size()
+    return buf[off:off + n].view(*shape)
+
+
+def _mm(A, B, C, **kw):
+    M, K = A.shape[-2:][::-1] if kw.get("transA") else A.shape[-2:]
+    code = {torch.float16: al.F16, torch.float32: al.F32}[C.dtype]
+    ws = torch.empty(al.alcop_unaligned_workspace_bytes(A.shape[0] if A.dim() == 3 else 1, M, C.shape[-1], K, code),
+                     dtype=torch.uint8)
+    bias = kw.get("bias")
+    return emu.call(al.alcop_bmm_unaligned, A, B, C, ws, reads=[A, B] + ([] if bias is None else [bias]),
+                    writes=[C, ws], **kw)
+
+
+def _ref(A, B, tA=False, tB=False):
+    return oracle.gemm(wl.bits(A.contiguous()), wl.bits(B.contiguous()), oracle.F16, tA, tB)
+
+
+@pytest.mark.parametrize("on", ["A", "B", "A_shifted", "A_transposed"])
+def test_a_product_may_overwrite_its_operand(on):
+    M, N, K = (130, 200, 200) if on[0] == "A" else (200, 136, 200)
+    if on == "A_transposed":
+        M = N = K = 200
+    A0, B0 = wl.small_ints((M, K), "f16", 31), wl.small_ints((K, N), "f16", 32)
+    ref = _ref(A0, B0, on == "A_transposed")
+    mem = _aligned(250, 200)
+    if on[0] == "A":
+        A, B = mem[:M], _odd(B0)
+        A.copy_(A0)
+        C = mem[40:40 + M] if on == "A_shifted" else mem[:M]
+    else:
+        A, B = _odd(A0), mem.view(-1)[:K * N].view(K, N)
+        B.copy_(B0)
+        C = mem.view(-1)[:M * N].view(M, N)
+    errs = _mm(A, B, C, transA=on == "A_transposed")
+    assert not errs, errs[:4]
+    assert np.array_equal(C.double().numpy(), ref)
+
+
+def test_a_batched_product_may_overwrite_another_entry():
+    b, M, N, K = 3, 72, 64, 64
+    A0, B0 = wl.small_ints((b, M, K), "f16", 33), wl.small_ints((b, K, N), "f16", 34)
+    mem = _aligned(b + 1, M, K)
+    A, C = mem[:b], mem[1:]                 # entry i of C on entry i + 1 of A
+    A.copy_(A0)
+    errs = _mm(A, _odd(B0), C)
+    assert not errs, errs[:4]
+    for i in range(b):
+        assert np.array_equal(C[i].double().numpy(), _ref(A0[i], B0[i])), i
+
+
+def test_a_product_may_overwrite_its_bias():
+    M, N, K = 200, 64, 24
+    A0, B0 = wl.small_ints((M, K), "f16", 35), wl.small_ints((K, N), "f16", 36)
+    C = _aligned(M, N, dtype=torch.float32)
+    bias = C[0]
+    bias.copy_(torch.arange(N) % 9 - 4)
+    ref = oracle.epilogue(_ref(A0, B0), 1.0, bias.double().numpy(), 0)
+    errs = _mm(_odd(A0), B0, C, bias=bias)
+    assert not errs, errs[:4]
+    assert np.array_equal(C.double().numpy(), ref)
+
+
+@pytest.mark.parametrize("on", ["x", "w", "bias"])
+def test_a_convolution_may_overwrite_its_operand(on):
+    N, H, W, C, K = 1, 20, 18, 16, 16
+    x0, w0 = wl.small_ints((N, H, W, C), "f16", 37), wl.small_ints((3, 3, C, K), "f16", 38)
+    ref = oracle.conv2d(wl.bits(x0), wl.bits(w0), oracle.F16, (1, 1), (1, 1))
+    b0 = torch.arange(K, dtype=torch.float32) % 7 - 3
+    ref = oracle.epilogue(ref.reshape(-1, K), 1.0, b0.double().numpy(), 0).reshape(ref.shape)
+    y = _aligned(N, H, W, K, dtype=torch.float32 if on == "bias" else torch.float16)
+    flat = y.view(-1)
+    x, w, bias = _odd(x0), _odd(w0), b0.clone()
+    if on == "x":
+        x = flat.view(x0.shape).copy_(x0)
+    elif on == "w":
+        w = flat[:w0.numel()].view(w0.shape).copy_(w0)
+    else:
+        bias = flat[:K].copy_(b0)
+    ws = torch.empty(al.alcop_conv2d_unaligned_workspace_bytes(N, H, W, C, K, 3, 3, (1, 1), (1, 1), (1, 1), al.F32),
+                     dtype=torch.uint8)
+    errs = emu.call(al.alcop_conv2d_igemm_unaligned, x, w, y, ws, (1, 1), (1, 1), bias=bias,
+                    reads=[x, w, bias], writes=[y, ws])
+    assert not errs, errs[:4]
+    assert np.array_equal(y.double().numpy(), ref)
