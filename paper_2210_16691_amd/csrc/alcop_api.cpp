@@ -1471,20 +1471,22 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
   hipStream_t st = (hipStream_t)hip_stream;
   // An operand is used where it lies if its chunks are whole and aligned and the result does not
   // overwrite it; otherwise it is padded into the workspace, each batch entry a dense matrix.  Rows of
-  // A (stored M x K) need no padding.
+  // A (stored M x K) need no padding.  Where the rows run along k, span_check counts K rounded up to
+  // whole k-tiles, of 128 at most: an operand that could be refused there is copied as well.
+  const double k_rows = (double)((K + 127L) / 128 * 128);
   auto bytes = [&](int esize, long ld, long stride, int rows, int cols) {
     return esize * ((batch - 1.0) * stride + (rows - 1.0) * ld + cols);
   };
   const double c_bytes = bytes(osz, ldc, strideC, M, N);
-  auto in_place = [&](const void* p, long ld, long stride, int rows, int cols) {
+  auto in_place = [&](const void* p, long ld, long stride, int rows, int cols, bool along_k) {
     return aligned16(p) && ld % 8 == 0 && (batch == 1 || stride % 8 == 0) && cols % 8 == 0 && K % 8 == 0 &&
-           2.0 * ((double)rows * ld) < 2147483648.0 &&
+           2.0 * ((along_k ? k_rows : rows) * ld) < 2147483648.0 &&
            !meets(p, bytes(2, ld, stride, rows, cols), C, c_bytes);
   };
   const int a_rows = transA ? K : M, a_cols = transA ? M : K, a_rd = transA ? k8 : M, a_cd = transA ? m8 : k8;
   const int b_rows = transB ? N : K, b_cols = transB ? K : N, b_rd = transB ? n8 : k8, b_cd = transB ? k8 : n8;
-  const bool a_ok = in_place(A, lda, strideA, a_rows, a_cols);
-  const bool b_ok = in_place(B, ldb, strideB, b_rows, b_cols) && N % 8 == 0;
+  const bool a_ok = in_place(A, lda, strideA, a_rows, a_cols, transA);
+  const bool b_ok = in_place(B, ldb, strideB, b_rows, b_cols, !transB) && N % 8 == 0;
   Call c = gemm_call(batch > 1 ? ALCOP_OP_BMM : ALCOP_OP_GEMM, a_ok ? A : ws + off[0], b_ok ? B : ws + off[1], C,
                      batch, transA ? m8 : M, n8, k8, a_ok ? lda : a_cd, b_ok ? ldb : b_cd, ldc,
                      a_ok ? strideA : (long)a_rd * a_cd, b_ok ? strideB : (long)b_rd * b_cd, strideC, transA,

@@ -105,3 +105,21 @@ def test_a_convolution_may_overwrite_its_operand(on):
                     reads=[x, w, bias], writes=[y, ws])
     assert not errs, errs[:4]
     assert np.array_equal(y.double().numpy(), ref)
+
+
+def test_an_operand_whose_rounded_span_is_too_long_is_copied():
+    # the loaders address K rounded up to a k-tile of rows: 64 rows at this pitch are 4 GiB
+    M, N, K, pitch = 5, 8, 8, 1 << 25
+    A0, B0 = wl.small_ints((M, K), "f16", 41), wl.small_ints((K, N), "f16", 42)
+    buf = torch.empty(K * pitch + 8, dtype=torch.float16)
+    B = buf[-buf.data_ptr() // 2 % 8:].as_strided((K, N), (pitch, 1)).copy_(B0)
+    A, C = _aligned(M, K).copy_(A0), _odd(torch.full((M, N), float("nan"), dtype=torch.float16))
+    assert B.data_ptr() % 16 == 0
+    errs = _mm(A, B, C)
+    assert not errs, errs[:4]
+    assert np.array_equal(C.double().numpy(), _ref(A0, B0))
+    At = buf[-buf.data_ptr() // 2 % 8:].as_strided((K, 8), (pitch, 1)).copy_(B0)       # A stored K x M
+    D = _odd(torch.full((8, N), float("nan"), dtype=torch.float16))
+    errs = _mm(At, _aligned(K, N).copy_(B0), D, transA=True)
+    assert not errs, errs[:4]
+    assert np.array_equal(D.double().numpy(), _ref(B0, B0, True))
