@@ -398,7 +398,8 @@ int check_call(const Call& c)
   if (c.lda < (c.transA ? c.M : c.K) || c.ldb < (c.transB ? c.K : c.N) ||
       c.ldc < (c.c_any ? c.Nv : c.N))
     return ALCOP_ERR_SHAPE;
-  if (c.lda >= (1L << 30) || c.ldb >= (1L << 30) || c.ldc >= (1L << 30)) return ALCOP_ERR_SIZE;
+  // (Mv is set by the unaligned entry points, which take any pitch of C)
+  if (c.lda >= (1L << 30) || c.ldb >= (1L << 30) || (c.ldc >= (1L << 30) && !c.Mv)) return ALCOP_ERR_SIZE;
   return ALCOP_OK;
 }
 
@@ -563,7 +564,7 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
   p.K = c.K;
   p.lda = (int)c.lda;
   p.ldb = (int)c.ldb;
-  p.ldc = (int)c.ldc;
+  p.ldc = c.ldc;
   p.strideA = c.strideA;
   p.strideB = c.strideB;
   p.strideC = c.strideC;

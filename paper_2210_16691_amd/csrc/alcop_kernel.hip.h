@@ -69,7 +69,8 @@ struct Params {
   const void* B;
   void* C;
   int M, N, K;                 // GEMM view
-  int lda, ldb, ldc;           // elements (host guarantees the byte spans fit 31 bits)
+  int lda, ldb;                // elements (host guarantees the byte spans fit 31 bits)
+  long ldc;                    // any pitch: rows of C are addressed with 64 bits
   long strideA, strideB, strideC;
   int out_dtype;               // 0 f16, 1 bf16, 2 f32
   // rows and columns of C that exist (M and N unless the operands are zero-padded images), and

@@ -123,3 +123,37 @@ def test_an_operand_whose_rounded_span_is_too_long_is_copied():
     errs = _mm(At, _aligned(K, N).copy_(B0), D, transA=True)
     assert not errs, errs[:4]
     assert np.array_equal(D.double().numpy(), _ref(B0, B0, True))
+
+
+def _far_rows(device, kind):
+    """Three rows of C 2^30 + 1 elements apart (2^30 + 8 for the aligned form)."""
+    M, N, K, pitch = 3, 24, 40, (1 << 30) + (8 if kind == "aligned" else 1)
+    A0, B0 = wl.small_ints((M, K), "f16", 43), wl.small_ints((K, N), "f16", 44)
+    buf = torch.empty(2 * pitch + N + 8, dtype=torch.float16, device=device)
+    C = buf[-buf.data_ptr() // 2 % 8:].as_strided((M, N), (pitch, 1))
+    C.fill_(float("nan"))
+    return A0, B0, C
+
+
+@pytest.mark.parametrize("kind", ["aligned", "odd", "waves_split_k"])
+def test_rows_of_the_result_may_be_far_apart(kind):
+    A0, B0, C = _far_rows("cpu", kind)
+    s = al.sched(64, 64, 64, 32, 32, 3, 2, 1) if kind != "waves_split_k" else al.sched(16, 16, 64, 16, 16, 2, 1, 0, variant=3)
+    errs = _mm(_odd(A0), B0, C, sched=s)
+    assert not errs, errs[:4]
+    assert np.array_equal(C.double().numpy(), _ref(A0, B0))
+    with pytest.raises(al.AlcopError) as e:            # the other entry points keep their limit
+        emu.call(al.alcop_gemm, A0, B0, C, reads=[A0, B0], writes=[C])
+    assert e.value.code in (al.ERR_SIZE, al.ERR_ALIGN)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["aligned", "odd", "persistent", "waves_split_k"])
+def test_rows_of_the_result_may_be_far_apart_on_the_gpu(kind):
+    A0, B0, C = _far_rows("cuda", kind)
+    s = {"persistent": al.sched(64, 64, 64, 32, 32, 3, 2, 1, variant=2),
+         "waves_split_k": al.sched(16, 16, 64, 16, 16, 2, 1, 0, variant=3)}.get(kind, al.sched(64, 64, 64, 32, 32, 3, 2, 1))
+    ws = torch.empty(al.alcop_unaligned_workspace_bytes(1, 3, 24, 40, al.F16), dtype=torch.uint8, device="cuda")
+    al.alcop_bmm_unaligned(A0.cuda(), B0.cuda(), C, ws, sched=s)
+    torch.cuda.synchronize()
+    assert np.array_equal(C.cpu().double().numpy(), _ref(A0, B0))
