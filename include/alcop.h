@@ -496,7 +496,8 @@ int alcop_sched_auto(const alcop_problem* prob /* host */, alcop_sched* out /* h
  * Tuning cache on disk (the tuner's trial outcome per problem, so that a later process skips the
  * timing).  Text file, one line per problem:
  *   op batch M N K transA transB in out conv_C : bm bn bk wm wn stages reg_stages fuse raster l2 variant
- * (the last number may be missing in files written before the field existed: 0)
+ * (the last number may be missing in files written before the field existed: 0; the word "auto" behind
+ * it marks a pick of the library that no tuning run made, which is read back as such)
  * alcop_cache_save writes every cached entry and returns their number; alcop_cache_load merges
  * the file's entries into the cache (entries that name a schedule this library cannot run for
  * that problem are skipped) and returns the number accepted.  Negative return = alcop_status.

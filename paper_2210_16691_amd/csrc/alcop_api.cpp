@@ -1846,10 +1846,11 @@ int alcop_cache_save(const char* path)
       const CacheKey& k = kv.first;
       const alcop_sched& s = kv.second.s;
       // key order: op batch M N K transB in out conv_C transA
-      std::fprintf(f, "%d %d %d %d %d %d %d %d %d %d : %d %d %d %d %d %d %d %d %d %d %d\n", std::get<0>(k),
+      std::fprintf(f, "%d %d %d %d %d %d %d %d %d %d : %d %d %d %d %d %d %d %d %d %d %d%s\n", std::get<0>(k),
                    std::get<1>(k), std::get<2>(k), std::get<3>(k), std::get<4>(k), std::get<9>(k),
                    std::get<5>(k), std::get<6>(k), std::get<7>(k), std::get<8>(k), s.bm, s.bn, s.bk,
-                   s.wm, s.wn, s.stages, s.reg_stages, s.fuse_inner, s.raster, s.l2_prefetch, s.variant);
+                   s.wm, s.wn, s.stages, s.reg_stages, s.fuse_inner, s.raster, s.l2_prefetch, s.variant,
+                   kv.second.tuned ? "" : " auto");
       n++;
     }
   }
@@ -1894,8 +1895,12 @@ int load_cache_file(const char* path)
     p.out = (alcop_dtype)out;
     p.conv_C = cc;
     if (check_sched(p, s, nullptr) != ALCOP_OK) continue;   // not runnable here: ignore the entry
+    // a pick comes back as one: it replaces no tuned entry, and a convolution call still picks for its
+    // own geometry
+    const bool tuned = std::strstr(line, " auto") == nullptr;
     std::lock_guard<std::mutex> lk(g_cache_mu);
-    g_cache[key_of(p)] = CacheEntry{s, true};
+    CacheEntry& entry = g_cache.emplace(key_of(p), CacheEntry{s, false}).first->second;
+    if (tuned || !entry.tuned) entry = CacheEntry{s, tuned};
     n++;
   }
   std::fclose(f);

@@ -1,0 +1,51 @@
+"""What a saved and reloaded tuning cache does to calls without a schedule, on the CPU model."""
+import re
+
+import numpy as np
+import torch
+
+import emu_util as emu
+import oracle
+import paper_2210_16691_amd as al
+import workloads as wl
+
+
+def _tile(err):
+    return re.findall(r"-> (tile .*) variant (\d)", err)[-1]
+
+
+def test_the_librarys_own_picks_stay_picks_after_save_and_load(tmp_path, monkeypatch, capfd):
+    # the entry of a convolution's problem description knows no image geometry: read back as if it had
+    # been tuned it would keep the kernels with a resident patch from being picked
+    N, H, W, C, K = 1, 13, 11, 16, 80
+    x, w = wl.small_ints((N, H, W, C), "f16", 51), wl.small_ints((3, 3, C, K), "f16", 52)
+    ref = oracle.conv2d(wl.bits(x), wl.bits(w), oracle.F16, (1, 1), (1, 1))
+    f = str(tmp_path / "cache")
+    monkeypatch.setenv("ALCOP_LOG", "1")
+
+    def run():
+        y = torch.full(ref.shape, float("nan"))
+        assert not emu.call(al.alcop_conv2d_igemm, x, w, y, (1, 1), (1, 1), reads=[x, w], writes=[y])
+        assert np.array_equal(y.double().numpy(), ref)
+        return _tile(capfd.readouterr().err)
+
+    first = run()
+    assert first[1] == "4"
+    prob = al.problem(al.OP_CONV2D, N * H * W, K, 9 * C, al.F16, al.F32, conv_C=C)
+    with emu._swapped():
+        plain = al.alcop_sched_auto(prob)
+        assert plain.variant != 4
+        n = al.alcop_cache_save(f)
+        assert n >= 1 and al.alcop_cache_load(f) == n
+        assert al.alcop_sched_auto(prob).key() == plain.key()
+    assert run() == first
+    # a tuned entry survives a file's pick of the same problem, and is one after its own save and load
+    line = [t for t in open(f) if t.startswith("2 1 %d %d %d " % (N * H * W, K, 9 * C))]
+    tuned = tmp_path / "tuned"
+    other = [s for s in emu.space(prob) if s.key() != plain.key()][0]
+    tuned.write_text("%s: %s\n" % (line[0].split(":")[0], " ".join(map(str, other.key()))))
+    with emu._swapped():
+        assert al.alcop_cache_load(str(tuned)) == 1 and al.alcop_cache_load(f) == n
+        assert al.alcop_cache_save(f) == n and al.alcop_cache_load(f) == n
+        assert al.alcop_sched_auto(prob).key() == other.key()
+    assert run() != first
