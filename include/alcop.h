@@ -242,7 +242,8 @@ int alcop_conv2d_igemm_dilated(const void* x, const void* w, void* y, int N, int
  *   A, B, C: DEVICE pointers aligned to their element size; lda, ldb, ldc, strides in elements,
  *     any value allowed by the shape (lda >= K or M, ...); batch = 1 with strides 0 is a GEMM.
  *   ep: host, may be NULL; ep->bias: DEVICE pointer to N fp32 values, 4-byte aligned.
- *   sched: a schedule for the padded problem (M, N, K rounded up to 8), or NULL = the library's pick.
+ *   sched: a schedule for the padded problem (M, N, K rounded up to 8), or NULL = the tuned one of
+ *     that problem, else the library's pick.
  *   workspace: DEVICE memory, 16-byte aligned, at least alcop_unaligned_workspace_bytes(batch, M, N,
  *     K, out) bytes (that function returns 0 for arguments no call accepts); owned by the caller,
  *     overwritten by the call.  Calls that share a workspace must be ordered on one stream.
@@ -259,10 +260,12 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
 /*
  * The same for a convolution whose channel counts are not multiples of 8 (an RGB stem: C = 3) or
  * whose tensors are not 16-byte aligned: x (NHWC) and the weights ([R][S][C][K]) are copied to an
- * image of 16-byte chunks (C rounded up to 8 channels, or, with a NULL schedule and few channels,
- * several pixels or a whole filter row per chunk: fewer zeros to multiply), the convolution runs on
- * the padded tensors (the padding adds exact zeros) and the K valid channels of every output pixel
- * are stored to y (NPQK, dense).  Geometry, dilation and ep as for alcop_conv2d_igemm_dilated;
+ * image of 16-byte chunks (C rounded up to 8 channels, or, with few channels, a NULL schedule and no
+ * tuned one for the problem so padded, several pixels or a whole filter row per chunk: fewer zeros
+ * to multiply), the convolution runs on the padded tensors (padding meets padding only, as exact
+ * zeros; pixels beside a window do not reach it, whatever they hold) and the K valid channels of
+ * every output pixel are stored to y (NPQK, dense).  Which layout is taken also depends on the room
+ * the workspace has for it.  Geometry, dilation and ep as for alcop_conv2d_igemm_dilated;
  * sched: a schedule for the problem padded to C and K rounded up to 8, or NULL.  workspace: at least
  * alcop_conv2d_unaligned_workspace_bytes(...) bytes, otherwise as above.
  */

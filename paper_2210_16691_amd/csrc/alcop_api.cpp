@@ -324,6 +324,17 @@ void load_env_cache()
   });
 }
 
+// The schedule that a tuning run or a cache file left for the problem, if any.
+bool tuned_sched(const alcop_problem& p, alcop_sched* out)
+{
+  load_env_cache();
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  const auto it = g_cache.find(key_of(p));
+  if (it == g_cache.end() || !it->second.tuned) return false;
+  *out = it->second.s;
+  return true;
+}
+
 // What a NULL / zero schedule resolves to: the tuning cache, else the library's pick.
 int auto_sched(const alcop_problem& p, alcop_sched* out)
 {
@@ -1502,6 +1513,13 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
   if (!b_ok) pk.matrix(B, ws + off[1], batch, b_rows, b_cols, strideB, ldb, b_rd, b_cd, 2);
   rc = pk.launch(st);
   if (rc) return rc;
+  // a tuned schedule is one for the padded problem
+  alcop_sched tuned;
+  if (c.M != m8 && (!sched || sched->bm == 0)) {
+    alcop_problem padded = problem_of(c);
+    padded.M = m8;
+    if (tuned_sched(padded, &tuned)) sched = &tuned;
+  }
   return run(c, sched, hip_stream);
 }
 
@@ -1566,7 +1584,9 @@ int alcop_conv2d_igemm_unaligned(const void* x, const void* w, void* y, int N, i
   Call c;
   int rc = conv_call(&c, x, w, y, N, H, W, c8, k8, R, S, stride_h, stride_w, pad_h, pad_w, in, out, 0, dil_h, dil_w);
   if (rc) return rc;
-  const XForm f = choose_xform(c, automatic ? C : c8, x_room);
+  alcop_sched tuned;                  // ... and so is a tuned one
+  const bool compact = C % 8 != 0 && automatic && !tuned_sched(problem_of(c), &tuned);
+  const XForm f = choose_xform(c, compact ? C : c8, x_room);
   const size_t w_off = f.padded ? r256(2.0 * N * H * f.width * f.pix) : off[1];
   const size_t b_off = f.padded ? w_off + r256(2.0 * R * f.chans * k8) : off[3];
   if (b_off + r256(4.0 * k8) > need) return ALCOP_ERR_SIZE;   // cannot happen: forms are chosen to fit
