@@ -168,9 +168,9 @@ def lib() -> ctypes.CDLL:
         import torch  # noqa: F401  (the module below links against it)
 
         from . import _binding as m
-        m.init(*[ctypes.cast(f, ctypes.c_void_p).value for f in
-                 (L.alcop_gemm_fused, L.alcop_bmm_fused, L.alcop_bmm_unaligned, L.alcop_conv2d_igemm_dilated,
-                  L.alcop_conv2d_igemm_unaligned)])
+        m.init(Sched, *[ctypes.cast(f, ctypes.c_void_p).value for f in
+                        (L.alcop_gemm_fused, L.alcop_bmm_fused, L.alcop_bmm_unaligned, L.alcop_conv2d_igemm_dilated,
+                         L.alcop_conv2d_igemm_unaligned)])
         _lib, _marshal, _marshal_lib = L, m, L
     return _lib
 

@@ -25,6 +25,8 @@ struct Api {
   decltype(&alcop_conv2d_igemm_unaligned) conv_any = nullptr;
 } api;
 
+PyObject* sched_type = nullptr;   // the binding's ctypes mirror of alcop_sched
+
 // Raised to leave a call to the Python code.
 struct Unusual {};
 
@@ -51,6 +53,7 @@ alcop_dtype dtype(const at::Tensor& t)
 
 int truth(PyObject* o)
 {
+  need(PyLong_Check(o));            // True and False are integers
   const int v = PyObject_IsTrue(o);
   need(v >= 0);
   return v;
@@ -90,6 +93,8 @@ struct Schedule {
   explicit Schedule(PyObject* o)
   {
     if (o == Py_None) return;
+    const int is = PyObject_IsInstance(o, sched_type);    // any other buffer is not a schedule
+    need(is == 1);
     Py_buffer b;
     need(PyObject_GetBuffer(o, &b, PyBUF_SIMPLE) == 0);
     const bool ok = b.len == (Py_ssize_t)sizeof(s);
@@ -285,18 +290,22 @@ PyObject* conv_any(PyObject*, PyObject* const* a, Py_ssize_t n)
   });
 }
 
-// init(gemm_fused, bmm_fused, bmm_unaligned, conv_dilated, conv_unaligned): addresses in the library
+// init(Sched, gemm_fused, bmm_fused, bmm_unaligned, conv_dilated, conv_unaligned): the class of schedules
+// and addresses in the library
 PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
-  if (n != 5) {
-    PyErr_SetString(PyExc_TypeError, "init takes five addresses");
+  if (n != 6 || !PyType_Check(a[0])) {
+    PyErr_SetString(PyExc_TypeError, "init takes a class and five addresses");
     return nullptr;
   }
   void* f[5];
   for (int i = 0; i < 5; i++) {
-    f[i] = PyLong_AsVoidPtr(a[i]);
+    f[i] = PyLong_AsVoidPtr(a[i + 1]);
     if (PyErr_Occurred()) return nullptr;
   }
+  Py_INCREF(a[0]);
+  Py_XDECREF(sched_type);
+  sched_type = a[0];
   api.gemm = (decltype(api.gemm))f[0];
   api.bmm = (decltype(api.bmm))f[1];
   api.bmm_any = (decltype(api.bmm_any))f[2];

@@ -62,3 +62,17 @@ def test_same_bits_as_the_ctypes_path(case):
         outs.append(C)
     assert not torch.isnan(outs[0]).any()
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
+
+
+@pytest.mark.gpu
+def test_arguments_of_other_types_stay_refused():
+    # 44 bytes of something else have the size of a schedule
+    s = al.sched(64, 64, 64, 32, 32, 3, 2, 1)
+    A = torch.zeros(64, 64, dtype=torch.float16, device="cuda")
+    for other in (bytes(s), bytearray(s), torch.tensor(s.key(), dtype=torch.int32).numpy()):
+        with pytest.raises(TypeError):
+            al.alcop_gemm(A, A, torch.empty_like(A), sched=other)
+    with pytest.raises(TypeError):
+        al.alcop_gemm(A, A, torch.empty_like(A), transB=None)
+    al.alcop_gemm(A, A, torch.empty_like(A), sched=s)
+    torch.cuda.synchronize()
