@@ -13,6 +13,8 @@
 
 #include <c10/hip/HIPStream.h>
 
+#include <string>
+
 #include "../../include/alcop.h"
 
 namespace {
@@ -29,6 +31,11 @@ PyObject* sched_type = nullptr;   // the binding's ctypes mirror of alcop_sched
 
 // Raised to leave a call to the Python code.
 struct Unusual {};
+
+// An exception out of the library's call itself, which is not made a second time.
+struct Failed {
+  std::string what;
+};
 
 inline void need(bool ok)
 {
@@ -159,6 +166,9 @@ PyObject* guarded(F&& f)
   } catch (const Unusual&) {
     PyErr_Clear();
     Py_RETURN_NONE;
+  } catch (const Failed& e) {
+    PyErr_SetString(PyExc_RuntimeError, e.what.c_str());
+    return nullptr;
   } catch (const std::exception&) {   // from the tensor accessors
     PyErr_Clear();
     Py_RETURN_NONE;
@@ -166,15 +176,20 @@ PyObject* guarded(F&& f)
   return PyLong_FromLong(rc);
 }
 
-// The call itself, without the interpreter lock (as ctypes makes it).
+// The call itself, without the interpreter lock (as ctypes makes it), which is taken back however the
+// call ends.
 template <class F>
 int unlocked(F&& f)
 {
-  int rc;
-  Py_BEGIN_ALLOW_THREADS
-  rc = f();
-  Py_END_ALLOW_THREADS
-  return rc;
+  struct Unlock {
+    PyThreadState* state = PyEval_SaveThread();
+    ~Unlock() { PyEval_RestoreThread(state); }
+  } unlock;
+  try {
+    return f();
+  } catch (const std::exception& e) {
+    throw Failed{e.what()};
+  }
 }
 
 // mm(A, B, C, transA, transB, sched, stream[, alpha, bias, act]): 2-D gemm, 3-D batched

@@ -1,5 +1,7 @@
 """The C++ argument marshalling of the hot entry points: leaves to the Python code what it does not
 take, and otherwise makes the same call (same bits) as the ctypes path."""
+import ctypes
+
 import pytest
 import torch
 
@@ -75,4 +77,23 @@ def test_arguments_of_other_types_stay_refused():
     with pytest.raises(TypeError):
         al.alcop_gemm(A, A, torch.empty_like(A), transB=None)
     al.alcop_gemm(A, A, torch.empty_like(A), sched=s)
+    torch.cuda.synchronize()
+
+
+@pytest.mark.gpu
+def test_an_exception_out_of_the_library_is_raised_under_the_interpreter_lock():
+    # the C++ runtime's own thrower in the place of the entry points: nothing is launched
+    al.lib()
+    addr = lambda f: ctypes.cast(f, ctypes.c_void_p).value
+    L = al._lib
+    A = torch.zeros(64, 64, dtype=torch.float16, device="cuda")
+    try:
+        al._marshal.init(al.Sched, *[addr(ctypes.CDLL("libstdc++.so.6")._ZSt17__throw_bad_allocv)] * 5)
+        for _ in range(3):
+            with pytest.raises(RuntimeError):
+                al.alcop_gemm(A, A, torch.empty_like(A))
+    finally:
+        al._marshal.init(al.Sched, *[addr(f) for f in (L.alcop_gemm_fused, L.alcop_bmm_fused, L.alcop_bmm_unaligned,
+                                                       L.alcop_conv2d_igemm_dilated, L.alcop_conv2d_igemm_unaligned)])
+    al.alcop_gemm(A, A, torch.empty_like(A))
     torch.cuda.synchronize()
