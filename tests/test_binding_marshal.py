@@ -29,6 +29,19 @@ def _mm(f, tB=False, tA=False, b=0, pitch=0, **kw):
     return lambda C: f(A, B, C, **dict(kw, **({"transB": tB} if tB else {}), **({"transA": tA} if tA else {})))
 
 
+class _Recorder:
+    """The marshalling module, with the results of its calls written down."""
+
+    def __init__(self, module):
+        self.module, self.results = module, []
+
+    def __getattr__(self, name):
+        def f(*args):
+            self.results.append(getattr(self.module, name)(*args))
+            return self.results[-1]
+        return f
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", ["gemm", "gemm_ta", "fused", "bmm", "bmm_fused", "any", "conv", "krsc", "fusedconv",
                                   "dilated", "convany"])
@@ -53,14 +66,16 @@ def test_same_bits_as_the_ctypes_path(case):
     al.lib()
     outs = []
     for native in (al._lib, None):
-        keep, al._marshal_lib = al._marshal_lib, native
+        module, keep = al._marshal, al._marshal_lib
+        al._marshal, al._marshal_lib = _Recorder(module), native
         try:
             C = torch.full(shape, float("nan"), dtype=torch.float16, device="cuda")
             torch.cuda.synchronize()
             run(C)
             torch.cuda.synchronize()
+            assert al._marshal.results == ([0] if native else [])   # it took the call, or was not asked
         finally:
-            al._marshal_lib = keep
+            al._marshal, al._marshal_lib = module, keep
         outs.append(C)
     assert not torch.isnan(outs[0]).any()
     assert torch.equal(outs[0].view(torch.int16), outs[1].view(torch.int16))
