@@ -214,16 +214,16 @@ def main():
     achieved = flops / (kernel_us * 1e-6) / 1e12
     # context, not the metric: the same schedule on all-zero operands executes the same instruction
     # stream with less switching in the matrix pipes and data paths; what it gains is clock
-    Az, Bz = torch.zeros_like(Ad), torch.zeros_like(Bd)
+    Az, Bz, Cz = torch.zeros_like(Ad), torch.zeros_like(Bd), torch.empty_like(Cd)   # Cd is checked below
     for _ in range(200):
-        al.alcop_gemm(Az, Bz, Cd, best, stream=stream)
+        al.alcop_gemm(Az, Bz, Cz, best, stream=stream)
     e0.record(stream)
     for _ in range(n50):
-        al.alcop_gemm(Az, Bz, Cd, best, stream=stream)
+        al.alcop_gemm(Az, Bz, Cz, best, stream=stream)
     e1.record(stream)
     torch.cuda.synchronize()
     zero_us = e0.elapsed_time(e1) * 1e3 / n50
-    del Az, Bz
+    del Az, Bz, Cz
 
     traffic, traffic_source = None, None
     tf = os.path.join(ROOT, "profiles", "hbm_traffic.json")
