@@ -44,13 +44,18 @@ struct Gfx950 {
   }
 
   // Buffer resource for a wave-uniform base address.  The words are passed through
-  // readfirstlane so that the descriptor provably lives in scalar registers.
+  // readfirstlane so that the descriptor provably lives in scalar registers.  A vector-memory
+  // instruction must not read a scalar register within five wait states of the vector instruction
+  // that wrote it.  The compiler keeps that distance for instructions of its own, not for those in
+  // inline asm (dma16), and a load that reads a stale base goes to an arbitrary address: the words
+  // pass through the wait here.
   __device__ static __forceinline__ Rsrc make_rsrc(const void* base, int bytes)
   {
     const uint64_t a = (uint64_t)(uintptr_t)base;
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    const int n = __builtin_amdgcn_readfirstlane(bytes);
+    uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    int n = __builtin_amdgcn_readfirstlane(bytes);
+    asm("s_nop 4" : "+s"(lo), "+s"(hi), "+s"(n));
     return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)(((uint64_t)hi << 32) | lo), 0, n,
                                              0x00020000);
   }
