@@ -391,7 +391,8 @@ int alcop_sched_space(const alcop_problem* prob /* host */, alcop_sched* out /* 
 /*
  * The kernels outside the default space built for the problem.  They run when a caller names
  * them or asks the tuner for them (alcop_tune with variants = 1); the static model never picks
- * one on its own (the library's pick may be of variant 3, see alcop_sched_auto).  They are
+ * one on its own (the library's pick by measured cost may have bk = 128 or be of variant 3 or, for a
+ * convolution call, 1 or 4; see alcop_sched_auto).  They are
  *   - the schedule variant 1, whose feasibility depends on more than the
  *     problem description: for a convolution the variant with the input patch resident in LDS,
  *     which also needs stride 1 and a patch that fits the LDS (alcop_sched_supported only checks

@@ -19,8 +19,10 @@
 // cache line per row and k-tile, and wide tiles fetch fewer rows (3873 x 2872 with B stored N x K, bf16:
 // K = 7232 187 us with persistent 128 x 128 tiles and 167 with 256 x 192, K = 7192 235 and 181).  The
 // kernels below are the ones that a greedy selection by the regret of the estimated best keeps; the
-// pick is 3 % above the best in the mean and 7 % at the 90th percentile, on products above 12 GFLOP too,
-// where a fit without e, f and the layouts left 8 % and 30 % (operands cycled through three buffers).
+// pick is 3 % above the best in the mean and 7 % at the 90th percentile (1.53 times it at worst), on
+// products above 12 GFLOP too, where a fit without e, f and the layouts left 8 % and 30 % (operands
+// cycled through three buffers).  These figures are of the products that the kernels and coefficients
+// were chosen on; none were held out.
 #pragma once
 #include <algorithm>
 
@@ -104,8 +106,11 @@ inline double measured_us(const alcop_problem& p, const MeasuredCost& m)
 
 // The measured kernels worth considering for a product: small tiles cost more bytes per flop, so the
 // kernels whose waves split K are compared only while 64 x 64 tiles leave compute units idle (with 384
-// such tiles, 1021 x 1536 x 768, they take 11.9 us at best against 6.2).  Both operands transposed use
-// the costs of A stored K x M.
+// such tiles, 1021 x 1536 x 768, they take 11.9 us at best against 6.2).  Mean time of the pick over the
+// best kernel, with and without them: up to 64 such tiles 1.02 and 1.35, 64 to 128 1.02 and 1.08, 128 to
+// 256 1.02 and 1.01; above 256 their costs never come out lowest (45 products up to 512), the line only
+// keeps the fit from being used where nothing speaks for it.  Both operands transposed use the costs of
+// A stored K x M.
 inline bool measured_applies(const alcop_problem& p, const MeasuredCost& m)
 {
   if (p.op == ALCOP_OP_CONV2D) return false;
@@ -121,7 +126,8 @@ inline bool measured_applies(const alcop_problem& p, const MeasuredCost& m)
 //     us = a + b * turns * stages + c * turns + d * turns * (block-wide loads of the patch).
 // The model's first choice was 30 % above the best kernel in the mean (most where few tiles leave
 // compute units idle: 20 x 32 x 2400 20.4 us against 6.0, and where a patch saves eight of nine reads
-// of A: 100352 x 64 x 576 19.1 against 12.2); the cheapest of these is 2 %.
+// of A: 100352 x 64 x 576 19.1 against 12.2); the cheapest of these is 2 %, on the convolutions that the
+// fit has seen.
 struct MeasuredConv {
   alcop_sched s;
   int am;              // loader of A: 1 tap per k-tile, 2 tap per chunk, 3 patch, 4 patch of any geometry
@@ -184,7 +190,10 @@ inline double measured_conv_us(const alcop_problem& p, const MeasuredConv& m, do
   return m.a + m.b * turns * kt + m.c * turns + m.d * (m.am == 4 ? turns * patch_loads : bytes / 5.1e6);
 }
 
-// as for the products: the kernels whose waves split K only while 64 x 64 tiles are few
+// The kernels whose waves split K only while 64 x 64 tiles are few.  A gather pays longer for few tiles
+// than a matrix does: with and without them the pick of a gathering kernel is 1.01 and 1.40 times the best
+// up to 128 tiles, 1.02 and 1.04 from 128 to 256.  From 256 to 512 (22 convolutions) they are never
+// the cheapest by cost, so that there the line may lie anywhere.
 inline bool measured_conv_applies(const alcop_problem& p, const MeasuredConv& m)
 {
   return m.s.variant != 3 || (double)((p.M + 63) / 64) * ((p.N + 63) / 64) <= 512;

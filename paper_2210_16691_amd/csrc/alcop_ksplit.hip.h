@@ -11,7 +11,7 @@
 // order (deterministic), with the fused epilogue and the conversion in the same pass.
 //
 // Small tiles fetch more bytes per flop than large ones, so this pays only while the machine is
-// short of tiles; pick_ksplit in alcop_api.cpp draws that line.
+// short of tiles; measured_applies and measured_conv_applies in alcop_dispatch.h draw that line.
 //
 // The matrix instruction is v_mfma_f32_16x16x32: X lane l = row l%16, k = 8*(l/16)..+7, Y likewise
 // by column, D lane l = column l%16, rows 4*(l/16)..+3 (X from B, Y from A, as in alcop_kernel.hip.h:
