@@ -412,8 +412,7 @@ int check_call(const Call& c)
   if (c.lda < (c.transA ? c.M : c.K) || c.ldb < (c.transB ? c.K : c.N) ||
       c.ldc < (c.c_any ? c.Nv : c.N))
     return ALCOP_ERR_SHAPE;
-  // (Mv is set by the unaligned entry points, which take any pitch of C)
-  if (c.lda >= (1L << 30) || c.ldb >= (1L << 30) || (c.ldc >= (1L << 30) && !c.Mv)) return ALCOP_ERR_SIZE;
+  if (c.lda >= (1L << 30) || c.ldb >= (1L << 30) || c.ldc >= (1L << 30)) return ALCOP_ERR_SIZE;
   return ALCOP_OK;
 }
 
@@ -578,7 +577,7 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
   p.K = c.K;
   p.lda = (int)c.lda;
   p.ldb = (int)c.ldb;
-  p.ldc = c.ldc;
+  p.ldc = (int)c.ldc;
   p.strideA = c.strideA;
   p.strideB = c.strideB;
   p.strideC = c.strideC;
@@ -1033,9 +1032,9 @@ inline long r8(long x) { return (x + 7) & ~7L; }
 inline size_t r256(double bytes) { return ((size_t)bytes + 255) & ~(size_t)255; }
 inline int out_size(alcop_dtype out) { return out == ALCOP_F32 ? 4 : 2; }
 
-// Sections of the workspace: padded A, padded B, padded C, padded bias.  Results go straight to C, so
-// that its section serves the compact images of few-channel convolutions only (and is as large as the
-// output type makes it); it stays part of the size that callers reserve.  Returns the total, or 0 if a
+// Sections of the workspace: padded A, padded B, padded C, padded bias.  Results go straight to C; its
+// section serves rows of C too far apart for that, and compact images of few-channel convolutions
+// (whose room therefore depends on the output type).  Returns the total, or 0 if a
 // section would reach 2 GiB (the kernels' 32-bit offsets; C 4 GiB).
 size_t unaligned_layout(double a_elems, double b_elems, double c_elems, long n8, alcop_dtype out,
                         size_t off[4])
@@ -1511,6 +1510,14 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
   c.Mv = M;
   c.Nv = N;
   c.c_any = !(aligned16(C) && N % 8 == 0 && ldc % 8 == 0 && (batch == 1 || strideC % 8 == 0));
+  // The kernels hold the pitch of C in 32 bits: rows further apart are copied out of a dense result.
+  const bool far = ldc >= (1L << 30);
+  if (far) {
+    c.C = ws + off[2];
+    c.ldc = n8;
+    c.strideC = (long)m8 * n8;
+    c.c_any = 0;
+  }
   Packer pk;
   int rc = pack_epilogue(ep, N, ws + off[3], c_bytes, &c, &pk);
   if (rc) return rc;
@@ -1525,7 +1532,10 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
     padded.M = m8;
     if (tuned_sched(padded, &tuned)) sched = &tuned;
   }
-  return run(c, sched, hip_stream);
+  rc = run(c, sched, hip_stream);
+  if (rc || !far) return rc;
+  const CopyOutParams o{c.C, C, batch, M, N, osz, n8, c.strideC, ldc, strideC};
+  return launch_copy_out(o, st) == hipSuccess ? ALCOP_OK : ALCOP_ERR_LAUNCH;
 }
 
 // Output extent of the convolution, or false if the arguments do not describe one.

@@ -69,8 +69,7 @@ struct Params {
   const void* B;
   void* C;
   int M, N, K;                 // GEMM view
-  int lda, ldb;                // elements (host guarantees the byte spans fit 31 bits)
-  long ldc;                    // any pitch: rows of C are addressed with 64 bits
+  int lda, ldb, ldc;           // elements (host guarantees the byte spans fit 31 bits)
   long strideA, strideB, strideC;
   int out_dtype;               // 0 f16, 1 bf16, 2 f32
   // rows and columns of C that exist (M and N unless the operands are zero-padded images), and
@@ -96,9 +95,14 @@ struct Params {
   // C + z * zstrideC elements (C is then the caller's workspace)
   int ksplit_len;
   long zstrideC;
-  // convolution with an LDS-resident input patch (AM == 3): filter height, row length of the
-  // zero-padded image, tiles per image, direct-to-LDS loads per thread that bring in the patch
-  int cR, cWp, ntj, patch_loads;
+  union {
+    // convolution with an LDS-resident input patch (AM == 3): filter height, row length of the
+    // zero-padded image, tiles per image, direct-to-LDS loads per thread that bring in the patch
+    struct { int cR, cWp, ntj, patch_loads; };
+    // ... with a resident patch for any geometry, windows whose last chunk runs past the filter row
+    // (ragged): the bits of that chunk's third and fourth word that belong to the window
+    struct { int ragged; uint32_t rkeep[2]; };
+  };
   // persistent producer / consumer kernels (alcop_stream.hip.h): blocks launched and batch count;
   // block b works on tiles b, b + sgrid, b + 2 sgrid, ... of the ntm * ntn * sbatch tiles
   int sgrid, sbatch;
@@ -108,10 +112,6 @@ struct Params {
   // byte distance of neighbouring taps; entries of the chunk table
   int rWs, rHs, rslots, rloads, rpitch, rc8, rdS, rdR, rtab;
   int rstep_c, rstep_col, rstep_row;   // 256 slots further: chunks, columns, rows
-  // windows whose last chunk runs past the filter row: the bits of the chunk's third and fourth word
-  // that belong to the window (ragged: any do not)
-  int ragged;
-  uint32_t rkeep[2];
   FastDiv rQ, rPQ, rWsDiv, rImg, rCP, rC8, rS;
 };
 

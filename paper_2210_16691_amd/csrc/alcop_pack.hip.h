@@ -119,4 +119,33 @@ __global__ void __launch_bounds__(PACK_THREADS) alcop_pack(const PackParams p)
   HW::global_store16_keep((char*)g.dst + (size_t)idx * 16, v);
 }
 
+// C from a dense image of it, for rows of C further apart than the products can address: one element
+// per thread.  For completeness, not for speed.
+struct CopyOutParams {
+  const void* src;
+  void* dst;
+  int batch, rows, cols, esize;      // bytes per element: 2 or 4
+  long s_row, s_batch, d_row, d_batch;   // in elements
+};
+
+template <class HW>
+__global__ void __launch_bounds__(PACK_THREADS) alcop_copy_out(const CopyOutParams p)
+{
+  const long i = (long)HW::block_x() * PACK_THREADS + HW::wave_id() * 64 + HW::lane_id();
+  const long r = i / p.cols, c = i - r * p.cols;
+  const long b = r / p.rows, m = r - b * p.rows;
+  if (b >= p.batch) return;
+  const char* s = (const char*)p.src + (b * p.s_batch + m * p.s_row + c) * p.esize;
+  char* d = (char*)p.dst + (b * p.d_batch + m * p.d_row + c) * p.esize;
+  if (p.esize == 2)
+    HW::global_store_u16(d, HW::global_load_u16(s));
+  else
+    HW::global_store_u32(d, HW::global_load_u32(s));
+}
+
+inline unsigned copy_out_blocks(const CopyOutParams& p)
+{
+  return (unsigned)(((long)p.batch * p.rows * p.cols + PACK_THREADS - 1) / PACK_THREADS);
+}
+
 }  // namespace alcop

@@ -52,6 +52,8 @@ hipError_t launch_splitk_reduce(const ReduceParams& p, dim3 grid, hipStream_t st
 
 // Copies into the padded workspace images, all segments of a call (alcop_pack.hip.h).
 hipError_t launch_pack(const PackParams& p, unsigned blocks, hipStream_t st);
+// C from a dense image of it in the workspace.
+hipError_t launch_copy_out(const CopyOutParams& p, hipStream_t st);
 
 // Device address and size of the library's own scratch array on the current device (set up on
 // the first call per device; allocates nothing afterwards).  Its size is part of the interface

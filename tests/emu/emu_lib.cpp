@@ -317,6 +317,12 @@ hipError_t launch_pack(const PackParams& p, unsigned blocks, hipStream_t)
   emu::run_grid(&pack_entry, &p, PACK_THREADS, 0, blocks, 1, 1);
   return hipSuccess;
 }
+static void copy_out_entry(const void* p) { alcop_copy_out<emu::Emu>(*(const CopyOutParams*)p); }
+hipError_t launch_copy_out(const CopyOutParams& p, hipStream_t)
+{
+  emu::run_grid(&copy_out_entry, &p, PACK_THREADS, 0, copy_out_blocks(p), 1, 1);
+  return hipSuccess;
+}
 // host stand-in for the library's device scratch array
 hipError_t splitk_scratch(void** ptr, size_t* bytes)
 {
