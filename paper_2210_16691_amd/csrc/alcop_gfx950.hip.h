@@ -44,26 +44,23 @@ struct Gfx950 {
   }
 
   // Buffer resource for a wave-uniform base address.  The words are passed through
-  // readfirstlane so that the descriptor provably lives in scalar registers.  A vector-memory
-  // instruction must not read a scalar register within five wait states of the vector instruction
-  // that wrote it.  The compiler keeps that distance for instructions of its own, not for those in
-  // inline asm (dma16), and a load that reads a stale base goes to an arbitrary address: the words
-  // pass through the wait here.
+  // readfirstlane so that the descriptor provably lives in scalar registers.
   __device__ static __forceinline__ Rsrc make_rsrc(const void* base, int bytes)
   {
     const uint64_t a = (uint64_t)(uintptr_t)base;
-    uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-    uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-    int n = __builtin_amdgcn_readfirstlane(bytes);
-    asm("s_nop 4" : "+s"(lo), "+s"(hi), "+s"(n));
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+    const int n = __builtin_amdgcn_readfirstlane(bytes);
     return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)(((uint64_t)hi << 32) | lo), 0, n,
                                              0x00020000);
   }
 
   __device__ static __forceinline__ void dma16(Rsrc rsrc, uint32_t voff, uint32_t lds_dst)
   {
-    // M0 holds the wave-uniform LDS destination; lane l lands at M0 + 16*l.
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+    // M0 holds the wave-uniform LDS destination; lane l lands at M0 + 16*l.  The load needs one wait
+    // state after the write of M0, and five after a vector instruction (v_readfirstlane) that wrote a
+    // word of the descriptor: the compiler keeps those for instructions of its own, not in here.
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :
                  : "s"(lds_dst), "v"(voff), "s"(rsrc)
                  : "memory");
