@@ -534,7 +534,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
       const int ih = ihp - p.cph, iw = jj - ihp * p.cWp - p.cpw;
       const bool ok = row < rows && (unsigned)ih < (unsigned)p.cH && (unsigned)iw < (unsigned)p.cW;
       const uint32_t off = (uint32_t)((((p_img * p.cH + ih) * p.cW) + iw) * p.cC * 2 + c * 16);
-      HW::dma16(la.rsrc, ok ? off : 0x80000000u, patch_base + (uint32_t)(i * C::NT + wave * 64) * 16u);
+      HW::dma16_first(la.rsrc, ok ? off : 0x80000000u, patch_base + (uint32_t)(i * C::NT + wave * 64) * 16u);
     }
   } else {
     // implicit GEMM: row m of A is output pixel (img, p, q); a k-tile lies inside one filter tap
@@ -619,20 +619,26 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
     if constexpr (C::AM == 2) a_in_k = kt * BK + a_k8 < Kb;
     st_kb = st_live ? (uint32_t)kt * lb.kstep : 0x80000000u;
   };
-  auto issue_one = [&](int idx) {
+  auto dma = [&](bool first, typename HW::Rsrc rsrc, uint32_t voff, uint32_t dst) {
+    if (first)
+      HW::dma16_first(rsrc, voff, dst);
+    else
+      HW::dma16(rsrc, voff, dst);
+  };
+  auto issue_one = [&](int idx, bool first = false) {
     if (idx < NLA) {
       const int i = idx;
       if constexpr (C::AM == 0) {
-        HW::dma16(la.rsrc, st_voffA + st_ka + (uint32_t)i * la.step, st_dst + i * (NWAVES * 1024));
+        dma(first, la.rsrc, st_voffA + st_ka + (uint32_t)i * la.step, st_dst + i * (NWAVES * 1024));
       } else {
         bool ok = st_live && (unsigned)(ih0[i] + crd) < (unsigned)p.cH &&
                   (unsigned)(iw0[i] + csd) < (unsigned)p.cW;
         if constexpr (C::AM == 2) ok = ok && a_in_k;
-        HW::dma16(la.rsrc, ok ? coff[i] + st_tap : 0x80000000u, st_dst + i * (NWAVES * 1024));
+        dma(first, la.rsrc, ok ? coff[i] + st_tap : 0x80000000u, st_dst + i * (NWAVES * 1024));
       }
     } else if (idx < NLA + NLB) {
       const int i = idx - NLA;
-      HW::dma16(lb.rsrc, st_voffB + st_kb + (uint32_t)i * lb.step,
+      dma(first, lb.rsrc, st_voffB + st_kb + (uint32_t)i * lb.step,
             st_dst + A_BYTES + i * (NWAVES * 1024));
     } else if constexpr (C::PF) {
       HW::touch4(pf_ptr, pf_dst);
@@ -655,10 +661,10 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
       }
     }
   };
-  auto issue = [&](int kt, int slot) {
+  auto issue = [&](int kt, int slot, bool first = false) {
     stage_begin(kt, slot);
 #pragma unroll
-    for (int i = 0; i < C::L; i++) issue_one(i);
+    for (int i = 0; i < C::L; i++) issue_one(i, first);
     stage_end();
   };
 
@@ -754,7 +760,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
     constexpr int G = (NKI % R == 0) ? R : ((NKI % 2 == 0 && R % 2 == 0) ? 2 : 1);   // gcd(NKI, R)
     constexpr int U = R / G;                  // periods per unrolled body: register slots are static
 #pragma unroll
-    for (int s = 0; s < S; s++) issue(s, s);
+    for (int s = 0; s < S; s++) issue(s, s, s == 0);
     HW::template wait_vm<C::WAIT0>();
     HW::block_barrier();
     set_read_slot(lds0);
@@ -804,7 +810,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
     // steps 0..NKI-2; the wait for k-tile ko+1 and the barrier open step NKI-1, whose reads
     // already fetch the first fragment of k-tile ko+1.
 #pragma unroll
-    for (int s = 0; s < S - 1; s++) issue(s, s);
+    for (int s = 0; s < S - 1; s++) issue(s, s, s == 0);
     HW::template wait_vm<C::WAIT>();
     HW::block_barrier();
     set_read_slot(lds0);
@@ -835,7 +841,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
   } else {
     if constexpr (S >= 2) {
 #pragma unroll
-      for (int s = 0; s < S - 1; s++) issue(s, s);
+      for (int s = 0; s < S - 1; s++) issue(s, s, s == 0);
     }
     int rslot = 0, wslot = (S >= 2) ? S - 1 : 0;
     for (int ko = 0; ko < nko; ko++) {
@@ -847,7 +853,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
       } else {
         HW::wait_lds();
         HW::block_barrier();                 // producer_acquire: slot 0 is free
-        issue(ko, 0);
+        issue(ko, 0, true);
         HW::template wait_vm<0>();                    // consumer_wait
         HW::block_barrier();
       }

@@ -18,6 +18,10 @@ struct Ablated : Gfx950 {
   {
     if constexpr (!(DROP & ALCOP_DIAG_NO_DMA)) Gfx950::dma16(rsrc, voff, lds_dst);
   }
+  __device__ static __forceinline__ void dma16_first(Rsrc rsrc, uint32_t voff, uint32_t lds_dst)
+  {
+    if constexpr (!(DROP & ALCOP_DIAG_NO_DMA)) Gfx950::dma16_first(rsrc, voff, lds_dst);
+  }
   __device__ static __forceinline__ void touch4(const char* gptr, uint32_t lds_dst)
   {
     if constexpr (!(DROP & ALCOP_DIAG_NO_DMA)) Gfx950::touch4(gptr, lds_dst);

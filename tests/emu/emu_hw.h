@@ -333,6 +333,7 @@ struct Emu {
     b.lanes[b.cur].pending.push_back(p);
   }
 
+  static void dma16_first(Rsrc r, uint32_t voff, uint32_t lds_dst) { dma16(r, voff, lds_dst); }
   static void dma16(Rsrc r, uint32_t voff, uint32_t lds_dst)
   {
     Block& b = *blk();

@@ -4,14 +4,18 @@ A vector-memory instruction may read a scalar register only five wait states aft
 instruction that wrote it.  The compiler keeps that distance for its own instructions but does not
 look into inline asm, where the direct-to-LDS loads are: with a shorter one a load can take a stale
 base address, which is a fault now and then and nothing that results show."""
+import concurrent.futures as cf
+import multiprocessing
 import os
 import re
+import struct
 import subprocess
 
 import pytest
 
 from paper_2210_16691_amd import build as b
 
+OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 WAIT = 5
 
 
@@ -55,13 +59,35 @@ def test_the_scan_counts_wait_states():
         assert len(violations("\n".join(["\tv_readfirstlane_b32 s17, v4"] + between + [load]))[1]) == n
 
 
-@pytest.mark.parametrize("source", ["inst_f16_kn_mid.hip", "inst_nk_big.hip", "inst_convres_rsck.hip", "inst_ksplit.hip"])
-def test_loads_keep_their_distance_from_the_descriptor(source, tmp_path):
-    if not os.path.exists(b.HIPCC):
-        pytest.skip("no hipcc")
-    out = tmp_path / "k.s"
-    subprocess.run([b.HIPCC] + b.FLAGS + ["-x", "hip", "-S", "--cuda-device-only", os.path.join(b.CSRC, source), "-o", str(out)],
-                   check=True, stderr=subprocess.DEVNULL)
-    seen, bad = violations(out.read_text())
-    assert seen > 100
-    assert not bad, bad[:3]
+def _code_objects(path):
+    """The gfx950 code objects bundled in a library."""
+    data = open(path, "rb").read()
+    for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data):
+        o = m.start()
+        n, at = struct.unpack_from("<Q", data, o + 24)[0], o + 32
+        for _ in range(n):
+            offset, size, length = struct.unpack_from("<QQQ", data, at)
+            if b"gfx950" in data[at + 24:at + 24 + length]:
+                yield data[o + offset:o + offset + size]
+            at += 24 + length
+
+
+def _scan(path):
+    asm = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", "--no-show-raw-insn", path], check=True,
+                         stdout=subprocess.PIPE, text=True).stdout
+    return violations(re.sub(r"//.*|<.*>:", "", asm))
+
+
+def test_loads_keep_their_distance_from_the_descriptor(tmp_path):
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump")
+    files = []
+    for i, code in enumerate(_code_objects(b.LIB)):
+        files.append(str(tmp_path / ("%d.co" % i)))
+        open(files[-1], "wb").write(code)
+    assert len(files) >= 20
+    with cf.ProcessPoolExecutor(max_workers=8, mp_context=multiprocessing.get_context("spawn")) as ex:
+        found = list(ex.map(_scan, files))
+    assert sum(n for n, _ in found) > 100000
+    bad = [v for _, vs in found for v in vs]
+    assert not bad, (len(bad), bad[:3])
