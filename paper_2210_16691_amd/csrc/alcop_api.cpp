@@ -66,7 +66,7 @@ struct Call {
   int cN, cH, cW, cC, cK, cR, cS, csh, csw, cph, cpw, cP, cQ;
   int cdh, cdw;   // dilation
   int cPix;       // elements between pixels of x if not cC (0)
-  int ragged;     // of the 8 elements of a window's last chunk, those inside the window (0: all)
+  int ragged;     // 1: a window ends in the middle of its last chunk of 8 elements
   // C without 16-byte chunks: its valid rows and columns if not M and N (0), any element alignment
   int Mv, Nv, c_any;
   // fused epilogue
@@ -490,7 +490,7 @@ int resident_of(const Call& c, const alcop_sched& s, const KernelEntry* e, Resid
   const int wk = 4 / ((s.bm / 64) * (s.bn / 64));
   if (c.K > 1 << 20) return ALCOP_ERR_SCHED;
   r.table = convres_table(c.K, wk);
-  if (convres_lds(e->patch_off, e->lds_bytes, r.loads, r.table) > 160 * 1024) return ALCOP_ERR_SCHED;
+  if (convres_lds(e->patch_off, e->lds_bytes, r.loads, r.table, c.ragged) > 160 * 1024) return ALCOP_ERR_SCHED;
   if (out) *out = r;
   return ALCOP_OK;
 }
@@ -648,9 +648,7 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
       p.rCP = FastDiv::of((uint32_t)(r.pitch / 16));
       p.rC8 = FastDiv::of((uint32_t)(c.cC / 8));
       p.rS = FastDiv::of((uint32_t)c.cS);
-      p.ragged = c.ragged != 0;
-      for (int e = 4; e < 8; e++)
-        if (e < c.ragged) p.rkeep[(e - 4) / 2] |= 0xffffu << (16 * (e & 1));
+      p.ragged = c.ragged;
     }
   }
   dim3 grid((unsigned)(p.ntm * p.ntn), (unsigned)c.batch, 1);
@@ -1127,7 +1125,7 @@ int pack_epilogue(const alcop_epilogue* ep, int N, char* ws_bias, double c_bytes
 //                The gather sees a filter S = 1 wide with that many channels, whose windows overlap.
 //                If px does not divide S, the last chunk's pixels past the filter are data of other
 //                windows: only the kernels that clear them take the call (Call::ragged), and only
-//                where at least half of that chunk is the window's.
+//                where they are half of the chunk (C = 3 or 4 and an odd S among others).
 //   window form  one window per output column: the S * C elements of a filter row, padded to 8.
 // The pixel form multiplies 8 / C times as much padding as data: a 7 x 7 stem on RGB reduces over
 // 392 elements instead of 147 (pair form: 224).  Picked by bytes: the image is written and read
@@ -1185,8 +1183,8 @@ XForm choose_xform(const Call& c, int C, double x_room)
       const int ch = (S + px - 1) / px;
       const long last = (Q - 1) * (sw / px) + ch;          // chunks a row must have
       const int in = 8 - (ch * px - S) * cg;               // elements of the last chunk in the window
-      if (last < 0x3fffffff && in >= 4)
-        consider(XForm{PACK_PIX, cg, px, ch, (int)last, 8, 8 * ch, 1, sw / px, 0, true, in < 8 ? in : 0});
+      if (last < 0x3fffffff && (in == 8 || in == 4))
+        consider(XForm{PACK_PIX, cg, px, ch, (int)last, 8, 8 * ch, 1, sw / px, 0, true, in == 4});
     }
   }
   if ((double)S * C < 65536.0 && Q < 0x3fffffff)

@@ -22,9 +22,9 @@
 //
 // Ragged windows (RG).  Where several pixels share a chunk, the last chunk of a filter row may hold
 // pixels past the window.  They are data of other windows and meet weights of zero, which is not
-// enough: 0 * inf.  The table marks all chunks but those, and the fragments of the unmarked ones have
-// the words past the window cleared before their first use: per 16 elements of K seven vector
-// instructions beside four matrix instructions, 0.6 us of the 35 that the call on the stem below takes.
+// enough: 0 * inf.  The second half of those chunks is cleared in the fragments before their first use,
+// with a mask that the table holds beside the offset: per 16 elements of K four vector instructions
+// beside four matrix instructions, 0.5 us of the 33 that the call on the stem below takes.
 //
 // Waves.  Every wave owns a 64 x 64 tile (4 waves of 64 x 64 read 96 clocks of LDS per 128 of
 // matrix instructions; 32-wide wave tiles are bound by those reads).  Tiles smaller than 256 x 64 or
@@ -70,9 +70,9 @@ inline int convres_table(int K, int wk)
   const int stages = ((K + 63) / 64 + wk - 1) / wk;
   return ((stages + 1) * wk * 8 + 255) / 256 * 256;
 }
-inline long convres_lds(long ring, long min_lds, long loads, long table)
+inline long convres_lds(long ring, long min_lds, long loads, long table, bool ragged)
 {
-  const long need = ring + loads * 4096 + table * 4;
+  const long need = ring + loads * 4096 + table * (ragged ? 8 : 4);
   return need > min_lds ? need : min_lds;
 }
 
@@ -166,7 +166,6 @@ __global__ void __launch_bounds__(C::NT) alcop_convres(const Params p)
     for (int i = 0; i < C::L; i++) issue_one(i);
   }
 
-  constexpr uint32_t WHOLE = 0x40000000u;      // RG: every word of the chunk belongs to the window
   // ---- chunk table ---------------------------------------------------------------------------------
   const uint32_t tab = patch + (uint32_t)p.rloads * 4096u;
   for (int e = 0; e < p.rtab; e += C::NT) {
@@ -174,9 +173,11 @@ __global__ void __launch_bounds__(C::NT) alcop_convres(const Params p)
     const int tap = (int)p.rC8.div((uint32_t)kc);
     const int r = (int)p.rS.div((uint32_t)tap);
     const int cc = kc - tap * (int)p.rC8.d;
-    uint32_t off = (uint32_t)(cc * 16 + (tap - r * p.cS) * p.rdS + r * p.rdR);
-    if (C::RG && cc != (int)p.rC8.d - 1) off |= WHOLE;
-    HW::lds_write(tab + (uint32_t)kc * 4u, kc * 8 < p.K ? off : 0x80000000u);
+    const uint32_t off = kc * 8 < p.K ? (uint32_t)(cc * 16 + (tap - r * p.cS) * p.rdS + r * p.rdR) : 0x80000000u;
+    if constexpr (C::RG)
+      HW::lds_write(tab + (uint32_t)kc * 8u, u32x2{off, cc == (int)p.rC8.d - 1 ? 0u : ~0u});
+    else
+      HW::lds_write(tab + (uint32_t)kc * 4u, off);
   }
 
   // ---- readers ---------------------------------------------------------------------------------------
@@ -188,24 +189,29 @@ __global__ void __launch_bounds__(C::NT) alcop_convres(const Params p)
     rdA[t] = patch + (uint32_t)((position(m < p.M ? m : tm * BM) - pos0) * p.rpitch);
   }
   const uint32_t zeros = patch + (uint32_t)p.rslots * 16u;       // the patch has rslots + 1 slots at least
-  const uint32_t tabw = tab + (uint32_t)(wk * 8 + (lane >> 5)) * 4u;
-  uint32_t oc[4], on[4];
-  auto read_offsets = [&](int kt, uint32_t (&o)[4]) __attribute__((always_inline)) {
+  constexpr uint32_t TE = C::RG ? 8u : 4u;     // bytes per table entry
+  const uint32_t tabw = tab + (uint32_t)(wk * 8 + (lane >> 5)) * TE;
+  uint32_t oc[4], on[4], mc[4], mn[4];         // offsets; RG: masks of the chunks' second halves
+  auto read_offsets = [&](int kt, uint32_t (&o)[4], uint32_t (&mask)[4]) __attribute__((always_inline)) {
 #pragma unroll
-    for (int ki = 0; ki < 4; ki++) o[ki] = HW::lds_read4(tabw + (uint32_t)(kt * (WK * 32) + ki * 8));
+    for (int ki = 0; ki < 4; ki++) {
+      const uint32_t at = tabw + (uint32_t)(kt * (WK * 8) + ki * 2) * TE;
+      if constexpr (C::RG) {
+        const u32x2 v = HW::lds_read8(at);
+        o[ki] = v[0];
+        mask[ki] = v[1];
+      } else {
+        o[ki] = HW::lds_read4(at);
+      }
+    }
   };
   constexpr int NRI = 2 + OB::NRI;
   u32x4 fa[2][2], fb[2][2];
   auto read_one = [&](int ki, int r, uint32_t o, u32x4 (&a)[2], u32x4 (&b)[2]) __attribute__((always_inline)) {
     if (r < 2)
-      a[r] = HW::lds_read16((int)o < 0 ? zeros : rdA[r] + (C::RG ? o & ~WHOLE : o));
+      a[r] = HW::lds_read16((int)o < 0 ? zeros : rdA[r] + o);
     else
       read_instr<OB, HW>(curB, ki, r - 2, b);
-  };
-  auto clip = [&](uint32_t o, u32x4& a) __attribute__((always_inline)) {
-    const uint32_t whole = (uint32_t)((int)(o << 1) >> 31);
-    a[2] &= p.rkeep[0] | whole;
-    a[3] &= p.rkeep[1] | whole;
   };
   auto open_slot = [&](int slot) __attribute__((always_inline)) {
 #pragma unroll
@@ -223,7 +229,7 @@ __global__ void __launch_bounds__(C::NT) alcop_convres(const Params p)
   HW::template wait_vm<C::WAIT>();             // the patch and stage 0 have landed (this wave's part)
   HW::wait_lds();
   HW::block_barrier();
-  read_offsets(0, oc);
+  read_offsets(0, oc, mc);
   open_slot(0);
 #pragma unroll
   for (int r = 0; r < NRI; r++) read_one(0, r, oc[0], fa[0], fb[0]);
@@ -234,13 +240,16 @@ __global__ void __launch_bounds__(C::NT) alcop_convres(const Params p)
     wslot = (wslot + 1 == S) ? 0 : wslot + 1;
 #pragma unroll
     for (int ki = 0; ki < 4; ki++) {
-      if (ki == 0) read_offsets(kt + 1, on);
+      if (ki == 0) read_offsets(kt + 1, on, mn);
+      const uint32_t mask = C::RG ? mc[ki] : 0u;   // step 3 moves on to the next stage's masks
 #pragma unroll
       for (int m = 0; m < 4; m++) {
         const int i = m >> 1, j = m & 1;
-        if (C::RG && m == 0) {                 // here, since step 3 moves on to the next stage's offsets
-          clip(oc[ki], fa[ki & 1][0]);
-          clip(oc[ki], fa[ki & 1][1]);
+        if constexpr (C::RG) {
+          if (m < 2) {                         // the first use of fragment m
+            fa[ki & 1][m][2] &= mask;
+            fa[ki & 1][m][3] &= mask;
+          }
         }
         acc[i][j] = HW::template mma<C::DT>(fb[ki & 1][i], fa[ki & 1][j], acc[i][j]);
         if (ki < 3) {
@@ -259,7 +268,10 @@ __global__ void __launch_bounds__(C::NT) alcop_convres(const Params p)
             rslot = (rslot + 1 == S) ? 0 : rslot + 1;
             open_slot(rslot);
 #pragma unroll
-            for (int e = 0; e < 4; e++) oc[e] = on[e];
+            for (int e = 0; e < 4; e++) {
+              oc[e] = on[e];
+              if (C::RG) mc[e] = mn[e];
+            }
           }
 #pragma unroll
           for (int r = 2 * m; r < 2 * m + 2 && r < NRI; r++) read_one(0, r, oc[0], fa[0], fb[0]);

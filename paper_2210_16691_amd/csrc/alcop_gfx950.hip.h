@@ -129,6 +129,10 @@ struct Gfx950 {
   {
     return *(const ALCOP_LDS uint32_t*)(uintptr_t)addr;
   }
+  __device__ static __forceinline__ u32x2 lds_read8(uint32_t addr)
+  {
+    return *(const ALCOP_LDS u32x2*)(uintptr_t)addr;
+  }
   __device__ static __forceinline__ u32x2 lds_read_tr8(uint32_t addr)
   {
     s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((ALCOP_LDS s16x4*)(uintptr_t)addr);

@@ -24,7 +24,7 @@ hipError_t launch_convres(const Params& p, dim3 grid, hipStream_t st)
 {
   const hipError_t rc = prepare_convres<C, D>();
   if (rc != hipSuccess) return rc;
-  const unsigned lds = (unsigned)convres_lds(C::RING_BYTES, C::MIN_LDS, p.rloads, p.rtab);
+  const unsigned lds = (unsigned)convres_lds(C::RING_BYTES, C::MIN_LDS, p.rloads, p.rtab, p.ragged);
   if (p.ragged)
     alcop_convres<D, Gfx950><<<grid, dim3(D::NT), lds, st>>>(p);
   else

@@ -99,9 +99,9 @@ struct Params {
     // convolution with an LDS-resident input patch (AM == 3): filter height, row length of the
     // zero-padded image, tiles per image, direct-to-LDS loads per thread that bring in the patch
     struct { int cR, cWp, ntj, patch_loads; };
-    // ... with a resident patch for any geometry, windows whose last chunk runs past the filter row
-    // (ragged): the bits of that chunk's third and fourth word that belong to the window
-    struct { int ragged; uint32_t rkeep[2]; };
+    // ... with a resident patch for any geometry: the second half of a window's last chunk is not of
+    // the window
+    int ragged;
   };
   // persistent producer / consumer kernels (alcop_stream.hip.h): blocks launched and batch count;
   // block b works on tiles b, b + sgrid, b + 2 sgrid, ... of the ntm * ntn * sbatch tiles
@@ -534,7 +534,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
       const int ih = ihp - p.cph, iw = jj - ihp * p.cWp - p.cpw;
       const bool ok = row < rows && (unsigned)ih < (unsigned)p.cH && (unsigned)iw < (unsigned)p.cW;
       const uint32_t off = (uint32_t)((((p_img * p.cH + ih) * p.cW) + iw) * p.cC * 2 + c * 16);
-      HW::dma16_first(la.rsrc, ok ? off : 0x80000000u, patch_base + (uint32_t)(i * C::NT + wave * 64) * 16u);
+      HW::dma16(la.rsrc, ok ? off : 0x80000000u, patch_base + (uint32_t)(i * C::NT + wave * 64) * 16u);
     }
   } else {
     // implicit GEMM: row m of A is output pixel (img, p, q); a k-tile lies inside one filter tap

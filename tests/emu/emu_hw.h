@@ -487,6 +487,16 @@ struct Emu {
     }
     return v;
   }
+  static u32x2 lds_read8(uint32_t addr)
+  {
+    wave_sync();
+    u32x2 v = {0, 0};
+    if (const unsigned char* p = lds_ptr(addr, 8, 8, "ds_read_b64")) {
+      memcpy(&v, p, 8);
+      note_read(addr, 8);
+    }
+    return v;
+  }
   static u32x2 lds_read_tr8(uint32_t addr)
   {
     Block& b = *blk();

@@ -60,7 +60,7 @@ void add_ksplit(std::vector<KernelEntry>& t)
 template <class C, class D>
 hipError_t launch_emulated_convres(const Params& p, dim3 grid, hipStream_t)
 {
-  emu::run_grid(p.ragged ? &emu::convres_entry<D> : &emu::convres_entry<C>, &p, C::NT, (uint32_t)convres_lds(C::RING_BYTES, C::MIN_LDS, p.rloads, p.rtab),
+  emu::run_grid(p.ragged ? &emu::convres_entry<D> : &emu::convres_entry<C>, &p, C::NT, (uint32_t)convres_lds(C::RING_BYTES, C::MIN_LDS, p.rloads, p.rtab, p.ragged),
                 grid.x, grid.y, grid.z);
   return hipSuccess;
 }
