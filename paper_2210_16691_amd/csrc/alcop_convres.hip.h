@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(C::NT) alcop_convres(const Params p)
   const bool fused = p.alpha != 1.0f || p.bias != nullptr || p.act != 0;
   const int n0 = tn * BN, m0 = tm * BM;
   f32x4 bv[8];
-  if (WK == 1 && fused) load_bias<2, HW>(p, n0 + wn * 64, lane, bv);
+  if (WK == 1 && fused) load_bias<8, HW>(p, n0 + wn * 64, lane, bv);
   HW::template wait_vm<0>();                   // the loads that fetch nothing still write LDS
   HW::wait_lds();
   HW::block_barrier();                         // every wave has left the ring and the patch
@@ -346,7 +346,7 @@ __global__ void __launch_bounds__(C::NT) alcop_convres(const Params p)
       constexpr int RSB = 64 * OBY + 16, LPR = 64 * OBY / 16, RPI = 64 / LPR;
 #pragma unroll
       for (int j = 0; j < 2; j++) {
-        park_band<OT, RSB, HW>(p, acc, j, mine, lane, fused, bv);
+        park_band<OT, RSB, HW>(p, acc, j, mine, lane, fused, n0 + wn * 64, bv);
 #pragma unroll
         for (int t = 0; t < 32 / RPI; t++) {
           const int r = t * RPI + lane / LPR, c16 = lane % LPR;

@@ -190,6 +190,8 @@ struct KCfg {
   using OA = Opnd<AL ? LAY_MN : LAY_K, BM, WM, BK, NT>;
   using OB = Opnd<BL ? LAY_K : LAY_MN, BN, WN, BK, NT>;
   static constexpr int TM = WM / 32, TN = WN / 32, NKI = BK / 16;
+  static constexpr bool FLAT_STORES = !AL && TM == 4 && TN == 4;   // see store_chunk_if
+  static constexpr int BIAS_GROUPS = TN * 4;   // groups of bias values held in the epilogue
   // AM == 3 keeps its A operand in a patch outside the ring: a stage holds the B tile only
   static constexpr int A_BYTES = AM == 3 ? 0 : OA::BYTES, B_BYTES = OB::BYTES;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
@@ -379,16 +381,16 @@ __device__ __forceinline__ void tile_of_block(const Params& p, int lid, int& tm,
 // Fetched one group at a time where it is used, each load under its own lane mask, the bias cost
 // a serial chain of TM * TN * 4 memory latencies: 4096 x 3072 x 768 bf16 with bias and ReLU took
 // 29.9 us against 21.2 us without them.
-template <int TN, class HW>
-__device__ __forceinline__ void load_bias(const Params& p, int n0, int lane, f32x4 (&bv)[TN * 4])
+template <int N4, class HW>
+__device__ __forceinline__ void load_bias(const Params& p, int n0, int lane, f32x4 (&bv)[N4])
 {
   if (p.bias == nullptr) {
 #pragma unroll
-    for (int g = 0; g < TN * 4; g++) bv[g] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int g = 0; g < N4; g++) bv[g] = f32x4{0.f, 0.f, 0.f, 0.f};
     return;
   }
 #pragma unroll
-  for (int g = 0; g < TN * 4; g++) {
+  for (int g = 0; g < N4; g++) {
     const int n = n0 + 8 * g + 4 * (lane >> 5);
     bv[g] = HW::global_load_f32x4(p.bias + (n < p.N ? n : 0));
   }
@@ -396,10 +398,13 @@ __device__ __forceinline__ void load_bias(const Params& p, int n0, int lane, f32
 
 // Converts the 32-row band j of the accumulators to the output type and parks it in LDS at
 // `ebase` (row stride RS bytes).  act(): t < floor ? 0 : t with floor = 0 (ReLU) or -infinity.
-template <class OT, int RS, class HW, int TN, int TM>
+// `bv` holds the bias of all columns (load_bias), or space for the groups fetched here (of a
+// 32-column block, or a single one); n0: the first column.
+template <class OT, int RS, class HW, int TN, int TM, int NB>
 __device__ __forceinline__ void park_band(const Params& p, f32x16 (&acc)[TN][TM], int j, uint32_t ebase,
-                                          int lane, bool fused, const f32x4 (&bv)[TN * 4])
+                                          int lane, bool fused, int n0, f32x4 (&bv)[NB])
 {
+  static_assert(NB == TN * 4 || NB == 4 || NB == 1, "bias groups");
   typedef OT ot4 __attribute__((ext_vector_type(4)));
   const uint32_t row = ebase + (lane & 31) * RS + 4 * (lane >> 5) * (int)sizeof(OT);
   auto put = [&](int i, int vq, f32x4 v) __attribute__((always_inline)) {
@@ -407,27 +412,47 @@ __device__ __forceinline__ void park_band(const Params& p, f32x16 (&acc)[TN][TM]
                    HW::template cvt<OT>(v[2]), HW::template cvt<OT>(v[3])};
     HW::lds_write(row + (i * 32 + 8 * vq) * (int)sizeof(OT), h);
   };
-  if (fused) {
-    const float floor = p.act == 1 ? 0.f : -__builtin_inff();
+  auto put_fused = [&](int i, int vq, f32x4 b, float floor) __attribute__((always_inline)) {
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float t = acc[i][j][4 * vq + e] * p.alpha + b[e];
+      v[e] = t < floor ? 0.f : t;
+    }
+    put(i, vq, v);
+  };
+  auto put_plain = [&](int i, int vq) __attribute__((always_inline)) {
+    put(i, vq, f32x4{acc[i][j][4 * vq + 0], acc[i][j][4 * vq + 1], acc[i][j][4 * vq + 2],
+                     acc[i][j][4 * vq + 3]});
+  };
+  if constexpr (NB == 1) {
+    // the branch is taken group by group: with the two cases each as a whole, the compiler spills
+    // accumulators ahead of it, in calls without a bias too
 #pragma unroll
     for (int i = 0; i < TN; i++)
 #pragma unroll
       for (int vq = 0; vq < 4; vq++) {
-        f32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          const float t = acc[i][j][4 * vq + e] * p.alpha + bv[i * 4 + vq][e];
-          v[e] = t < floor ? 0.f : t;
+        if (fused) {
+          const float floor = p.act == 1 ? 0.f : -__builtin_inff();
+          load_bias<1, HW>(p, n0 + i * 32 + 8 * vq, lane, bv);
+          put_fused(i, vq, bv[0], floor);
+        } else {
+          put_plain(i, vq);
         }
-        put(i, vq, v);
       }
+  } else if (fused) {
+    const float floor = p.act == 1 ? 0.f : -__builtin_inff();
+#pragma unroll
+    for (int i = 0; i < TN; i++) {
+      if constexpr (NB < TN * 4) load_bias<NB, HW>(p, n0 + i * 32, lane, bv);
+#pragma unroll
+      for (int vq = 0; vq < 4; vq++) put_fused(i, vq, bv[(i * 4 + vq) % NB], floor);
+    }
   } else {
 #pragma unroll
     for (int i = 0; i < TN; i++)
 #pragma unroll
-      for (int vq = 0; vq < 4; vq++)
-        put(i, vq, f32x4{acc[i][j][4 * vq + 0], acc[i][j][4 * vq + 1], acc[i][j][4 * vq + 2],
-                         acc[i][j][4 * vq + 3]});
+      for (int vq = 0; vq < 4; vq++) put_plain(i, vq);
   }
 }
 
@@ -436,6 +461,21 @@ __device__ __forceinline__ void park_band(const Params& p, f32x16 (&acc)[TN][TM]
 // address, and the row's last, partial chunk element by element.  A copy of C through an aligned
 // image cost more than the product it followed (51 MB of a 7x7 stem: 37 us).
 template <class OT, class HW>
+__device__ __forceinline__ void store_elements(const Params& p, char* dst, int n, u32x4 v)
+{
+#pragma unroll 1
+  for (; n < p.Nv; n++, dst += sizeof(OT)) {     // the low element of v, then v shifted down by it
+    if constexpr (sizeof(OT) == 2) {
+      HW::global_store_u16(dst, (uint16_t)v[0]);
+      v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
+    } else {
+      HW::global_store_u32(dst, v[0]);
+      v = u32x4{v[1], v[2], v[3], 0u};
+    }
+  }
+}
+
+template <class OT, class HW>
 __device__ __forceinline__ void store_chunk(const Params& p, char* dst, int n, u32x4 v)
 {
   if (!p.c_any) {
@@ -443,20 +483,28 @@ __device__ __forceinline__ void store_chunk(const Params& p, char* dst, int n, u
     return;
   }
   constexpr int PER = 16 / (int)sizeof(OT);
-  if (n + PER <= p.Nv) {
+  if (n + PER <= p.Nv)
     HW::global_store16_any(dst, v);
-  } else {
-#pragma unroll 1
-    for (; n < p.Nv; n++, dst += sizeof(OT)) {     // the low element of v, then v shifted down by it
-      if constexpr (sizeof(OT) == 2) {
-        HW::global_store_u16(dst, (uint16_t)v[0]);
-        v = u32x4{(v[0] >> 16) | (v[1] << 16), (v[1] >> 16) | (v[2] << 16), (v[2] >> 16) | (v[3] << 16), v[3] >> 16};
-      } else {
-        HW::global_store_u32(dst, v[0]);
-        v = u32x4{v[1], v[2], v[3], 0u};
-      }
-    }
+  else
+    store_elements<OT, HW>(p, dst, n, v);
+}
+
+// The same for lanes with `ok`, no branch on lanes within another.  Where such branches end together
+// the compiler keeps one restoring of the lane mask for both, and with no register left it has put
+// the reload of a split register ahead of that, under the inner mask: lanes past the last column
+// kept what the inner branch had left there.  The kernels of 128 x 128 wave tiles were so (products
+// with a last tile of columns that is not full).
+template <class OT, class HW>
+__device__ __forceinline__ void store_chunk_if(const Params& p, char* dst, int n, u32x4 v, bool ok)
+{
+  constexpr int PER = 16 / (int)sizeof(OT);
+  if (!p.c_any) {
+    if (ok & (n < p.N)) HW::global_store16(dst, v);
+    return;
   }
+  const bool whole = n + PER <= p.Nv;
+  if (ok & whole) HW::global_store16_any(dst, v);
+  store_elements<OT, HW>(p, dst, (ok & !whole) ? n : p.Nv, v);
 }
 
 template <class C, class HW>
@@ -882,8 +930,9 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
     }
   }
   const bool fused = p.alpha != 1.0f || p.bias != nullptr || p.act != 0;
-  f32x4 bv[TN * 4];
-  if (fused) load_bias<TN, HW>(p, tn * BN + wn * WN, lane, bv);   // in flight during the drain
+  f32x4 bv[C::BIAS_GROUPS];
+  if constexpr (C::BIAS_GROUPS == TN * 4)
+    if (fused) load_bias<TN * 4, HW>(p, tn * BN + wn * WN, lane, bv);   // in flight during the drain
   HW::template wait_vm<0>();   // drain the zero-fill loads of the ring's tail before the ring is reused
   HW::wait_lds();
   HW::block_barrier();   // every wave has finished reading the ring
@@ -905,7 +954,7 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
     if constexpr (C::SK) Cb += (long)HW::block_z() * p.zstrideC * OB;
 #pragma unroll
     for (int j = 0; j < TM; j++) {
-      park_band<OT, RS, HW>(p, acc, j, ebase, lane, fused, bv);
+      park_band<OT, RS, HW>(p, acc, j, ebase, lane, fused, n0, bv);
       // a row is LPR lanes long; when that does not divide 64 (a wave tile 96 wide) the last
       // lanes of an instruction idle and the last instruction covers fewer rows
       constexpr bool EVEN = 64 % LPR == 0 && 32 % RPI == 0;
@@ -930,7 +979,11 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
           row_ok = pp < p.cP && qq < p.cQ;
           m = (p_img * p.cP + pp) * p.cQ + qq;
         }
-        if (lane_ok && row_ok) store_chunk<OT, HW>(p, Cb + ((long)m * p.ldc + n) * OB, n, v);
+        char* dst = Cb + ((long)m * p.ldc + n) * OB;
+        if constexpr (C::FLAT_STORES)
+          store_chunk_if<OT, HW>(p, dst, n, v, lane_ok & row_ok);
+        else if (lane_ok && row_ok)
+          store_chunk<OT, HW>(p, dst, n, v);
       }
     }
   };

@@ -240,7 +240,7 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
       // the following tiles: convert, transpose one 32-row band at a time through this wave's own
       // staging area, store whole 128-byte lines
       f32x4 bv[TN * 4];
-      if (fused) load_bias<TN, HW>(p, tn * BN + wn * WN, lane, bv);
+      if (fused) load_bias<TN * 4, HW>(p, tn * BN + wn * WN, lane, bv);
       auto epilogue = [&](auto zero) __attribute__((always_inline)) {
         using OT = decltype(zero);
         constexpr int OBY = sizeof(OT);
@@ -251,7 +251,7 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
         char* Cb = (char*)p.C + (long)batch * p.strideC * OBY;
 #pragma unroll
         for (int jj = 0; jj < TM; jj++) {
-          park_band<OT, RS, HW>(p, acc, jj, ebase, lane, fused, bv);
+          park_band<OT, RS, HW>(p, acc, jj, ebase, lane, fused, n0, bv);
           // a row is LPR lanes long; when that does not divide 64 (a wave tile 96 wide) the last
           // lanes of an instruction idle and the last instruction covers fewer rows
           constexpr bool EVEN = 64 % LPR == 0 && 32 % RPI == 0;

@@ -99,6 +99,9 @@ void emu_part_0(std::vector<KernelEntry>& t)
 void emu_part_1(std::vector<KernelEntry>& t)
 {
   add<0, 256, 256, 32, 128, 64, 2, 2, 1, 0, 0>(t);     // 8 waves
+  add<0, 256, 256, 64, 128, 128, 2, 2, 1, 0, 0>(t);    // bias fetched group by group,
+  add<0, 256, 256, 64, 128, 128, 2, 3, 1, 0, 0>(t);    // and block by block
+  add<0, 128, 192, 32, 64, 96, 3, 2, 1, 0, 0>(t);
   add<0, 256, 128, 64, 128, 64, 2, 2, 1, 0, 0>(t);
   add<0, 64, 64, 32, 32, 32, 1, 1, 0, 0, 0>(t);
   add<0, 64, 64, 32, 32, 32, 4, 2, 1, 0, 0>(t);

@@ -168,6 +168,23 @@ def test_leading_dimensions_and_output_guard():
 
 
 # ---- fused epilogue, BMM, convolution ---------------------------------------------------------
+@pytest.mark.parametrize("tile", [(256, 256, 64, 128, 128, 2, 2, 1), (256, 256, 64, 128, 128, 2, 3, 1),
+                                  (128, 192, 32, 64, 96, 3, 2, 1), (256, 192, 32, 128, 96, 3, 2, 1)])
+def test_fused_epilogue_of_wide_wave_tiles(tile):
+    # the bias held whole, for a 32-column block or for a group; columns past N in the last ones
+    M, N, K = 136, 200, 128
+    A, B = wl.small_ints((M, K), "f16", 151), wl.small_ints((K, N), "f16", 152)
+    bias = torch.arange(N, dtype=torch.float32) - 90
+    for alpha, b, act in [(0.5, bias, 1), (1.0, bias, 0), (-2.0, None, 0)]:
+        C = torch.full((M, N), float("nan"))
+        errs = emu.call(al.alcop_gemm_fused, A, B, C, alpha, b, act, al.sched(*tile),
+                        reads=[A, B] + ([] if b is None else [b]), writes=[C])
+        assert not errs
+        ref = oracle.epilogue(oracle.gemm(wl.bits(A), wl.bits(B), oracle.F16), alpha,
+                              None if b is None else b.double().numpy(), act)
+        assert np.array_equal(C.double().numpy(), ref), (alpha, act)
+
+
 def test_fused_epilogue_and_bmm():
     s = al.sched(128, 128, 64, 64, 64, 3, 2, 1)
     M, N, K = 136, 72, 136

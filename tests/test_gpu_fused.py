@@ -29,6 +29,22 @@ def test_integers_exact_scale_bias_relu():
             assert np.array_equal(to_f64(C), ref), (alpha, use_bias, act, repr(s))
 
 
+@pytest.mark.parametrize("tile", [(256, 256, 64, 128, 128, 2, 2, 1), (256, 256, 64, 128, 128, 2, 3, 1),
+                                  (128, 192, 32, 64, 96, 3, 2, 1), (256, 192, 32, 128, 96, 3, 2, 1)])
+def test_wide_wave_tiles_integers_exact(tile):
+    # the bias held whole, for a 32-column block or for a group; columns past N in the last ones
+    M, N, K = 392, 456, 256
+    A, B = wl.small_ints((M, K), "f16", 511), wl.small_ints((K, N), "f16", 512)
+    bias = torch.arange(N, dtype=torch.float32) - 90
+    base = oracle.gemm(wl.bits(A), wl.bits(B), oracle.F16)
+    for alpha, b, act in [(0.5, bias, 1), (1.0, bias, 0), (-2.0, None, 0), (1.0, None, 0)]:
+        C = torch.full((M, N), float("nan"), dtype=torch.float32, device=DEV)
+        al.alcop_gemm_fused(A.to(DEV), B.to(DEV), C, alpha, None if b is None else b.to(DEV), act, al.sched(*tile))
+        torch.cuda.synchronize()
+        ref = oracle.epilogue(base, alpha, None if b is None else b.numpy(), act)
+        assert np.array_equal(to_f64(C), ref), (alpha, act)
+
+
 def test_default_epilogue_equals_plain_gemm():
     A = wl.uniform((256, 256), "f16", 504)
     B = wl.uniform((256, 256), "f16", 505)

@@ -1,4 +1,4 @@
-"""The waits that the hardware leaves to software, in the machine code of the kernels.
+"""The machine code of the kernels: the waits that the hardware leaves to software, and registers.
 
 A vector-memory instruction may read a scalar register only five wait states after the vector
 instruction that wrote it.  The compiler keeps that distance for its own instructions but does not
@@ -59,6 +59,48 @@ def test_the_scan_counts_wait_states():
         assert len(violations("\n".join(["\tv_readfirstlane_b32 s17, v4"] + between + [load]))[1]) == n
 
 
+def late_restores(asm):
+    """Vector registers restored between the end of a branch on lanes and the restoring of the lane mask.
+
+    Such a write reaches only the lanes of the inner mask.  Where the compiler has to reload a register
+    that the branch used for something else, the other lanes keep what the branch left there."""
+    lines, targets = [], set()
+    for line in asm.splitlines():
+        m = re.match(r"\s+(\S+)\s*(.*?)\s*// ([0-9A-F]+):", line)
+        if m:
+            lines.append((int(m[3], 16), m[1], m[2]))
+            if m[1] == "s_cbranch_execz":
+                n = int(m[2])
+                targets.add(lines[-1][0] + 4 + 4 * (n - 65536 if n >= 32768 else n))
+    bad, written, ended = [], [], False
+    for address, op, args in lines:
+        if address in targets or op.startswith("global_store"):
+            ended, written = True, written if address in targets else []
+        if op == "s_or_b64" and args.startswith("exec, exec"):
+            bad += ["%s ahead of %s %s" % (written[0], op, args)] if ended and written else []
+            ended, written = False, []
+        elif "exec" in args or op.startswith(("s_cbranch", "s_branch", "s_endpgm")):
+            ended, written = False, []
+        elif ended and re.match(r"scratch_load|v_mov_b|v_accvgpr_", op) and re.search(r",.*\b([va][\d\[]|off)", args):
+            written.append("%s %s" % (op, args))       # a copy or a reload, not a new value
+    return bad
+
+
+def test_the_scan_finds_late_restores():
+    code = """
+\ts_and_saveexec_b64 s[16:17], vcc                       // 000000000100:
+\ts_cbranch_execz 7                                      // 000000000104: <k+0x24>
+\tv_lshl_add_u64 v[254:255], v[18:19], 2, s[14:15]       // 000000000108:
+\ts_and_b64 exec, exec, vcc                              // 000000000110:
+\ts_cbranch_execz 2                                      // 000000000114: <k+0x20>
+\tglobal_store_dwordx4 v[254:255], v[14:17], off nt      // 000000000118:
+\t%s                                                     // 000000000120:
+\ts_or_b64 exec, exec, s[16:17]                          // 000000000124:
+"""
+    assert len(late_restores(code % "v_mov_b32_e32 v255, v26")) == 1
+    assert not late_restores(code % "s_mov_b32 s4, 0")
+
+
 def _code_objects(path):
     """The gfx950 code objects bundled in a library."""
     data = open(path, "rb").read()
@@ -75,19 +117,30 @@ def _code_objects(path):
 def _scan(path):
     asm = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", "--no-show-raw-insn", path], check=True,
                          stdout=subprocess.PIPE, text=True).stdout
-    return violations(re.sub(r"//.*|<.*>:", "", asm))
+    tiles = re.findall(r"^[0-9a-f]+ <\w*Cfg\w*>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", asm, re.M | re.S)
+    return violations(re.sub(r"//.*|<.*>:", "", asm)), [b for t in tiles for b in late_restores(t)], len(tiles)
 
 
-def test_loads_keep_their_distance_from_the_descriptor(tmp_path):
+@pytest.fixture(scope="module")
+def scans(tmp_path_factory):
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
     files = []
     for i, code in enumerate(_code_objects(b.LIB)):
-        files.append(str(tmp_path / ("%d.co" % i)))
+        files.append(str(tmp_path_factory.mktemp("code") / ("%d.co" % i)))
         open(files[-1], "wb").write(code)
     assert len(files) >= 20
     with cf.ProcessPoolExecutor(max_workers=8, mp_context=multiprocessing.get_context("spawn")) as ex:
-        found = list(ex.map(_scan, files))
-    assert sum(n for n, _ in found) > 100000
-    bad = [v for _, vs in found for v in vs]
+        return list(ex.map(_scan, files))
+
+
+def test_loads_keep_their_distance_from_the_descriptor(scans):
+    assert sum(n for (n, _), _, _ in scans) > 100000
+    bad = [v for (_, vs), _, _ in scans for v in vs]
+    assert not bad, (len(bad), bad[:3])
+
+
+def test_no_register_is_restored_under_an_inner_lane_mask(scans):
+    assert sum(n for _, _, n in scans) > 1000
+    bad = [v for _, vs, _ in scans for v in vs]
     assert not bad, (len(bad), bad[:3])
