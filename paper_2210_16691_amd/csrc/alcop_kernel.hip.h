@@ -191,7 +191,11 @@ struct KCfg {
   using OB = Opnd<BL ? LAY_K : LAY_MN, BN, WN, BK, NT>;
   static constexpr int TM = WM / 32, TN = WN / 32, NKI = BK / 16;
   static constexpr bool FLAT_STORES = !AL && TM == 4 && TN == 4;   // see store_chunk_if
-  static constexpr int BIAS_GROUPS = TN * 4;   // groups of bias values held in the epilogue
+  // groups of bias values held in the epilogue (see load_bias)
+  static constexpr int BIAS_GROUPS = AL                   ? TN * 4
+                                     : TM == 4 && TN == 4 ? (R > 2 && BK > 32 ? 4 : 1)
+                                     : TM == 2 && TN == 3 ? 4
+                                                          : TN * 4;
   // AM == 3 keeps its A operand in a patch outside the ring: a stage holds the B tile only
   static constexpr int A_BYTES = AM == 3 ? 0 : OA::BYTES, B_BYTES = OB::BYTES;
   static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
@@ -381,6 +385,22 @@ __device__ __forceinline__ void tile_of_block(const Params& p, int lid, int& tm,
 // Fetched one group at a time where it is used, each load under its own lane mask, the bias cost
 // a serial chain of TM * TN * 4 memory latencies: 4096 x 3072 x 768 bf16 with bias and ReLU took
 // 29.9 us against 21.2 us without them.
+//
+// Where the accumulators leave no registers for the array (48 or 64 of them), it costs every call,
+// with a bias or not, and the tile-at-a-time kernel (KCfg::BIAS_GROUPS) holds less of it:
+//  - 64 x 96 wave tiles go from 252 registers to 296, so that a compute unit holds one block and
+//    not two.  They fetch the four groups of a 32-column block where they are used.
+//    128x192x32, 4096 x 3072 x 768 f16, S3 R2 fused: 24.0 -> 21.6 us (S1 R1: 41.5 -> 25.2), with
+//    bias and ReLU 26.7 -> 24.0; 2048^3, where one block is all there is, 26.4 -> 26.4 and
+//    28.1 -> 28.5.  The persistent kernel's blocks have a compute unit each: it keeps the array
+//    (25.2 us with bias and ReLU; 26.6 block by block).
+//  - 128 x 128 wave tiles spill.  They fetch group by group, where one register group is all it
+//    takes (256x256x32 S3 R2 fused at the same size: 38.4 -> 24.4 us, with bias and ReLU 42.7 ->
+//    35.4; block by block 31.3 and 38.7), but for three or four register slots of a 64-deep tile,
+//    where a block's four groups spill less (S2 R4: 29.7 -> 27.8 us and 39.7 -> 31.7; group by
+//    group 27.2 and 41.7).
+//  - 128 x 96 wave tiles have the room (fused 24.9 us with the array, 26.3 block by block).
+// A stored K x M keeps the array for every tile.
 template <int N4, class HW>
 __device__ __forceinline__ void load_bias(const Params& p, int n0, int lane, f32x4 (&bv)[N4])
 {

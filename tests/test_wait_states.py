@@ -144,3 +144,40 @@ def test_no_register_is_restored_under_an_inner_lane_mask(scans):
     assert sum(n for _, _, n in scans) > 1000
     bad = [v for _, vs, _ in scans for v in vs]
     assert not bad, (len(bad), bad[:3])
+
+
+READELF = "/opt/rocm/llvm/bin/llvm-readelf"
+
+
+def _registers(path):
+    """{tile-at-a-time kernel's template arguments: (vector registers, bytes of scratch)}"""
+    notes = subprocess.run([READELF, "--notes", path], check=True, stdout=subprocess.PIPE, text=True).stdout
+    out = {}
+    for block in notes.split("- .agpr_count:")[1:]:
+        value = lambda key: re.search(key + r":\s+(\S+)", block)[1]
+        cfg = re.search(r"4KCfgI([Li\dE]+)EE", value(r"\.name"))
+        if cfg:
+            out[tuple(map(int, re.findall(r"Li(\d+)E", cfg[1] + "E")))] = (
+                int(value(r"\.vgpr_count")), int(value(r"\.private_segment_fixed_size")))
+    return out
+
+
+def test_the_bias_of_a_tile_takes_no_registers_that_the_kernel_lacks(tmp_path):
+    # held whole it took two blocks of 64 x 96 waves per compute unit to one (more than 256
+    # registers), and 128 x 128 waves to 400 - 964 bytes of scratch (280 - 392 without)
+    if not os.path.exists(READELF):
+        pytest.skip("no llvm-readelf")
+    kernels = {}
+    for code in _code_objects(b.LIB):
+        path = str(tmp_path / "code.co")
+        open(path, "wb").write(code)
+        kernels.update(_registers(path))
+    seen = set()
+    for (_, _, _, _, wm, wn, _, r, _, _, _, a_km, *_), (vgprs, scratch) in kernels.items():
+        if a_km:
+            continue               # A stored K x M keeps the array
+        seen.add((wm, wn))
+        if (wm, wn) == (64, 96):
+            assert vgprs <= 256
+        assert scratch <= (0 if (wm, wn) != (128, 128) else 392 if r > 2 else 296), (wm, wn, r)
+    assert {(64, 96), (128, 96), (128, 128), (64, 64)} <= seen
