@@ -19,6 +19,11 @@ hipError_t prepare_instance()
     attr_rc = hipFuncSetAttribute((const void*)alcop_mainloop<C, Gfx950>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   C::AM == 3 ? 160 * 1024 : C::LDS_BYTES);
+    if constexpr (mainloop_small<C>()) {
+      if (attr_rc == hipSuccess)
+        attr_rc = hipFuncSetAttribute((const void*)alcop_mainloop_small<C, Gfx950>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+    }
   });
   return attr_rc;
 }
@@ -28,6 +33,13 @@ hipError_t launch_instance(const Params& p, dim3 grid, hipStream_t st)
 {
   const hipError_t rc = prepare_instance<C>();
   if (rc != hipSuccess) return rc;
+  if constexpr (mainloop_small<C>()) {
+    SmallArgs s;
+    if (small_args(p, grid.y, &s)) {
+      alcop_mainloop_small<C, Gfx950><<<grid, dim3(C::NT), dynamic_lds_bytes<C>(p), st>>>(s);
+      return hipGetLastError();
+    }
+  }
   alcop_mainloop<C, Gfx950><<<grid, dim3(C::NT), dynamic_lds_bytes<C>(p), st>>>(p);
   return hipGetLastError();
 }

@@ -13,6 +13,11 @@ hipError_t prepare_ksplit()
   std::call_once(once, [] {
     attr_rc = hipFuncSetAttribute((const void*)alcop_ksplit<C, Gfx950>,
                                   hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+    if constexpr (C::AM == 0) {
+      if (attr_rc == hipSuccess)
+        attr_rc = hipFuncSetAttribute((const void*)alcop_ksplit_small<C, Gfx950>,
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS_BYTES);
+    }
   });
   return attr_rc;
 }
@@ -22,6 +27,13 @@ hipError_t launch_ksplit(const Params& p, dim3 grid, hipStream_t st)
 {
   const hipError_t rc = prepare_ksplit<C>();
   if (rc != hipSuccess) return rc;
+  if constexpr (C::AM == 0) {
+    SmallArgs s;
+    if (small_args(p, grid.y, &s)) {
+      alcop_ksplit_small<C, Gfx950><<<grid, dim3(C::NT), C::LDS_BYTES, st>>>(s);
+      return hipGetLastError();
+    }
+  }
   alcop_ksplit<C, Gfx950><<<grid, dim3(C::NT), C::LDS_BYTES, st>>>(p);
   return hipGetLastError();
 }

@@ -115,6 +115,82 @@ struct Params {
   FastDiv rQ, rPQ, rWsDiv, rImg, rCP, rC8, rS;
 };
 
+// The arguments of a product of matrices in 64 bytes, for kernels that small calls are given.  A call
+// whose kernel takes 2 to 3 us is bound by how fast launches can be issued, and that depends on the bytes of
+// arguments: one launch every 2.8 us with 16 or 64 bytes, 3.4 with 128, 3.7 with the 368 of Params (empty
+// kernels; the line lies at one 64-byte line).  N and K are multiples of 8: their low bits hold flags.
+struct SmallArgs {
+  const void* A;
+  const void* B;
+  void* C;
+  int M, N, K;                 // N: + 1 raster order, + 2 batched; K: + out_dtype, + 4 ReLU
+  int lda, ldb, ldc;
+  union {
+    const float* bias;         // one matrix
+    int strideAB[2];           // batched, no bias
+  };
+  int strideC;
+  float alpha;
+};
+static_assert(sizeof(SmallArgs) == 64, "one line");
+
+// Whether a call can be described so; the unaligned entry points' zero-padded images cannot.
+inline bool small_args(const Params& p, unsigned batch, SmallArgs* s)
+{
+  const bool batched = batch > 1;
+  if (p.c_any || p.Mv != p.M || p.Nv != p.N || ((p.N | p.K) & 7) || (p.raster & ~1) || p.pf_dist) return false;
+  if (batched && (p.bias || (p.strideA | p.strideB | p.strideC) >> 31)) return false;
+  s->A = p.A;
+  s->B = p.B;
+  s->C = p.C;
+  s->M = p.M;
+  s->N = p.N | p.raster | (batched ? 2 : 0);
+  s->K = p.K | p.out_dtype | (p.act ? 4 : 0);
+  s->lda = p.lda;
+  s->ldb = p.ldb;
+  s->ldc = p.ldc;
+  s->strideC = 0;
+  if (batched) {
+    s->strideAB[0] = (int)p.strideA;
+    s->strideAB[1] = (int)p.strideB;
+    s->strideC = (int)p.strideC;
+  } else {
+    s->bias = p.bias;
+  }
+  s->alpha = p.alpha;
+  return true;
+}
+
+template <class C>
+__device__ __forceinline__ Params expand_args(const SmallArgs& s)
+{
+  Params p = {};
+  p.A = s.A;
+  p.B = s.B;
+  p.C = s.C;
+  p.M = p.Mv = s.M;
+  p.N = p.Nv = s.N & ~7;
+  p.K = s.K & ~7;
+  p.lda = s.lda;
+  p.ldb = s.ldb;
+  p.ldc = s.ldc;
+  if (s.N & 2) {
+    p.strideA = s.strideAB[0];
+    p.strideB = s.strideAB[1];
+    p.strideC = s.strideC;
+  } else {
+    p.bias = s.bias;
+  }
+  p.out_dtype = s.K & 3;
+  p.act = (s.K >> 2) & 1;
+  p.alpha = s.alpha;
+  p.raster = s.N & 1;
+  p.ntm = (p.M + C::BM - 1) / C::BM;
+  p.ntn = (p.N + C::BN - 1) / C::BN;
+  p.group_m = p.ntm < 8 ? p.ntm : 8;
+  return p;
+}
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
@@ -528,7 +604,7 @@ __device__ __forceinline__ void store_chunk_if(const Params& p, char* dst, int n
 }
 
 template <class C, class HW>
-__global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
+__device__ __forceinline__ void mainloop_body(const Params& p)
 {
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, WM = C::WM, WN = C::WN, S = C::S;
   constexpr int TM = C::TM, TN = C::TN, NKI = C::NKI, NLA = C::NLA, NLB = C::NLB;
@@ -1013,6 +1089,25 @@ __global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
     epilogue((_Float16)0);
   else
     epilogue((__bf16)0);
+}
+
+template <class C, class HW>
+__global__ void __launch_bounds__(C::NT) alcop_mainloop(const Params p)
+{
+  mainloop_body<C, HW>(p);
+}
+
+// The tiles that products of a few hundred rows and columns are given (SmallArgs).
+template <class C>
+constexpr bool mainloop_small()
+{
+  return C::AM == 0 && !C::SK && !C::PF && C::BM == 64 && C::BN == 64 &&
+         (C::BK == 64 ? C::FUSE && C::S >= 3 && C::R == 2 : C::BK == 32 && C::S == 3 && C::R == 1);
+}
+template <class C, class HW>
+__global__ void __launch_bounds__(C::NT) alcop_mainloop_small(const SmallArgs s)
+{
+  mainloop_body<C, HW>(expand_args<C>(s));
 }
 
 }  // namespace alcop

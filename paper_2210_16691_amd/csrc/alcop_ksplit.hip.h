@@ -98,7 +98,7 @@ struct WCfg {
 };
 
 template <class C, class HW>
-__global__ void __launch_bounds__(C::NT) alcop_ksplit(const Params p)
+__device__ __forceinline__ void ksplit_body(const Params& p)
 {
   constexpr int BM = C::BM, BN = C::BN, BK = C::BK, S = C::S, TM = C::TM, TN = C::TN;
   using OA = typename C::OA;
@@ -332,6 +332,18 @@ __global__ void __launch_bounds__(C::NT) alcop_ksplit(const Params p)
     else
       store((__bf16)0);
   }
+}
+
+template <class C, class HW>
+__global__ void __launch_bounds__(C::NT) alcop_ksplit(const Params p)
+{
+  ksplit_body<C, HW>(p);
+}
+
+template <class C, class HW>
+__global__ void __launch_bounds__(C::NT) alcop_ksplit_small(const SmallArgs s)
+{
+  ksplit_body<C, HW>(expand_args<C>(s));
 }
 
 }  // namespace alcop

@@ -719,6 +719,17 @@ void ksplit_entry(const void* p)
 }
 
 template <class C>
+void ksplit_small_entry(const void* p)
+{
+  alcop::alcop_ksplit_small<C, Emu>(*(const alcop::SmallArgs*)p);
+}
+template <class C>
+void mainloop_small_entry(const void* p)
+{
+  alcop::alcop_mainloop_small<C, Emu>(*(const alcop::SmallArgs*)p);
+}
+
+template <class C>
 void convres_entry(const void* p)
 {
   alcop::alcop_convres<C, Emu>(*(const alcop::Params*)p);

@@ -14,6 +14,13 @@ namespace alcop {
 template <class C>
 hipError_t launch_emulated(const Params& p, dim3 grid, hipStream_t)
 {
+  if constexpr (mainloop_small<C>()) {
+    SmallArgs s;
+    if (small_args(p, grid.y, &s)) {
+      emu::run_grid(&emu::mainloop_small_entry<C>, &s, C::NT, dynamic_lds_bytes<C>(p), grid.x, grid.y, grid.z);
+      return hipSuccess;
+    }
+  }
   emu::run_grid(&emu::mainloop_entry<C>, &p, C::NT, dynamic_lds_bytes<C>(p), grid.x, grid.y, grid.z);
   return hipSuccess;
 }
@@ -45,6 +52,13 @@ void add_stream(std::vector<KernelEntry>& t)
 template <class C>
 hipError_t launch_emulated_ksplit(const Params& p, dim3 grid, hipStream_t)
 {
+  if constexpr (C::AM == 0) {
+    SmallArgs s;
+    if (small_args(p, grid.y, &s)) {
+      emu::run_grid(&emu::ksplit_small_entry<C>, &s, C::NT, C::LDS_BYTES, grid.x, grid.y, grid.z);
+      return hipSuccess;
+    }
+  }
   emu::run_grid(&emu::ksplit_entry<C>, &p, C::NT, C::LDS_BYTES, grid.x, grid.y, grid.z);
   return hipSuccess;
 }
