@@ -592,6 +592,7 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
   p.bias = (const float*)c.bias;
   p.act = c.act;
   p.group_m = std::min(8, p.ntm);
+  if (c.op != ALCOP_OP_CONV2D) p.keep = c.bias != nullptr || c.act;   // a layer's result (store_chunk)
   // sharers of a panel among the blocks one XCD runs side by side (32 CUs, blocks per CU by LDS)
   const int per_cu = std::max(1, std::min(2, (160 * 1024) / e->lds_bytes));
   // The touch addresses of an M/N-contiguous operand walk whole k-tiles; with a partial last

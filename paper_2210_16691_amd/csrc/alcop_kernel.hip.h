@@ -102,6 +102,8 @@ struct Params {
     // ... with a resident patch for any geometry: the second half of a window's last chunk is not of
     // the window
     int ragged;
+    // products of matrices: C stays in the caches (store_chunk)
+    int keep;
   };
   // persistent producer / consumer kernels (alcop_stream.hip.h): blocks launched and batch count;
   // block b works on tiles b, b + sgrid, b + 2 sgrid, ... of the ntm * ntn * sbatch tiles
@@ -188,6 +190,7 @@ __device__ __forceinline__ Params expand_args(const SmallArgs& s)
   p.ntm = (p.M + C::BM - 1) / C::BM;
   p.ntn = (p.N + C::BN - 1) / C::BN;
   p.group_m = p.ntm < 8 ? p.ntm : 8;
+  p.keep = p.bias != nullptr || p.act;
   return p;
 }
 
@@ -267,6 +270,8 @@ struct KCfg {
   using OB = Opnd<BL ? LAY_K : LAY_MN, BN, WN, BK, NT>;
   static constexpr int TM = WM / 32, TN = WN / 32, NKI = BK / 16;
   static constexpr bool FLAT_STORES = !AL && TM == 4 && TN == 4;   // see store_chunk_if
+  // kernels that can leave C in the caches (store_chunk): layers; not where no register is free
+  static constexpr bool KEEPS = AM == 0 && !AL && !SK && !FLAT_STORES;
   // groups of bias values held in the epilogue (see load_bias)
   static constexpr int BIAS_GROUPS = AL                   ? TN * 4
                                      : TM == 4 && TN == 4 ? (R > 2 && BK > 32 ? 4 : 1)
@@ -552,6 +557,11 @@ __device__ __forceinline__ void park_band(const Params& p, f32x16 (&acc)[TN][TM]
   }
 }
 
+template <bool V>
+struct KeepC {
+  static constexpr bool value = V;
+};
+
 // Stores one 16-byte chunk of a row of C, columns n .. of it.  C's rows start at multiples of 16
 // bytes and hold whole chunks, or (c_any) anywhere: then a chunk goes out at its element-aligned
 // address, and the row's last, partial chunk element by element.  A copy of C through an aligned
@@ -571,11 +581,23 @@ __device__ __forceinline__ void store_elements(const Params& p, char* dst, int n
   }
 }
 
-template <class OT, class HW>
+//
+// KEEP: the store is written through and its line stays in the memory-side cache, where another XCD finds
+// it; otherwise the line is the first to be evicted (non-temporal).  The result of a layer with a bias or an
+// activation is what the next layer reads: the two layers of 4096 x 768 x 3072 took 55.0 us non-temporal, 49.0
+// so (a plain store 49 to 51: dirty lines are written back when the kernel ends).  Of 60 such pairs, 130 to 8000
+// tokens, one was slower (2 %) and the others 0 to 20 % faster.  A result that nothing asks for again takes the place of
+// operands: 3 to 14 % lost in the gradient products of 16 sizes of 60, up to 30 % in scores of 50 MB and more.
+template <class OT, class HW, bool KEEP = false>
 __device__ __forceinline__ void store_chunk(const Params& p, char* dst, int n, u32x4 v)
 {
   if (!p.c_any) {
-    if (n < p.N) HW::global_store16(dst, v);
+    if (n < p.N) {
+      if constexpr (KEEP)
+        HW::global_store16_through(dst, v);
+      else
+        HW::global_store16(dst, v);
+    }
     return;
   }
   constexpr int PER = 16 / (int)sizeof(OT);
@@ -1055,31 +1077,41 @@ __device__ __forceinline__ void mainloop_body(const Params& p)
       // lanes of an instruction idle and the last instruction covers fewer rows
       constexpr bool EVEN = 64 % LPR == 0 && 32 % RPI == 0;
       constexpr int NIT = (32 + RPI - 1) / RPI;
+      auto store_band = [&](auto keep) __attribute__((always_inline)) {
 #pragma unroll
-      for (int t = 0; t < NIT; t++) {
-        int r = t * RPI + lane / LPR;
-        const int c16 = lane % LPR;
-        bool lane_ok = true;
-        if constexpr (!EVEN) {
-          lane_ok = lane < RPI * LPR && r < 32;
-          if (!lane_ok) r = 0;            // every lane takes part in the read; idle ones store nothing
+        for (int t = 0; t < NIT; t++) {
+          int r = t * RPI + lane / LPR;
+          const int c16 = lane % LPR;
+          bool lane_ok = true;
+          if constexpr (!EVEN) {
+            lane_ok = lane < RPI * LPR && r < 32;
+            if (!lane_ok) r = 0;            // every lane takes part in the read; idle ones store nothing
+          }
+          const u32x4 v = HW::lds_read16(ebase + r * RS + c16 * 16);
+          int m = m0 + j * 32 + r;
+          const int n = n0 + c16 * (16 / OB);
+          bool row_ok = m < p.Mv;
+          if constexpr (C::AM == 3) {
+            // position of the padded output space -> output pixel; columns >= Q are not stored
+            const int jj = p_j0 + wm * WM + j * 32 + r;
+            const int pp = jj / p.cWp, qq = jj - pp * p.cWp;
+            row_ok = pp < p.cP && qq < p.cQ;
+            m = (p_img * p.cP + pp) * p.cQ + qq;
+          }
+          char* dst = Cb + ((long)m * p.ldc + n) * OB;
+          if constexpr (C::FLAT_STORES)
+            store_chunk_if<OT, HW>(p, dst, n, v, lane_ok & row_ok);
+          else if (lane_ok && row_ok)
+            store_chunk<OT, HW, decltype(keep)::value>(p, dst, n, v);
         }
-        const u32x4 v = HW::lds_read16(ebase + r * RS + c16 * 16);
-        int m = m0 + j * 32 + r;
-        const int n = n0 + c16 * (16 / OB);
-        bool row_ok = m < p.Mv;
-        if constexpr (C::AM == 3) {
-          // position of the padded output space -> output pixel; columns >= Q are not stored
-          const int jj = p_j0 + wm * WM + j * 32 + r;
-          const int pp = jj / p.cWp, qq = jj - pp * p.cWp;
-          row_ok = pp < p.cP && qq < p.cQ;
-          m = (p_img * p.cP + pp) * p.cQ + qq;
-        }
-        char* dst = Cb + ((long)m * p.ldc + n) * OB;
-        if constexpr (C::FLAT_STORES)
-          store_chunk_if<OT, HW>(p, dst, n, v, lane_ok & row_ok);
-        else if (lane_ok && row_ok)
-          store_chunk<OT, HW>(p, dst, n, v);
+      };
+      if constexpr (C::KEEPS) {
+        if (p.keep)
+          store_band(KeepC<true>{});
+        else
+          store_band(KeepC<false>{});
+      } else {
+        store_band(KeepC<false>{});
       }
     }
   };

@@ -256,19 +256,29 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
           // lanes of an instruction idle and the last instruction covers fewer rows
           constexpr bool EVEN = 64 % LPR == 0 && 32 % RPI == 0;
           constexpr int NIT = (32 + RPI - 1) / RPI;
+          auto store_band = [&](auto keep) __attribute__((always_inline)) {
 #pragma unroll
-          for (int t = 0; t < NIT; t++) {
-            int r = t * RPI + lane / LPR;
-            const int c16 = lane % LPR;
-            bool lane_ok = true;
-            if constexpr (!EVEN) {
-              lane_ok = lane < RPI * LPR && r < 32;
-              if (!lane_ok) r = 0;        // every lane takes part in the read; idle ones store nothing
+            for (int t = 0; t < NIT; t++) {
+              int r = t * RPI + lane / LPR;
+              const int c16 = lane % LPR;
+              bool lane_ok = true;
+              if constexpr (!EVEN) {
+                lane_ok = lane < RPI * LPR && r < 32;
+                if (!lane_ok) r = 0;        // every lane takes part in the read; idle ones store nothing
+              }
+              const u32x4 v = HW::lds_read16(ebase + r * RS + c16 * 16);
+              const int m = m0 + jj * 32 + r;
+              const int n = n0 + c16 * (16 / OBY);
+              if (lane_ok && m < p.Mv) store_chunk<OT, HW, decltype(keep)::value>(p, Cb + ((long)m * p.ldc + n) * OBY, n, v);
             }
-            const u32x4 v = HW::lds_read16(ebase + r * RS + c16 * 16);
-            const int m = m0 + jj * 32 + r;
-            const int n = n0 + c16 * (16 / OBY);
-            if (lane_ok && m < p.Mv) store_chunk<OT, HW>(p, Cb + ((long)m * p.ldc + n) * OBY, n, v);
+          };
+          if constexpr (C::AM == 0 && !C::AL) {
+            if (p.keep)
+              store_band(KeepC<true>{});
+            else
+              store_band(KeepC<false>{});
+          } else {
+            store_band(KeepC<false>{});
           }
         }
       };

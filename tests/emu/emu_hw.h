@@ -565,6 +565,7 @@ struct Emu {
     else
       fail("global store outside the output: block %u,%u thread %d", blk()->bx, blk()->by, blk()->cur);
   }
+  static void global_store16_through(void* ptr, u32x4 v) { global_store16(ptr, v); }
   static void global_store16_keep(void* ptr, u32x4 v) { global_store16(ptr, v); }
   template <class V>
   static void global_store(void* ptr, V v)
