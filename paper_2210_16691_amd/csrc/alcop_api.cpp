@@ -226,6 +226,7 @@ std::mutex g_cache_mu;
 struct CacheEntry {
   alcop_sched s;
   bool tuned;      // by alcop_tune or a cache file; else the library's pick
+  double us = 0;   // estimated time of that pick, once asked for (auto_us)
 };
 std::map<CacheKey, CacheEntry> g_cache;    // problem -> chosen schedule
 
@@ -355,6 +356,18 @@ int auto_sched(const alcop_problem& p, alcop_sched* out)
   std::lock_guard<std::mutex> lk(g_cache_mu);
   g_cache.emplace(key_of(p), CacheEntry{*out, false});
   return ALCOP_OK;
+}
+
+// The estimated time of a product with the library's pick; negative where a schedule was tuned for it.
+double auto_us(const alcop_problem& p)
+{
+  alcop_sched s;
+  if (auto_sched(p, &s)) return -1.0;
+  std::lock_guard<std::mutex> lk(g_cache_mu);
+  const auto it = g_cache.find(key_of(p));
+  if (it == g_cache.end() || it->second.tuned) return -1.0;
+  if (it->second.us == 0.0) it->second.us = measured_best_us(p);
+  return it->second.us;
 }
 
 // The same for a convolution call, whose image geometry decides which patch kernels can serve it: a
@@ -1093,6 +1106,12 @@ struct Packer {
     g.s_batch = s_batch;
     g.s_row = s_row;
   }
+  double bytes() const
+  {
+    double n = 0;
+    for (int i = 0; i < p.nseg; i++) n += 16.0 * p.seg[i].chunks;
+    return n;
+  }
   int launch(hipStream_t st) const
   {
     if (too_big) return ALCOP_ERR_SIZE;
@@ -1522,8 +1541,6 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
   if (rc) return rc;
   if (!a_ok) pk.matrix(A, ws + off[0], batch, a_rows, a_cols, strideA, lda, a_rd, a_cd, 2);
   if (!b_ok) pk.matrix(B, ws + off[1], batch, b_rows, b_cols, strideB, ldb, b_rd, b_cd, 2);
-  rc = pk.launch(st);
-  if (rc) return rc;
   // a tuned schedule is one for the padded problem
   alcop_sched tuned;
   if (c.M != m8 && (!sched || sched->bm == 0)) {
@@ -1531,6 +1548,34 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
     padded.M = m8;
     if (tuned_sched(padded, &tuned)) sched = &tuned;
   }
+  // Without the copies, in one launch, where no schedule says otherwise and the copies would not
+  // be paid back.  Rows hold eight elements and are less than 2^23 apart (32-bit offsets within a tile);
+  // nothing that is read is overwritten by the result.
+  const int min_row = std::min(transA ? M : K, transB ? K : N);
+  if (pk.p.nseg > 0 && batch == 1 && !far && (!sched || sched->bm == 0) && min_row >= 8 &&
+      std::max(lda, ldb) < (1L << 23) && !meets(A, bytes(2, lda, strideA, a_rows, a_cols), C, c_bytes) &&
+      !meets(B, bytes(2, ldb, strideB, b_rows, b_cols), C, c_bytes) &&
+      !(ep && ep->bias && meets(ep->bias, 4.0 * N, C, c_bytes))) {
+    const double us = auto_us(problem_of(c));
+    if (us >= 0.0 && direct_pays(M, N, K, us, pk.bytes())) {
+      DirectArgs d;
+      d.A = A;
+      d.B = B;
+      d.C = C;
+      d.bias = ep ? (const float*)ep->bias : nullptr;
+      d.M = M;
+      d.N = N;
+      d.K = K;
+      d.lda = (int)lda;
+      d.ldb = (int)ldb;
+      d.ldc = (int)ldc;
+      d.alpha = c.alpha;
+      d.flags = (int)out | (c.act ? 4 : 0) | 8 | (c.c_any ? 16 : 0);
+      return launch_direct(d, in == ALCOP_BF16, transA, transB, st) == hipSuccess ? ALCOP_OK : ALCOP_ERR_LAUNCH;
+    }
+  }
+  rc = pk.launch(st);
+  if (rc) return rc;
   rc = run(c, sched, hip_stream);
   if (rc || !far) return rc;
   const CopyOutParams o{c.C, C, batch, M, N, osz, n8, c.strideC, ldc, strideC};

@@ -199,4 +199,32 @@ inline bool measured_conv_applies(const alcop_problem& p, const MeasuredConv& m)
   return m.s.variant != 3 || (double)((p.M + 63) / 64) * ((p.N + 63) / 64) <= 512;
 }
 
+// The estimated time of the cheapest of the measured kernels.
+inline double measured_best_us(const alcop_problem& p)
+{
+  double best = 1e30;
+  for (const MeasuredCost& m : kMeasured)
+    if (measured_applies(p, m)) best = std::min(best, measured_us(p, m));
+  return best;
+}
+
+// Products of operands that are not made of aligned chunks: padded copies and a pipelined kernel
+// (`product_us` by its estimate, `copied` bytes written by the copy), or 64 x 64 tiles that load them as
+// they are (alcop_direct.hip.h).  Fitted on one half of 296 products (16 to 4096 rows, columns and K, every
+// layout, bf16); on the other half the estimates are within 17 and 12 % at the 90th percentile.  A k-tile of
+// the direct kernel costs 0.3 us per turn (misaligned loads: 24 bytes per clock and compute unit, the aligned
+// ones of the pipelined loops 40 to 50), so it loses on long K and where tiles are many; short of that it
+// saves the copy's launch (216 x 89 x 1766: 10.2 us with copies, 12.3 without; 142 x 1816 x 229: 7.8 and 4.9).
+// With the line at 0.85 the direct kernel is taken for 73 % of the products, 1.38 times faster in the mean over
+// all of them; one is slower by more than 1 % (26 x 30 x 567, one operand copied: 6.5 and 7.3), at 1.0 there
+// are eleven.
+inline bool direct_pays(int M, int N, int K, double product_us, double copied)
+{
+  const double tiles = (double)((M + 63) / 64) * ((N + 63) / 64), turns = (double)(((long)tiles + 255) / 256);
+  const double kt = (K + 63) / 64, bytes = 2.0 * ((double)M * K + (double)K * N + (double)M * N);
+  const double with_copies = 2.38 + 1.41 * product_us + 1.64 * copied / 5.1e6;
+  const double direct = 3.12 + (0.033 + 0.282 * turns) * kt + 0.267 * turns + 0.68 * bytes / 5.1e6;
+  return direct < 0.85 * with_copies;
+}
+
 }  // namespace alcop

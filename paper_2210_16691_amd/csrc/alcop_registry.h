@@ -1,8 +1,10 @@
 // Table of the kernels built into the library: one entry per template instance.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <type_traits>
 #include <vector>
 
+#include "alcop_direct.hip.h"
 #include "alcop_kernel.hip.h"
 #include "alcop_pack.hip.h"
 #include "alcop_splitk.hip.h"
@@ -54,6 +56,28 @@ hipError_t launch_splitk_reduce(const ReduceParams& p, dim3 grid, hipStream_t st
 hipError_t launch_pack(const PackParams& p, unsigned blocks, hipStream_t st);
 // C from a dense image of it in the workspace.
 hipError_t launch_copy_out(const CopyOutParams& p, hipStream_t st);
+
+// Product of operands at any element address (alcop_direct.hip.h).
+hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, hipStream_t st);
+// ... with a launcher of one configuration, LAUNCH<DCfg>::go(args, blocks, stream).  Two k-tiles ahead
+// where there are no more (K <= 128: 235 x 3780 x 59 4.2 us, 4.5 with four, which load the last again), else
+// four (26 x 41 x 2500 22.7 us with two, 15.8 with four).
+template <template <class> class LAUNCH>
+hipError_t dispatch_direct(const DirectArgs& a, int dt, bool transA, bool transB, hipStream_t st)
+{
+  const unsigned blocks = (unsigned)((a.M + 63) / 64) * (unsigned)((a.N + 63) / 64);
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  auto depth = [&](auto cdt, auto cbl, auto cal) {
+    constexpr int DT = decltype(cdt)::value, BL = decltype(cbl)::value, AL = decltype(cal)::value;
+    return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL>>::go(a, blocks, st);
+  };
+  auto layouts = [&](auto cdt) {
+    if (transA) return transB ? depth(cdt, I1{}, I1{}) : depth(cdt, I0{}, I1{});
+    return transB ? depth(cdt, I1{}, I0{}) : depth(cdt, I0{}, I0{});
+  };
+  return dt ? layouts(I1{}) : layouts(I0{});
+}
 
 // Device address and size of the library's own scratch array on the current device (set up on
 // the first call per device; allocates nothing afterwards).  Its size is part of the interface

@@ -334,6 +334,19 @@ hipError_t launch_pack(const PackParams& p, unsigned blocks, hipStream_t)
   emu::run_grid(&pack_entry, &p, PACK_THREADS, 0, blocks, 1, 1);
   return hipSuccess;
 }
+template <class C>
+struct EmulatedDirect {
+  static void entry(const void* p) { alcop_direct<C, emu::Emu>(*(const DirectArgs*)p); }
+  static hipError_t go(const DirectArgs& a, unsigned blocks, hipStream_t)
+  {
+    emu::run_grid(&entry, &a, C::NT, C::LDS_BYTES, blocks, 1, 1);
+    return hipSuccess;
+  }
+};
+hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, hipStream_t st)
+{
+  return dispatch_direct<EmulatedDirect>(a, dt, transA, transB, st);
+}
 static void copy_out_entry(const void* p) { alcop_copy_out<emu::Emu>(*(const CopyOutParams*)p); }
 hipError_t launch_copy_out(const CopyOutParams& p, hipStream_t)
 {

@@ -1,0 +1,75 @@
+"""Products of operands that are not made of aligned chunks, in one launch (csrc/alcop_direct.hip.h): every
+layout at the edges of tiles and k-tiles, exactly.  Around the operands lie infinities, around C NaN."""
+import numpy as np
+import pytest
+import torch
+
+import emu_util as emu
+import oracle
+import paper_2210_16691_amd as al
+import workloads as wl
+from test_emulated_unaligned import _embed, _untouched
+
+TDT = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}
+ODT = {"f16": oracle.F16, "bf16": oracle.BF16}
+ADT = {"f16": al.F16, "bf16": al.BF16, "f32": al.F32}
+
+# the smallest rows; edges of 64 in every extent; one, two, three and more k-tiles, whole and not
+SIZES = [(9, 8, 8), (8, 9, 9), (64, 67, 64), (65, 63, 65), (130, 71, 129), (67, 129, 191), (66, 70, 320), (65, 9, 385)]
+
+
+def _case(dt, out, size, tA, tB, dev):
+    M, N, K = size
+    A0 = wl.small_ints((K, M) if tA else (M, K), dt, 50 + M)
+    B0 = wl.small_ints((N, K) if tB else (K, N), dt, 60 + N)
+    ref = oracle.gemm(wl.bits(A0), wl.bits(B0), ODT[dt], bool(tA), bool(tB))
+    bias0 = (torch.arange(N) % 5 - 2).float()
+    ref = oracle.epilogue(ref, 0.5, bias0.double().numpy(), 1)
+    ref = torch.from_numpy(ref).to(TDT[out]).double().numpy()      # sums here are exact in fp32
+
+    def place(t, offset, pad, fill):
+        view, buf = _embed(t, offset, pad, fill=fill)
+        moved = buf.to(dev)
+        return moved[offset:].as_strided(view.shape, view.stride()), moved
+
+    A, _ = place(A0, 1, 3, float("inf"))
+    B, _ = place(B0, 3, 1, float("inf"))
+    C, Cbuf = place(torch.full((M, N), float("nan"), dtype=TDT[out]), 1, 2, float("nan"))
+    bias = torch.cat([torch.full((1,), float("inf")), bias0]).to(dev)[1:]
+    ws = torch.full((al.alcop_unaligned_workspace_bytes(1, M, N, K, ADT[out]),), 255, dtype=torch.uint8, device=dev)
+    return A, B, C, Cbuf, bias, ws, ref
+
+
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dt,out", [("f16", "f16"), ("bf16", "f32"), ("bf16", "bf16")])
+def test_on_the_cpu_model(dt, out, tA, tB):
+    for n, size in enumerate(SIZES):
+        A, B, C, Cbuf, bias, ws, ref = _case(dt, out, size, tA, tB, "cpu")
+        # the workspace is out of bounds: nothing may be copied there
+        errs = emu.call(al.alcop_bmm_unaligned, A, B, C, ws, 0.5, bias, 1, transA=bool(tA), transB=bool(tB),
+                        reads=[A, B, bias], writes=[C], policy=emu.POLICIES[n % 4])
+        assert not errs, (size, errs[:3])
+        assert np.array_equal(C.double().numpy(), ref), size
+        assert _untouched(Cbuf, C), size
+
+
+@pytest.mark.parametrize("size,tA,tB", [((9, 5, 8), 0, 0), ((9, 9, 7), 0, 1), ((7, 9, 9), 1, 0), ((30, 30, 2500), 0, 0)])
+def test_rows_below_a_chunk_and_long_reductions_are_copied(size, tA, tB):
+    A, B, C, Cbuf, bias, ws, ref = _case("f16", "f32", size, tA, tB, "cpu")
+    errs = emu.call(al.alcop_bmm_unaligned, A, B, C, ws, 0.5, bias, 1, transA=bool(tA), transB=bool(tB),
+                    reads=[A, B, bias], writes=[C, ws])
+    assert not errs, errs[:3]
+    assert np.array_equal(C.double().numpy(), ref) and _untouched(Cbuf, C)
+    assert not bool((ws == 255).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dt,out", [("f16", "f16"), ("bf16", "f32"), ("bf16", "bf16")])
+def test_on_the_gpu(dt, out, tA, tB):
+    for size in SIZES + [(1021, 333, 257), (300, 2051, 67)]:
+        A, B, C, Cbuf, bias, ws, ref = _case(dt, out, size, tA, tB, "cuda:0")
+        al.alcop_bmm_unaligned(A, B, C, ws, 0.5, bias, 1, transA=bool(tA), transB=bool(tB))
+        torch.cuda.synchronize()
+        assert np.array_equal(C.double().cpu().numpy(), ref), size
+        assert _untouched(Cbuf, C) and bool((ws == 255).all()), size
