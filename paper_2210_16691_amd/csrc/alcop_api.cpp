@@ -597,7 +597,7 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
   p.out_dtype = (int)c.out;
   p.Mv = c.Mv ? c.Mv : c.M;
   p.Nv = c.Nv ? c.Nv : c.N;
-  p.c_any = c.c_any;
+  p.c_any = (short)c.c_any;
   p.ntm = (c.M + s.bm - 1) / s.bm;
   p.ntn = (c.N + s.bn - 1) / s.bn;
   p.raster = s.raster;
@@ -605,7 +605,7 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
   p.bias = (const float*)c.bias;
   p.act = c.act;
   p.group_m = std::min(8, p.ntm);
-  if (c.op != ALCOP_OP_CONV2D) p.keep = c.bias != nullptr || c.act;   // a layer's result (store_chunk)
+  if (c.op != ALCOP_OP_CONV2D) p.keep = (short)(c.bias != nullptr || c.act);   // a layer's result (store_chunk)
   // sharers of a panel among the blocks one XCD runs side by side (32 CUs, blocks per CU by LDS)
   const int per_cu = std::max(1, std::min(2, (160 * 1024) / e->lds_bytes));
   // The touch addresses of an M/N-contiguous operand walk whole k-tiles; with a partial last
@@ -629,11 +629,16 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
     p.cdw = c.cdw;
     p.cPix = c.cPix ? c.cPix : c.cC;
     p.a_span = (unsigned)(2L * c.cN * c.cH * c.cW * p.cPix);
+    p.rQ = FastDiv::of((uint32_t)c.cQ);
+    p.rPQ = FastDiv::of((uint32_t)c.cP * (uint32_t)c.cQ);
+    p.rC8 = FastDiv::of((uint32_t)(c.cC / 8));
+    p.rS = FastDiv::of((uint32_t)c.cS);
     if (e->am == 3) {
       Patch pt;
       if (patch_of(c, s, e, &pt) != ALCOP_OK) return ALCOP_ERR_SCHED;
       p.cR = c.cR;
       p.cWp = pt.wp;
+      p.rWsDiv = FastDiv::of((uint32_t)pt.wp);
       p.ntj = pt.ntj;
       p.patch_loads = pt.loads;
       p.ntm = pt.ntj * c.cN;                 // tiles of padded output positions, per image
@@ -655,13 +660,9 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
       p.rstep_c = 256 % cp;
       p.rstep_row = 256 / cp / r.ws;
       p.rstep_col = 256 / cp % r.ws;
-      p.rQ = FastDiv::of((uint32_t)c.cQ);
-      p.rPQ = FastDiv::of((uint32_t)c.cP * (uint32_t)c.cQ);
       p.rWsDiv = FastDiv::of((uint32_t)r.ws);
       p.rImg = FastDiv::of((uint32_t)r.ws * (uint32_t)r.hs);
       p.rCP = FastDiv::of((uint32_t)(r.pitch / 16));
-      p.rC8 = FastDiv::of((uint32_t)(c.cC / 8));
-      p.rS = FastDiv::of((uint32_t)c.cS);
       p.ragged = c.ragged;
     }
   }

@@ -64,37 +64,43 @@ struct FastDiv {
   }
 };
 
+// In the order of the 64-byte lines that a kernel fetches them by: a product of matrices needs the first
+// two, a convolution two more.  A line not fetched yet is a miss to memory at its first use, and the fused
+// function's values had one of their own at the start of the epilogue.  With tile_in_bands: 1529 x 2776 x 392
+// f16 10.9 -> 10.2 us, 5437 x 728 x 296 12.0 -> 11.6, gradients of 280 x 704 x 704 bf16 8.1 -> 7.75; convolution
+// 1 x 101 x 100 x 32 6.2 -> 5.85.
 struct Params {
   const void* A;
   const void* B;
   void* C;
   int M, N, K;                 // GEMM view
   int lda, ldb, ldc;           // elements (host guarantees the byte spans fit 31 bits)
-  long strideA, strideB, strideC;
-  int out_dtype;               // 0 f16, 1 bf16, 2 f32
-  // rows and columns of C that exist (M and N unless the operands are zero-padded images), and
-  // whether C's rows or its columns' extent are not 16-byte aligned
-  int Mv, Nv, c_any;
   int ntm, ntn;                // tile counts
   int raster, group_m;         // block -> tile order
+  int out_dtype;               // 0 f16, 1 bf16, 2 f32
+  // rows and columns of C that exist (M and N unless the operands are zero-padded images)
+  int Mv, Nv;
+  short c_any;                 // C's rows or its columns' extent are not 16-byte aligned
+  short keep;                  // products of matrices: C stays in the caches (store_chunk)
+  // consumer-side fused elementwise function: act(alpha * acc + bias[n])
+  float alpha;
+  int act;
+  const float* bias;
+  // persistent producer / consumer kernels (alcop_stream.hip.h): blocks launched and batch count;
+  // block b works on tiles b, b + sgrid, b + 2 sgrid, ... of the ntm * ntn * sbatch tiles
+  int sgrid, sbatch;
+  long strideA, strideB, strideC;
   // convolution geometry (AM != 0): x is NHWC, A rows are (img, p, q)
   int cH, cW, cC, cP, cQ, cS, csh, csw, cph, cpw;
   int cPix;                    // elements between neighbouring pixels of x: cC, or less where the
                                // channels of a tap span several pixels (windows that overlap)
   int cdh, cdw;                // dilation: filter tap (r, s) reads row ih0 + r * cdh, column iw0 + s * cdw
+  // by Q, P * Q, C / 8 and S for every convolution; rWsDiv: the row length of a resident patch.  A division
+  // by a value that is not constant is 35 vector instructions; a gather has two for each of a tile's
+  // loads, a patch one, and one for each of its stores (32 x 56 x 56 x 64
+  // 13.0 -> 12.5 us, 13 x 44 x 43 x 64 5.15 -> 4.75)
+  FastDiv rQ, rPQ, rWsDiv, rC8;
   unsigned a_span, b_span;     // conv: bytes of x; unused otherwise
-  // third pipeline level (HBM -> L2): every wave touches lines of k-tile kt + pf_dist when it
-  // issues k-tile kt; the lines of a panel are split among the pf_pa (pf_pb) blocks that share it
-  int pf_dist, pf_pa, pf_pb;
-  // consumer-side fused elementwise function: act(alpha * acc + bias[n])
-  float alpha;
-  const float* bias;
-  int act;
-  // split-K kernels (SK == 1): grid.z blocks share an output tile, block z reduces over
-  // k in [z * ksplit_len, min(K, (z + 1) * ksplit_len)) and stores its fp32 partial tile at
-  // C + z * zstrideC elements (C is then the caller's workspace)
-  int ksplit_len;
-  long zstrideC;
   union {
     // convolution with an LDS-resident input patch (AM == 3): filter height, row length of the
     // zero-padded image, tiles per image, direct-to-LDS loads per thread that bring in the patch
@@ -102,19 +108,23 @@ struct Params {
     // ... with a resident patch for any geometry: the second half of a window's last chunk is not of
     // the window
     int ragged;
-    // products of matrices: C stays in the caches (store_chunk)
-    int keep;
   };
-  // persistent producer / consumer kernels (alcop_stream.hip.h): blocks launched and batch count;
-  // block b works on tiles b, b + sgrid, b + 2 sgrid, ... of the ntm * ntn * sbatch tiles
-  int sgrid, sbatch;
+  FastDiv rS;
+  // third pipeline level (HBM -> L2): every wave touches lines of k-tile kt + pf_dist when it
+  // issues k-tile kt; the lines of a panel are split among the pf_pa (pf_pb) blocks that share it
+  int pf_dist, pf_pa, pf_pb;
+  // split-K kernels (SK == 1): grid.z blocks share an output tile, block z reduces over
+  // k in [z * ksplit_len, min(K, (z + 1) * ksplit_len)) and stores its fp32 partial tile at
+  // C + z * zstrideC elements (C is then the caller's workspace)
+  int ksplit_len;
+  long zstrideC;
   // convolution kernels with a resident patch for any geometry (alcop_convres.hip.h): the images as
   // rows of rWs positions, rHs rows each; the patch as rslots 16-byte slots (rloads block-wide
   // loads), rpitch bytes per position of which rc8 chunks hold channels; chunks per tap cC / 8; the
   // byte distance of neighbouring taps; entries of the chunk table
   int rWs, rHs, rslots, rloads, rpitch, rc8, rdS, rdR, rtab;
   int rstep_c, rstep_col, rstep_row;   // 256 slots further: chunks, columns, rows
-  FastDiv rQ, rPQ, rWsDiv, rImg, rCP, rC8, rS;
+  FastDiv rImg, rCP;
 };
 
 // The arguments of a product of matrices in 64 bytes, for kernels that small calls are given.  A call
@@ -438,6 +448,27 @@ __device__ __forceinline__ bool touch_line(const void* ptr, int t, int extent, i
   return true;
 }
 
+// Tile r of a matrix: bands of group_m (at most 8) row tiles, column by column within a band.  No division
+// where there is one band, nor within bands of 8: each is a chain of some 120 clocks ahead of the first load.
+__device__ __forceinline__ void tile_in_bands(const Params& p, int r, int& tm, int& tn)
+{
+  int first = 0, rows = p.ntm;
+  if (p.ntm > p.group_m) {
+    const int width = p.group_m * p.ntn;
+    const int g = r / width;
+    first = g * p.group_m;
+    rows = (p.ntm - first) < p.group_m ? (p.ntm - first) : p.group_m;
+    r -= g * width;
+  }
+  if (rows == 8) {
+    tn = r >> 3;
+    tm = first + (r & 7);
+  } else {
+    tn = r / rows;
+    tm = first + r - tn * rows;
+  }
+}
+
 // Block -> tile (paper Sec. 1: inter-tile parallelism; the order only affects L2 reuse).
 __device__ __forceinline__ void tile_of_block(const Params& p, int lid, int& tm, int& tn)
 {
@@ -446,13 +477,7 @@ __device__ __forceinline__ void tile_of_block(const Params& p, int lid, int& tm,
     // blocks are dealt to the 8 XCDs round robin: XCD x takes the x-th of 8 nearly equal runs of tiles
     const int x = lid & 7, rem8 = nblk & 7;
     lid = x * (nblk >> 3) + (x < rem8 ? x : rem8) + (lid >> 3);
-    const int width = p.group_m * p.ntn;
-    const int g = lid / width;
-    const int first = g * p.group_m;
-    const int gsz = (p.ntm - first) < p.group_m ? (p.ntm - first) : p.group_m;
-    const int rem = lid - g * width;
-    tm = first + rem % gsz;
-    tn = rem / gsz;
+    tile_in_bands(p, lid, tm, tn);
   } else {
     tm = lid / p.ntn;
     tn = lid - tm * p.ntn;
@@ -669,9 +694,9 @@ __device__ __forceinline__ void mainloop_body(const Params& p)
   bool a_in_k = true;                         // AM == 2: this lane's chunk lies below K
   int a_k8 = 0;                               // AM == 2: k of this lane's chunk within a k-tile
   if constexpr (C::SK && C::AM == 1) {        // the slice starts at tap k0 / C, channel k0 % C
-    const int tap = k0 / p.cC;
+    const int tap = (int)p.rC8.div((uint32_t)k0 / 8u);
     cc0 = k0 - tap * p.cC;
-    cr = tap / p.cS;
+    cr = (int)p.rS.div((uint32_t)tap);
     cs = tap - cr * p.cS;
     crd = cr * p.cdh;
     csd = cs * p.cdw;
@@ -696,7 +721,7 @@ __device__ __forceinline__ void mainloop_body(const Params& p)
       const int row = q / OA::CPR;
       const int c = (q % OA::CPR) ^ OA::template swz<HW>(row);
       const int jj = p_j0 + row;
-      const int ihp = jj / p.cWp;
+      const int ihp = (int)p.rWsDiv.div((uint32_t)jj);
       const int ih = ihp - p.cph, iw = jj - ihp * p.cWp - p.cpw;
       const bool ok = row < rows && (unsigned)ih < (unsigned)p.cH && (unsigned)iw < (unsigned)p.cW;
       const uint32_t off = (uint32_t)((((p_img * p.cH + ih) * p.cW) + iw) * p.cC * 2 + c * 16);
@@ -715,9 +740,9 @@ __device__ __forceinline__ void mainloop_body(const Params& p)
       // lane's own k
       a_k8 = c * 8;
       const int kc = k0 + a_k8;
-      const int tap = kc / p.cC;
+      const int tap = (int)p.rC8.div((uint32_t)kc / 8u);
       cc0 = kc - tap * p.cC;
-      cr = tap / p.cS;
+      cr = (int)p.rS.div((uint32_t)tap);
       cs = tap - cr * p.cS;
       crd = cr * p.cdh;
       csd = cs * p.cdw;
@@ -725,9 +750,9 @@ __device__ __forceinline__ void mainloop_body(const Params& p)
 #pragma unroll
     for (int i = 0; i < NLA; i++) {
       const int m = tm * BM + r + i * OA::RSTEP;
-      const int img = m / (p.cP * p.cQ);
+      const int img = (int)p.rPQ.div((uint32_t)m);
       const int pq = m - img * (p.cP * p.cQ);
-      const int pp = pq / p.cQ, qq = pq - pp * p.cQ;
+      const int pp = (int)p.rQ.div((uint32_t)pq), qq = pq - pp * p.cQ;
       ih0[i] = (m < p.M) ? pp * p.csh - p.cph : -0x40000000;
       iw0[i] = qq * p.csw - p.cpw;
       coff[i] = (uint32_t)((((img * p.cH + (pp * p.csh - p.cph)) * p.cW) + iw0[i]) * p.cPix * 2 +
@@ -1094,7 +1119,7 @@ __device__ __forceinline__ void mainloop_body(const Params& p)
           if constexpr (C::AM == 3) {
             // position of the padded output space -> output pixel; columns >= Q are not stored
             const int jj = p_j0 + wm * WM + j * 32 + r;
-            const int pp = jj / p.cWp, qq = jj - pp * p.cWp;
+            const int pp = (int)p.rWsDiv.div((uint32_t)jj), qq = jj - pp * p.cWp;
             row_ok = pp < p.cP && qq < p.cQ;
             m = (p_img * p.cP + pp) * p.cQ + qq;
           }

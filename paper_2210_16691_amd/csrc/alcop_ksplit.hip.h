@@ -160,9 +160,9 @@ __device__ __forceinline__ void ksplit_body(const Params& p)
       int row, c;
       OA::slot(i * 64 + lane, row, c);
       const int m = tm * BM + row;
-      const int img = m / (p.cP * p.cQ);
+      const int img = (int)p.rPQ.div((uint32_t)m);
       const int pq = m - img * (p.cP * p.cQ);
-      const int pp = pq / p.cQ, qq = pq - pp * p.cQ;
+      const int pp = (int)p.rQ.div((uint32_t)pq), qq = pq - pp * p.cQ;
       ih0[i] = (m < p.M) ? pp * p.csh - p.cph : -0x40000000;
       iw0[i] = qq * p.csw - p.cpw;
       coff[i] = (uint32_t)((((img * p.cH + (pp * p.csh - p.cph)) * p.cW) + iw0[i]) * p.cPix * 2 +
@@ -170,8 +170,8 @@ __device__ __forceinline__ void ksplit_body(const Params& p)
       if (i < NVA) {
         k8A[i] = c * 8;
         const int kc = kt0 * BK + (C::AM == 2 ? c * 8 : 0);
-        const int tap = kc / p.cC;
-        const int r = tap / p.cS;
+        const int tap = (int)p.rC8.div((uint32_t)kc / 8u);
+        const int r = (int)p.rS.div((uint32_t)tap);
         cc0[i] = kc - tap * p.cC;
         cs[i] = tap - r * p.cS;
         crd[i] = r * p.cdh;

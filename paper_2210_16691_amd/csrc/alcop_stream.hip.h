@@ -111,15 +111,9 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
   const bool by_xcd = p.raster == 1 && (total & 7) == 0 && (p.sgrid & 7) == 0;
   auto decode = [&](int t, int& batch, int& tm, int& tn) __attribute__((always_inline)) {
     if (by_xcd) t = (t & 7) * (total >> 3) + (t >> 3);
-    batch = t / per_mat;
+    batch = p.sbatch > 1 ? t / per_mat : 0;
     const int r = t - batch * per_mat;
-    const int width = p.group_m * p.ntn;
-    const int g = r / width;
-    const int f = g * p.group_m;
-    const int gsz = (p.ntm - f) < p.group_m ? (p.ntm - f) : p.group_m;
-    const int rem = r - g * width;
-    tm = f + rem % gsz;
-    tn = rem / gsz;
+    tile_in_bands(p, r, tm, tn);
   };
 
   if (wave >= C::NCW) {
@@ -154,9 +148,9 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
 #pragma unroll
         for (int i = 0; i < NLA; i++) {
           const int m = tm * BM + r + i * OA::RSTEP;
-          const int img = m / (p.cP * p.cQ);
+          const int img = (int)p.rPQ.div((uint32_t)m);
           const int pq = m - img * (p.cP * p.cQ);
-          const int pp = pq / p.cQ, qq = pq - pp * p.cQ;
+          const int pp = (int)p.rQ.div((uint32_t)pq), qq = pq - pp * p.cQ;
           ih0[i] = (m < p.M) ? pp * p.csh - p.cph : -0x40000000;
           iw0[i] = qq * p.csw - p.cpw;
           coff[i] = (uint32_t)((((img * p.cH + (pp * p.csh - p.cph)) * p.cW) + iw0[i]) * p.cPix * 2 + c * 16);
