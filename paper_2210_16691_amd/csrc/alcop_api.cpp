@@ -1106,6 +1106,7 @@ struct Packer {
     g.cols = cols;
     g.s_batch = s_batch;
     g.s_row = s_row;
+    g.total = (batch - 1) * s_batch + (rows - 1) * s_row + cols;
   }
   double bytes() const
   {
@@ -1662,6 +1663,7 @@ int alcop_conv2d_igemm_unaligned(const void* x, const void* w, void* y, int N, i
   if (!x_ok) {
     PackSeg& g = pk.add(f.kind, x, ws, 1, f.padded ? (long)N * H : pixels, f.padded ? (long)f.width * f.pix / 8 : c8 / 8, 2);
     g.s_row = f.padded ? (long)W * C : C;
+    g.total = pixels * C;
     if (!f.padded) {            // pixels x C -> pixels x C8: a plain matrix
       g.kind = PACK_MAT;
       g.rg = g.rows_d;
@@ -1691,6 +1693,7 @@ int alcop_conv2d_igemm_unaligned(const void* x, const void* w, void* y, int N, i
       g.s_batch = (long)S * C * K;
       g.s_grp = (long)C * K;
       g.s_row = K;
+      g.total = (long)R * S * C * K;
     }
   }
   rc = pk.launch(st);

@@ -24,8 +24,8 @@ namespace alcop {
 enum {
   PACK_MAT = 0,   // a matrix: rows of `cols` elements, zero beyond; rows may come in groups of rg
                   // of which the first nm (and the first nq groups) exist in the source
-  PACK_PIX = 1,   // an image row as pixels of cg elements (a power of two <= 8): `chans` channels
-                  // of a pixel and zeros; `pad` zero pixels before the first
+  PACK_PIX = 1,   // an image row as pixels of cg elements, 8 / cg to a chunk: cg = 1 or 2 channels, or 4 with 3
+                  // or 4 channels (`chans`) and zeros; `pad` zero pixels before the first
   PACK_WIN = 2,   // an image row as one window of cu elements per output column: the `win` elements
                   // its filter row covers (all taps and channels, contiguous in the source)
 };
@@ -39,6 +39,7 @@ struct PackSeg {
   FastDiv cpr, rows_d;    // chunks per destination row; destination rows per batch entry
   FastDiv rg;             // PACK_MAT: rows per group; PACK_WIN: chunks per window
   long s_batch, s_grp, s_row;   // source strides in elements: batch entry, row group, row
+  long total;             // elements from the source's first to its last, and what lies between
   int nq, nm, cols;       // PACK_MAT: valid groups, rows of a group, columns
   int width, chans;       // PACK_PIX / PACK_WIN: pixels of a source row, channels
   int pad, cg, stride;    // ... zero pixels on the left; elements per pixel; columns per output
@@ -72,6 +73,28 @@ __device__ __forceinline__ u32x4 load_chunk(const char* s, int esize, int lo, in
   return v;
 }
 
+// The eight 2-byte elements from element f of a source of `total` (0 <= f + 7 and f < total where any of them
+// is kept): one load but for the chunks at the source's very ends.  What belongs to no row or window of the
+// chunk is cleared afterwards (keep_elements): element by element, with a load each, a chunk of the 7 x 7
+// stem's images cost eight loads (32 x 224 x 224 x 3 8.7 us and
+// now 6.9; windows of 21 elements of 33 x 137 x 142 x 3 14.2 and 10.5).
+template <class HW>
+__device__ __forceinline__ u32x4 load_elements(const void* src, long f, long total)
+{
+  const char* s = (const char*)src + f * 2;
+  if (f >= 0 && f + 8 <= total) return HW::global_load16_any(s);
+  return load_chunk<HW>(s, 2, f < 0 ? (f < -8 ? 8 : (int)-f) : 0, total - f < 8 ? (total > f ? (int)(total - f) : 0) : 8);
+}
+
+// Elements [lo, hi) of v, zeros in place of the others.
+__device__ __forceinline__ u32x4 keep_elements(u32x4 v, int lo, int hi)
+{
+#pragma unroll
+  for (int d = 0; d < 4; d++)
+    v[d] &= (2 * d >= lo && 2 * d < hi ? 0xffffu : 0u) | (2 * d + 1 >= lo && 2 * d + 1 < hi ? 0xffff0000u : 0u);
+  return v;
+}
+
 // One thread writes one 16-byte chunk of one segment; the destinations are dense images.  Sources
 // need element alignment only.
 template <class HW>
@@ -95,7 +118,10 @@ __global__ void __launch_bounds__(PACK_THREADS) alcop_pack(const PackParams p)
     if ((int)q < g.nq && (int)m < g.nm) {
       const int c0 = (int)c * (16 / g.esize);
       const long off = (long)b * g.s_batch + (long)q * g.s_grp + (long)m * g.s_row + c0;
-      v = load_chunk<HW>((const char*)g.src + off * g.esize, g.esize, 0, g.cols - c0);
+      if (g.esize == 2)
+        v = keep_elements(load_elements<HW>(g.src, off, g.total), 0, g.cols - c0);
+      else
+        v = load_chunk<HW>((const char*)g.src + off * 4, 4, 0, g.cols - c0);
     }
   } else if (g.kind == PACK_WIN) {
     const uint32_t q = g.rg.div(c);
@@ -103,17 +129,15 @@ __global__ void __launch_bounds__(PACK_THREADS) alcop_pack(const PackParams p)
     const int f = ((int)q * g.stride - g.pad) * g.chans + e0;         // element of the image row
     const int end = g.width * g.chans - f;                            // elements left in the row
     const int hi = (g.win - e0) < end ? (g.win - e0) : end;
-    v = load_chunk<HW>((const char*)g.src + ((long)r * g.s_row + f) * 2, 2, -f, hi);
+    if (f > -8 && hi > 0) v = keep_elements(load_elements<HW>(g.src, (long)r * g.s_row + f, g.total), -f, hi);
   } else {
     const int px = 8 / g.cg;
-    const long row = (long)r * g.s_row;
-#pragma unroll
-    for (int e = 0; e < 8; e++) {
-      const int ch = e & (g.cg - 1);
-      const int iw = (int)c * px + (int)((uint32_t)e / (uint32_t)g.cg) - g.pad;
-      if (ch < g.chans && (unsigned)iw < (unsigned)g.width)
-        v[e >> 1] |= (uint32_t)HW::global_load_u16((const char*)g.src + (row + (long)iw * g.chans + ch) * 2)
-                     << (16 * (e & 1));
+    const int iw = (int)c * px - g.pad;                               // the chunk's first pixel
+    if (iw > -px && iw < g.width) {
+      v = load_elements<HW>(g.src, (long)r * g.s_row + (long)iw * g.chans, g.total);
+      if (g.cg == 4 && g.chans == 3)
+        v = u32x4{v[0], v[1] & 0xffffu, (v[1] >> 16) | (v[2] << 16), v[2] >> 16};
+      v = keep_elements(v, -iw * g.cg, (g.width - iw) * g.cg);
     }
   }
   HW::global_store16_keep((char*)g.dst + (size_t)idx * 16, v);
