@@ -794,6 +794,10 @@ __device__ __forceinline__ void mainloop_body(const Params& p)
   // A partial last k-tile selects the lane offsets that zero-fill chunks at k >= K: one select
   // per operand and k-tile, nothing per load.
   uint32_t st_ka = 0, st_kb = 0, st_dst = 0, st_tap = 0;
+  // AM 1, 2: rows of the image, none past the last k-tile.  (With the k-tile's own condition beside those on
+  // row and column the compiler branched around every load: 41 x 46 x 46 x 320, 3 x 3, 78.7 us, 74.9
+  // so; in the persistent kernel's producers 32 x 14 x 14 x 256 13.8 and 12.8.)
+  uint32_t st_rows = 0;
   uint32_t st_voffA = la.voff, st_voffB = lb.voff;
   bool st_live = false, st_pf_live = false;
   auto stage_begin = [&](int kt, int slot) {
@@ -806,7 +810,7 @@ __device__ __forceinline__ void mainloop_body(const Params& p)
     if constexpr (C::AM == 0)
       st_ka = st_live ? (uint32_t)kt * la.kstep : 0x80000000u;
     else if constexpr (C::AM != 3)
-      st_tap = (uint32_t)(((crd * p.cW + csd) * p.cPix + cc0) * 2);
+      st_rows = st_live ? (unsigned)p.cH : 0u, st_tap = (uint32_t)(((crd * p.cW + csd) * p.cPix + cc0) * 2);
     if constexpr (C::AM == 2) a_in_k = kt * BK + a_k8 < Kb;
     st_kb = st_live ? (uint32_t)kt * lb.kstep : 0x80000000u;
   };
@@ -822,9 +826,8 @@ __device__ __forceinline__ void mainloop_body(const Params& p)
       if constexpr (C::AM == 0) {
         dma(first, la.rsrc, st_voffA + st_ka + (uint32_t)i * la.step, st_dst + i * (NWAVES * 1024));
       } else {
-        bool ok = st_live && (unsigned)(ih0[i] + crd) < (unsigned)p.cH &&
-                  (unsigned)(iw0[i] + csd) < (unsigned)p.cW;
-        if constexpr (C::AM == 2) ok = ok && a_in_k;
+        bool ok = ((unsigned)(ih0[i] + crd) < st_rows) & ((unsigned)(iw0[i] + csd) < (unsigned)p.cW);
+        if constexpr (C::AM == 2) ok = ok & a_in_k;
         dma(first, la.rsrc, ok ? coff[i] + st_tap : 0x80000000u, st_dst + i * (NWAVES * 1024));
       }
     } else if (idx < NLA + NLB) {

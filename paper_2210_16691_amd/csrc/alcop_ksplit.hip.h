@@ -189,6 +189,7 @@ __device__ __forceinline__ void ksplit_body(const Params& p)
     const uint32_t kb = live ? (uint32_t)kt * ksB : 0x80000000u;
     const uint32_t ka = live ? (uint32_t)kt * ksA : 0x80000000u;
     const int k0 = kt * BK;
+    const int kend = live ? p.K : 0;
 #pragma unroll
     for (int i = 0; i < OA::NL; i++) {
       constexpr int V = NVA;
@@ -198,8 +199,8 @@ __device__ __forceinline__ void ksplit_body(const Params& p)
         off = voA[v] + (uint32_t)(i / V) * stA + ka;
         if (OA::LAY == LAY_K && k0 + k8A[v] >= p.K) off |= 0x80000000u;
       } else {
-        const bool ok = live && k0 + k8A[v] < p.K && (unsigned)(ih0[i] + crd[v]) < (unsigned)p.cH &&
-                        (unsigned)(iw0[i] + csd[v]) < (unsigned)p.cW;
+        const bool ok = (k0 + k8A[v] < kend) & ((unsigned)(ih0[i] + crd[v]) < (unsigned)p.cH) &
+                        ((unsigned)(iw0[i] + csd[v]) < (unsigned)p.cW);
         off = ok ? coff[i] + (uint32_t)(((crd[v] * p.cW + csd[v]) * p.cPix + cc0[v]) * 2) : 0x80000000u;
       }
       HW::dma16(rsA, off, dst + i * 1024);

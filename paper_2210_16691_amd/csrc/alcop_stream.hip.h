@@ -173,14 +173,14 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
       const uint32_t voffA = voA | (tail ? tmA : 0u), voffB = voB | (tail ? tmB : 0u);
       const uint32_t ka = live ? (uint32_t)ikt * ksA : 0x80000000u;
       const uint32_t kb = live ? (uint32_t)ikt * ksB : 0x80000000u;
+      const uint32_t rows = live ? (uint32_t)p.cH : 0u;    // as in alcop_kernel.hip.h
       const uint32_t tap = (uint32_t)(((crd * p.cW + csd) * p.cPix + cc0) * 2);
 #pragma unroll
       for (int i = 0; i < NLA; i++) {
         if constexpr (C::AM == 0) {
           HW::dma16(rsA, voffA + ka + (uint32_t)i * stA, dst + i * (C::NPW * 1024));
         } else {
-          const bool ok = live && (unsigned)(ih0[i] + crd) < (unsigned)p.cH &&
-                          (unsigned)(iw0[i] + csd) < (unsigned)p.cW;
+          const bool ok = ((unsigned)(ih0[i] + crd) < rows) & ((unsigned)(iw0[i] + csd) < (unsigned)p.cW);
           HW::dma16(rsA, ok ? coff[i] + tap : 0x80000000u, dst + i * (C::NPW * 1024));
         }
       }
