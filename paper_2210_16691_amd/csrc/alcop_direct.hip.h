@@ -4,8 +4,7 @@
 // launches, and a product that reads what another kernel has just written to another L2.  Here the
 // tile loads go through registers instead: a global load of 16 bytes may start at any element, a
 // direct-to-LDS load may not.  The LDS image of a tile is the one of the pipelined loops (Opnd), two
-// stages of it; two or four k-tiles are in registers
-// or on their way there.
+// stages of it; two or four k-tiles are in registers or on their way there.
 //
 // Edges.  A chunk that would reach past the end of its row starts earlier, where the row's last eight
 // elements are, and is shifted down by what it starts early; zeros come in at the top.  A row past the

@@ -97,8 +97,8 @@ struct Params {
   int cdh, cdw;                // dilation: filter tap (r, s) reads row ih0 + r * cdh, column iw0 + s * cdw
   // by Q, P * Q, C / 8 and S for every convolution; rWsDiv: the row length of a resident patch.  A division
   // by a value that is not constant is 35 vector instructions; a gather has two for each of a tile's
-  // loads, a patch one, and one for each of its stores (32 x 56 x 56 x 64
-  // 13.0 -> 12.5 us, 13 x 44 x 43 x 64 5.15 -> 4.75)
+  // loads, a patch one, and one for each of its stores (32 x 56 x 56 x 64 13.0 -> 12.5 us, 13 x 44 x 43 x 64
+  // 5.15 -> 4.75)
   FastDiv rQ, rPQ, rWsDiv, rC8;
   unsigned a_span, b_span;     // conv: bytes of x; unused otherwise
   union {
@@ -606,7 +606,6 @@ __device__ __forceinline__ void store_elements(const Params& p, char* dst, int n
   }
 }
 
-//
 // KEEP: the store is written through and its line stays in the memory-side cache, where another XCD finds
 // it; otherwise the line is the first to be evicted (non-temporal).  The result of a layer with a bias or an
 // activation is what the next layer reads: the two layers of 4096 x 768 x 3072 took 55.0 us non-temporal, 49.0

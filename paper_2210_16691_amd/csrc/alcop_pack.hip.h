@@ -76,8 +76,8 @@ __device__ __forceinline__ u32x4 load_chunk(const char* s, int esize, int lo, in
 // The eight 2-byte elements from element f of a source of `total` (0 <= f + 7 and f < total where any of them
 // is kept): one load but for the chunks at the source's very ends.  What belongs to no row or window of the
 // chunk is cleared afterwards (keep_elements): element by element, with a load each, a chunk of the 7 x 7
-// stem's images cost eight loads (32 x 224 x 224 x 3 8.7 us and
-// now 6.9; windows of 21 elements of 33 x 137 x 142 x 3 14.2 and 10.5).
+// stem's images cost eight loads (32 x 224 x 224 x 3 8.7 us and now 6.9; windows of 21 elements of
+// 33 x 137 x 142 x 3 14.2 and 10.5).
 template <class HW>
 __device__ __forceinline__ u32x4 load_elements(const void* src, long f, long total)
 {
