@@ -150,11 +150,11 @@ struct Gfx950 {
     __builtin_nontemporal_store(v, (u32x4*)ptr);
   }
   // 16-byte store written through to memory, whose line the memory-side cache keeps (device scope).  The
-  // wait state is the one the compiler leaves between a store of its own this wide and the next write
-  // of its data registers.
+  // two wait states are those the compiler leaves between a store of its own wider than 8 bytes and the
+  // next vector instruction that writes its data registers; it does not look into inline asm.
   __device__ static __forceinline__ void global_store16_through(void* ptr, u32x4 v)
   {
-    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 0" : : "v"(ptr), "v"(v) : "memory");
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" : : "v"(ptr), "v"(v) : "memory");
   }
   __device__ static __forceinline__ f32x4 global_load_f32x4(const float* ptr)
   {

@@ -3,7 +3,11 @@
 A vector-memory instruction may read a scalar register only five wait states after the vector
 instruction that wrote it.  The compiler keeps that distance for its own instructions but does not
 look into inline asm, where the direct-to-LDS loads are: with a shorter one a load can take a stale
-base address, which is a fault now and then and nothing that results show."""
+base address, which is a fault now and then and nothing that results show.
+
+A vector instruction may write the data registers of a store wider than 8 bytes only two wait states
+after it.  The stores that are written in inline asm bring both along: what follows them is the
+compiler's choice."""
 import concurrent.futures as cf
 import multiprocessing
 import os
@@ -57,6 +61,56 @@ def test_the_scan_counts_wait_states():
     for between, n in (([move, "\ts_nop 0"], 1), ([move, "\ts_nop 2", "\tv_add_u32_e32 v1, s2, v1"], 0),
                        (["\tv_readfirstlane_b32 s20, v3"] + [move] * 3, 1), (["\ts_nop 4"], 0)):
         assert len(violations("\n".join(["\tv_readfirstlane_b32 s17, v4"] + between + [load]))[1]) == n
+
+
+STORE_WAIT = 2
+
+
+def _vectors(operand):
+    m = re.match(r"v\[(\d+):(\d+)\]|v(\d+)\b", operand.strip())
+    if not m:
+        return set()
+    return {int(m[3])} if m[3] else set(range(int(m[1]), int(m[2]) + 1))
+
+
+def store_violations(asm):
+    """(stores of more than 8 bytes from inline asm, those stores of any origin whose data registers are
+    written too early, or, from inline asm, that do not bring the wait along).  Only the asm writes
+    through (sc1)."""
+    code = [t.strip() for t in asm.splitlines()]
+    code = [t for t in code if t and t[0] not in ".;" and t[-1] != ":"]
+    parts = lambda t: (t.partition(" ")[0], t.partition(" ")[2].split(","), t)
+    seen, bad = 0, []
+    for i, t in enumerate(code):
+        if not re.match(r"(global|flat|scratch|buffer)_store_dwordx[34] ", t):
+            continue
+        op, args, t = parts(t)
+        if re.search(r"\bsc1\b", t):
+            seen += 1
+            o, a, _ = parts(code[i + 1])
+            if o != "s_nop" or int(a[0], 0) + 1 < STORE_WAIT:
+                bad.append("no wait of its own: " + t)
+        data = _vectors(args[0] if op.startswith("buffer_") else args[1])
+        waited = 0
+        for o, a, text in map(parts, code[i + 1:i + 1 + STORE_WAIT]):
+            if waited >= STORE_WAIT or o.startswith(("s_cbranch", "s_branch", "s_endpgm")):
+                break
+            if o.startswith("v_") and _vectors(a[0]) & data:
+                bad.append("%d wait states: %s ... %s" % (waited, t, text))
+                break
+            waited += int(a[0], 0) + 1 if o == "s_nop" else 1
+    return seen, bad
+
+
+def test_the_scan_finds_early_writes_of_stored_registers():
+    store, through = "\tglobal_store_dwordx4 v8, v[4:7], s[0:1]", "\tglobal_store_dwordx4 v[8:9], v[4:7], off sc1"
+    write, other = "\tv_mov_b32_e32 v6, 0", "\tv_mov_b32_e32 v8, 0"
+    for code, n in (([store, write], 1), ([store, "\ts_nop 0", write], 1), ([store, "\ts_nop 1", write], 0),
+                    ([store, other, other, write], 0), ([through, "\ts_nop 1", write], 0),
+                    ([through, "\ts_nop 0", "\ts_or_b64 exec, exec, s[2:3]", write], 1),
+                    (["\tglobal_store_dwordx2 v8, v[6:7], s[0:1]", write], 0),
+                    (["\tbuffer_store_dwordx4 v[4:7], v0, s[0:3], 0 offen", write], 1)):
+        assert len(store_violations("\n".join(code))[1]) == n, code
 
 
 def late_restores(asm):
@@ -118,7 +172,8 @@ def _scan(path):
     asm = subprocess.run([OBJDUMP, "-d", "--mcpu=gfx950", "--no-show-raw-insn", path], check=True,
                          stdout=subprocess.PIPE, text=True).stdout
     tiles = re.findall(r"^[0-9a-f]+ <\w*Cfg\w*>:\n(.*?)(?=^[0-9a-f]+ <|\Z)", asm, re.M | re.S)
-    return violations(re.sub(r"//.*|<.*>:", "", asm)), [b for t in tiles for b in late_restores(t)], len(tiles)
+    code = re.sub(r"//.*|<.*>:", "", asm)
+    return violations(code), [b for t in tiles for b in late_restores(t)], len(tiles), store_violations(code)
 
 
 @pytest.fixture(scope="module")
@@ -135,14 +190,20 @@ def scans(tmp_path_factory):
 
 
 def test_loads_keep_their_distance_from_the_descriptor(scans):
-    assert sum(n for (n, _), _, _ in scans) > 100000
-    bad = [v for (_, vs), _, _ in scans for v in vs]
+    assert sum(n for (n, _), *_ in scans) > 100000
+    bad = [v for (_, vs), *_ in scans for v in vs]
     assert not bad, (len(bad), bad[:3])
 
 
 def test_no_register_is_restored_under_an_inner_lane_mask(scans):
-    assert sum(n for _, _, n in scans) > 1000
-    bad = [v for _, vs, _ in scans for v in vs]
+    assert sum(n for _, _, n, _ in scans) > 1000
+    bad = [v for _, vs, *_ in scans for v in vs]
+    assert not bad, (len(bad), bad[:3])
+
+
+def test_stored_registers_keep_their_values_until_they_are_read(scans):
+    assert sum(n for *_, (n, _) in scans) > 1000
+    bad = [v for *_, (_, vs) in scans for v in vs]
     assert not bad, (len(bad), bad[:3])
 
 
