@@ -226,7 +226,6 @@ std::mutex g_cache_mu;
 struct CacheEntry {
   alcop_sched s;
   bool tuned;      // by alcop_tune or a cache file; else the library's pick
-  double us = 0;   // estimated time of that pick, once asked for (auto_us)
 };
 std::map<CacheKey, CacheEntry> g_cache;    // problem -> chosen schedule
 
@@ -339,15 +338,17 @@ bool tuned_sched(const alcop_problem& p, alcop_sched* out)
   return true;
 }
 
-// What a NULL / zero schedule resolves to: the tuning cache, else the library's pick.
-int auto_sched(const alcop_problem& p, alcop_sched* out)
+// What a NULL / zero schedule resolves to: the tuning cache, else the library's pick (*picked).
+int auto_sched(const alcop_problem& p, alcop_sched* out, bool* picked = nullptr)
 {
   load_env_cache();
+  if (picked) *picked = true;
   {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     auto it = g_cache.find(key_of(p));
     if (it != g_cache.end()) {
       *out = it->second.s;
+      if (picked) *picked = !it->second.tuned;
       return ALCOP_OK;
     }
   }
@@ -356,18 +357,6 @@ int auto_sched(const alcop_problem& p, alcop_sched* out)
   std::lock_guard<std::mutex> lk(g_cache_mu);
   g_cache.emplace(key_of(p), CacheEntry{*out, false});
   return ALCOP_OK;
-}
-
-// The estimated time of a product with the library's pick; negative where a schedule was tuned for it.
-double auto_us(const alcop_problem& p)
-{
-  alcop_sched s;
-  if (auto_sched(p, &s)) return -1.0;
-  std::lock_guard<std::mutex> lk(g_cache_mu);
-  const auto it = g_cache.find(key_of(p));
-  if (it == g_cache.end() || it->second.tuned) return -1.0;
-  if (it->second.us == 0.0) it->second.us = measured_best_us(p);
-  return it->second.us;
 }
 
 // The same for a convolution call, whose image geometry decides which patch kernels can serve it: a
@@ -729,15 +718,21 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
   return ALCOP_OK;
 }
 
-int run(const Call& c, const alcop_sched* sched, void* stream)
+// The kernel that a call gets, or why it is refused.
+struct Resolved {
+  alcop_sched s;
+  const KernelEntry* e = nullptr;
+  bool picked = false;         // products of matrices: by the library, without a tuned schedule
+};
+int resolve(const Call& c, const alcop_sched* sched, Resolved* out)
 {
   int rc = check_call(c);
   if (rc) return rc;
   const alcop_problem prob = problem_of(c);
-  alcop_sched s;
+  alcop_sched& s = out->s;
   const bool automatic = !sched || sched->bm == 0;
   if (automatic) {
-    rc = c.op == ALCOP_OP_CONV2D ? auto_conv_sched(c, prob, &s) : auto_sched(prob, &s);
+    rc = c.op == ALCOP_OP_CONV2D ? auto_conv_sched(c, prob, &s) : auto_sched(prob, &s, &out->picked);
     if (rc) return rc;
   } else {
     s = *sched;
@@ -760,8 +755,15 @@ int run(const Call& c, const alcop_sched* sched, void* stream)
     if (rc) return rc;
     rc = call_feasible(c, s, e);
   }
-  if (rc) return rc;
-  return launch_call(c, s, e, (hipStream_t)stream);
+  out->e = e;
+  return rc;
+}
+
+int run(const Call& c, const alcop_sched* sched, void* stream)
+{
+  Resolved r;
+  const int rc = resolve(c, sched, &r);
+  return rc ? rc : launch_call(c, r.s, r.e, (hipStream_t)stream);
 }
 
 // Predicted time of a split-K schedule: the main loop as a problem with batch x nz blocks over
@@ -1550,16 +1552,19 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
     padded.M = m8;
     if (tuned_sched(padded, &tuned)) sched = &tuned;
   }
+  Resolved r;
+  rc = resolve(c, sched, &r);
+  if (rc) return rc;
   // Without the copies, in one launch, where no schedule says otherwise and the copies would not
   // be paid back.  Rows hold eight elements and are less than 2^23 apart (32-bit offsets within a tile);
   // nothing that is read is overwritten by the result.
   const int min_row = std::min(transA ? M : K, transB ? K : N);
-  if (pk.p.nseg > 0 && batch == 1 && !far && (!sched || sched->bm == 0) && min_row >= 8 &&
+  if (pk.p.nseg > 0 && batch == 1 && !far && r.picked && min_row >= 8 &&
       std::max(lda, ldb) < (1L << 23) && !meets(A, bytes(2, lda, strideA, a_rows, a_cols), C, c_bytes) &&
       !meets(B, bytes(2, ldb, strideB, b_rows, b_cols), C, c_bytes) &&
       !(ep && ep->bias && meets(ep->bias, 4.0 * N, C, c_bytes))) {
-    const double us = auto_us(problem_of(c));
-    if (us >= 0.0 && direct_pays(M, N, K, us, pk.bytes())) {
+    const double us = measured_sched_us(problem_of(c), r.s);
+    if (direct_pays(M, N, K, us, pk.bytes())) {
       DirectArgs d;
       d.A = A;
       d.B = B;
@@ -1578,7 +1583,7 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
   }
   rc = pk.launch(st);
   if (rc) return rc;
-  rc = run(c, sched, hip_stream);
+  rc = launch_call(c, r.s, r.e, st);
   if (rc || !far) return rc;
   const CopyOutParams o{c.C, C, batch, M, N, osz, n8, c.strideC, ldc, strideC};
   return launch_copy_out(o, st) == hipSuccess ? ALCOP_OK : ALCOP_ERR_LAUNCH;

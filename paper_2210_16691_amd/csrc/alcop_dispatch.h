@@ -25,6 +25,7 @@
 // were chosen on; none were held out.
 #pragma once
 #include <algorithm>
+#include <cstring>
 
 #include "../../include/alcop.h"
 
@@ -199,12 +200,16 @@ inline bool measured_conv_applies(const alcop_problem& p, const MeasuredConv& m)
   return m.s.variant != 3 || (double)((p.M + 63) / 64) * ((p.N + 63) / 64) <= 512;
 }
 
-// The estimated time of the cheapest of the measured kernels.
-inline double measured_best_us(const alcop_problem& p)
+// The estimated time of a product with a schedule, or of the cheapest measured kernel where that one
+// was not measured.
+inline double measured_sched_us(const alcop_problem& p, const alcop_sched& s)
 {
   double best = 1e30;
-  for (const MeasuredCost& m : kMeasured)
-    if (measured_applies(p, m)) best = std::min(best, measured_us(p, m));
+  for (const MeasuredCost& m : kMeasured) {
+    if (!measured_applies(p, m)) continue;
+    if (std::memcmp(&m.s, &s, sizeof(s)) == 0) return measured_us(p, m);
+    best = std::min(best, measured_us(p, m));
+  }
   return best;
 }
 

@@ -1,5 +1,7 @@
 """Products of operands that are not made of aligned chunks, in one launch (csrc/alcop_direct.hip.h): every
 layout at the edges of tiles and k-tiles, exactly.  Around the operands lie infinities, around C NaN."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -73,3 +75,18 @@ def test_on_the_gpu(dt, out, tA, tB):
         torch.cuda.synchronize()
         assert np.array_equal(C.double().cpu().numpy(), ref), size
         assert _untouched(Cbuf, C) and bool((ws == 255).all()), size
+
+
+@pytest.mark.parametrize("size,tA,tB", [((8, 7800001, 129), 0, 0), ((8, 7800001, 129), 1, 0), ((3000001, 20, 321), 1, 0)])
+def test_a_product_that_its_kernel_refuses_stays_refused(size, tA, tB):
+    # padded, K rounded up to whole k-tiles reaches 2^31 bytes: refused before anything is launched,
+    # also where the product without copies looks cheaper (addresses that nothing may touch)
+    M, N, K = size
+    A, B, C, ws = (ctypes.c_void_p(i << 40) for i in (1, 2, 3, 4))
+    L = emu.lib()
+    L.emu_reset(1, 0)
+    need = L.alcop_unaligned_workspace_bytes(1, M, N, K, al.F16)
+    assert need > 0
+    rc = L.alcop_bmm_unaligned(A, B, C, 1, M, N, K, M if tA else K, K if tB else N, N, 0, 0, 0, tA, tB, al.F16, al.F16,
+                               None, None, ws, need, None)
+    assert rc == al.ERR_SIZE and L.emu_error_count() == 0
