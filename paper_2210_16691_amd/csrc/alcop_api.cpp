@@ -1108,7 +1108,11 @@ struct Packer {
     g.cols = cols;
     g.s_batch = s_batch;
     g.s_row = s_row;
-    g.total = (batch - 1) * s_batch + (rows - 1) * s_row + cols;
+    g.total = (rows - 1) * s_row + cols;
+    if (s_batch == g.total) {
+      g.total *= batch;
+      g.s_total = s_batch;
+    }
   }
   double bytes() const
   {
@@ -1699,6 +1703,7 @@ int alcop_conv2d_igemm_unaligned(const void* x, const void* w, void* y, int N, i
       g.s_grp = (long)C * K;
       g.s_row = K;
       g.total = (long)R * S * C * K;
+      g.s_total = g.s_batch;
     }
   }
   rc = pk.launch(st);

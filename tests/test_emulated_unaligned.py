@@ -93,6 +93,19 @@ def test_batched_with_bias_relu_and_a_persistent_schedule():
         assert _untouched(Cbuf, C)
 
 
+def test_batch_entries_may_be_allocations_of_their_own():
+    # the memory between two entries of a batch need not exist
+    b, M, N, K = 3, 12, 13, 21
+    A0, B0 = wl.small_ints((b, M, K), "f16", 7303), wl.small_ints((b, K, N), "f16", 7304)
+    A, _ = _embed(A0, 0, 0, batch_pad=64, fill=float("inf"))
+    B, _ = _embed(B0, 1, 0, batch_pad=64, fill=float("inf"))
+    C = torch.full((b, M, N), float("nan"), dtype=torch.float32)
+    ws = _workspace(al.alcop_unaligned_workspace_bytes(b, M, N, K, al.F32))
+    errs = emu.call(al.alcop_bmm_unaligned, A, B, C, ws, reads=list(A) + list(B), writes=[C, ws])
+    assert not errs, errs[:4]
+    assert np.array_equal(C.double().numpy(), oracle.bmm(wl.bits(A0), wl.bits(B0), oracle.F16))
+
+
 def test_aligned_operands_give_the_same_bits_as_the_plain_entry_point():
     M, N, K = 72, 64, 96
     A = wl.uniform((M, K), "f16", 7401)
