@@ -1582,7 +1582,8 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
       d.ldc = (int)ldc;
       d.alpha = c.alpha;
       d.flags = (int)out | (c.act ? 4 : 0) | 8 | (c.c_any ? 16 : 0);
-      return launch_direct(d, in == ALCOP_BF16, transA, transB, st) == hipSuccess ? ALCOP_OK : ALCOP_ERR_LAUNCH;
+      const bool split = r.s.variant == 3;
+      return launch_direct(d, in == ALCOP_BF16, transA, transB, split, st) == hipSuccess ? ALCOP_OK : ALCOP_ERR_LAUNCH;
     }
   }
   rc = pk.launch(st);

@@ -19,7 +19,11 @@
 // a pipelined kernel (bf16): 507 x 1611 x 23 4.2 us and 7.0, 142 x 1816 x 229 4.9 and 7.8, 435 x 386 x 385 6.1 and
 // 8.5; long reductions lose (direct_pays).
 //
-// The k order of a tile is the one of the pipelined loops with the same tile: the same bits.
+// Sums.  In place of a pipelined kernel (P = 1) the k order of an element is that kernel's: the same bits.  In
+// place of one whose waves split K, eight partial sums per element, as there are eight (or four) waves: one sum
+// over all of K had two to three times the error of the copies' route (fp16, fp32 result, 201 x 99 x 501 4.0e-7
+// against 1.4e-7).  Products that get such a kernel have at most one tile per compute unit (measured_applies), so
+// that the 112 registers more displace no block.
 #pragma once
 #include "alcop_kernel.hip.h"
 
@@ -38,11 +42,11 @@ struct DirectArgs {
 };
 static_assert(sizeof(DirectArgs) == 64, "one line");
 
-// D: k-tiles in registers or on their way there.
-template <int DT_, int D_, int BL_, int AL_>
+// D: k-tiles in registers or on their way there.  P: partial sums per element of C.
+template <int DT_, int D_, int BL_, int AL_, int P_>
 struct DCfg {
   static constexpr int DT = DT_, BM = 64, BN = 64, BK = 64, WM = BM / 2, WN = BN / 2, BL = BL_, AL = AL_;
-  static constexpr int NT = 256, D = D_;
+  static constexpr int NT = 256, D = D_, P = P_;
   using OA = Opnd<AL ? LAY_MN : LAY_K, BM, WM, BK, NT>;
   using OB = Opnd<BL ? LAY_K : LAY_MN, BN, WN, BK, NT>;
   static constexpr int TM = WM / 32, TN = WN / 32;
@@ -50,6 +54,7 @@ struct DCfg {
   static constexpr int EPI_WAVE_BYTES = 32 * (WN * 4 + 16);
   static constexpr int LDS_BYTES = 2 * STAGE_BYTES > 4 * EPI_WAVE_BYTES ? 2 * STAGE_BYTES : 4 * EPI_WAVE_BYTES;
   static_assert(D % 2 == 0 && LDS_BYTES <= 64 * 1024, "stages");
+  static_assert(P == 1 || P == 8, "a k-tile has four steps, and an even and an odd stage");
 };
 
 // The upper elements of v moved down by n elements, zeros above; nothing is left from 8 on.
@@ -172,13 +177,15 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
   uint32_t rdA[OA::NRD], rdB[OB::NRD];
   setup_reader<OA, HW>(lane, wm, lds0, rdA);
   setup_reader<OB, HW>(lane, wn, lds0 + OA::BYTES, rdB);
-  f32x16 acc[TN][TM];
+  f32x16 part[C::P][TN][TM];
 #pragma unroll
-  for (int i = 0; i < TN; i++)
+  for (int q = 0; q < C::P; q++)
 #pragma unroll
-    for (int j = 0; j < TM; j++)
+    for (int i = 0; i < TN; i++)
 #pragma unroll
-      for (int v = 0; v < 16; v++) acc[i][j][v] = 0.f;
+      for (int j = 0; j < TM; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) part[q][i][j][v] = 0.f;
 
   constexpr int D = C::D;
   u32x4 ra[D][OA::NL], rb[D][OB::NL];
@@ -219,7 +226,10 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
 #pragma unroll
       for (int i = 0; i < TN; i++)
 #pragma unroll
-        for (int j = 0; j < TM; j++) acc[i][j] = HW::template mma<C::DT>(fb[i], fa[j], acc[i][j]);
+        for (int j = 0; j < TM; j++) {
+          f32x16& acc = part[(4 * set + ki) % C::P][i][j];
+          acc = HW::template mma<C::DT>(fb[i], fa[j], acc);
+        }
     }
   };
   // No way out of this loop but its end: the compiler would wait for all loads at the loop's head.  The
@@ -245,6 +255,17 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
     HW::block_barrier();
   }
 
+#pragma unroll
+  for (int d = C::P / 2; d > 0; d /= 2)
+#pragma unroll
+    for (int q = 0; q < d; q++)
+#pragma unroll
+      for (int i = 0; i < TN; i++)
+#pragma unroll
+        for (int j = 0; j < TM; j++)
+#pragma unroll
+          for (int v = 0; v < 16; v++) part[q][i][j][v] += part[q + d][i][j][v];
+
   // ---- epilogue: as in the pipelined loops; the bias one value at a time, from any address ----------
   const int m0 = tm * BM + wm * WM, n0 = tn * BN + wn * WN;
   const bool fused = p.alpha != 1.0f || p.bias != nullptr || p.act != 0;
@@ -268,7 +289,7 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
     constexpr int OBY = sizeof(OT), RS = WN * OBY + 16, LPR = WN * OBY / 16, RPI = 64 / LPR;
 #pragma unroll
     for (int j = 0; j < TM; j++) {
-      park_band<OT, RS, HW>(p, acc, j, mine, lane, fused, n0, bv);
+      park_band<OT, RS, HW>(p, part[0], j, mine, lane, fused, n0, bv);
 #pragma unroll
       for (int t = 0; t < 32 / RPI; t++) {
         const int r = t * RPI + lane / LPR, c16 = lane % LPR;

@@ -57,20 +57,22 @@ hipError_t launch_pack(const PackParams& p, unsigned blocks, hipStream_t st);
 // C from a dense image of it in the workspace.
 hipError_t launch_copy_out(const CopyOutParams& p, hipStream_t st);
 
-// Product of operands at any element address (alcop_direct.hip.h).
-hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, hipStream_t st);
+// Product of operands at any element address (alcop_direct.hip.h); split: in place of a kernel whose waves
+// split K.
+hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, bool split, hipStream_t st);
 // ... with a launcher of one configuration, LAUNCH<DCfg>::go(args, blocks, stream).  Two k-tiles ahead
 // where there are no more (K <= 128: 235 x 3780 x 59 4.2 us, 4.5 with four, which load the last again), else
 // four (26 x 41 x 2500 22.7 us with two, 15.8 with four).
 template <template <class> class LAUNCH>
-hipError_t dispatch_direct(const DirectArgs& a, int dt, bool transA, bool transB, hipStream_t st)
+hipError_t dispatch_direct(const DirectArgs& a, int dt, bool transA, bool transB, bool split, hipStream_t st)
 {
   const unsigned blocks = (unsigned)((a.M + 63) / 64) * (unsigned)((a.N + 63) / 64);
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
   auto depth = [&](auto cdt, auto cbl, auto cal) {
     constexpr int DT = decltype(cdt)::value, BL = decltype(cbl)::value, AL = decltype(cal)::value;
-    return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL>>::go(a, blocks, st);
+    if (split) return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 8>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 8>>::go(a, blocks, st);
+    return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 1>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 1>>::go(a, blocks, st);
   };
   auto layouts = [&](auto cdt) {
     if (transA) return transB ? depth(cdt, I1{}, I1{}) : depth(cdt, I0{}, I1{});

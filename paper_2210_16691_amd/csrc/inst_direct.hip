@@ -1,4 +1,5 @@
-// Products of operands at any element address: both types, every operand layout, two pipeline depths.
+// Products of operands at any element address: both types, every operand layout, two pipeline depths, one or eight
+// partial sums.
 #include "alcop_gfx950.hip.h"
 #include "alcop_registry.h"
 namespace alcop {
@@ -13,9 +14,9 @@ struct Launch {
 };
 }  // namespace
 
-hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, hipStream_t st)
+hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, bool split, hipStream_t st)
 {
-  return dispatch_direct<Launch>(a, dt, transA, transB, st);
+  return dispatch_direct<Launch>(a, dt, transA, transB, split, st);
 }
 
 }  // namespace alcop

@@ -343,9 +343,9 @@ struct EmulatedDirect {
     return hipSuccess;
   }
 };
-hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, hipStream_t st)
+hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, bool split, hipStream_t st)
 {
-  return dispatch_direct<EmulatedDirect>(a, dt, transA, transB, st);
+  return dispatch_direct<EmulatedDirect>(a, dt, transA, transB, split, st);
 }
 static void copy_out_entry(const void* p) { alcop_copy_out<emu::Emu>(*(const CopyOutParams*)p); }
 hipError_t launch_copy_out(const CopyOutParams& p, hipStream_t)

@@ -77,6 +77,64 @@ def test_on_the_gpu(dt, out, tA, tB):
         assert _untouched(Cbuf, C) and bool((ws == 255).all()), size
 
 
+def _both_routes(dt, size, tA, tB, dev, call, auto):
+    """The product without copies and with them, each with its relative error against 64 bits, and whether the
+    kernel of the copies' route splits K among its waves (fp32 results)."""
+    M, N, K = size
+    A0, B0 = wl.uniform((K, M) if tA else (M, K), dt, 70 + M), wl.uniform((N, K) if tB else (K, N), dt, 80 + N)
+    ref = (A0.double().T if tA else A0.double()) @ (B0.double().T if tB else B0.double())
+    A, B = _embed(A0, 1, 0)[1].to(dev)[1:].view(A0.shape), _embed(B0, 1, 0)[1].to(dev)[1:].view(B0.shape)
+    ws = torch.empty(al.alcop_unaligned_workspace_bytes(1, M, N, K, al.F32), dtype=torch.uint8, device=dev)
+    up = lambda n: (n + 7) // 8 * 8
+    padded = auto(al.problem(al.OP_GEMM, up(M) if tA else M, up(N), up(K), ADT[dt], al.F32, transB=bool(tB),
+                             transA=bool(tA)))
+    out = []
+    for sched in (None, padded):
+        C = torch.empty(M, N, dtype=torch.float32, device=dev)
+        ws.fill_(255)
+        call(al.alcop_bmm_unaligned, A, B, C, ws, sched=sched, transA=bool(tA), transB=bool(tB))
+        C = C.cpu()
+        assert bool((ws == 255).all()) == (sched is None), size        # the route
+        out.append((C, ((C.double() - ref).norm() / ref.norm()).item()))
+    return out[0], out[1], padded.variant == 3
+
+
+def _no_more_error(dt, sizes, tA, tB, dev, call, auto):
+    split = 0
+    for size in sizes:
+        (C, direct), (D, copies), splits = _both_routes(dt, size, tA, tB, dev, call, auto)
+        if splits:
+            split += 1                        # other orders of the sum: the errors' norms differ a little
+            assert direct <= 1.05 * copies, (size, direct, copies)
+        else:
+            assert torch.equal(C, D), size    # the same order
+    return split
+
+
+# most of these get a kernel that splits K among four or eight waves, where copied; all get the direct kernel
+ROUTES = [(142, 181, 229), (100, 203, 449), (201, 99, 501), (260, 131, 395), (67, 66, 65), (435, 386, 385)]
+
+
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+def test_no_more_error_than_with_copies_on_the_cpu_model(tA, tB):
+    def call(f, A, B, C, ws, **kw):
+        errs = emu.call(f, A, B, C, ws, reads=[A, B], writes=[C, ws], **kw)
+        assert not errs, errs[:3]
+
+    def auto(prob):
+        with emu._swapped():
+            return al.alcop_sched_auto(prob)
+    split = _no_more_error("f16", ROUTES, tA, tB, "cpu", call, auto)
+    assert split >= (0 if tA and not tB else 4)      # the model holds no such kernel for this layout
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dt", ["f16", "bf16"])
+def test_no_more_error_than_with_copies_on_the_gpu(dt, tA, tB):
+    assert _no_more_error(dt, ROUTES, tA, tB, "cuda:0", lambda f, *a, **kw: f(*a, **kw), al.alcop_sched_auto) >= 4
+
+
 @pytest.mark.parametrize("size,tA,tB", [((8, 7800001, 129), 0, 0), ((8, 7800001, 129), 1, 0), ((3000001, 20, 321), 1, 0)])
 def test_a_product_that_its_kernel_refuses_stays_refused(size, tA, tB):
     # padded, K rounded up to whole k-tiles reaches 2^31 bytes: refused before anything is launched,
