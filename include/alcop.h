@@ -524,8 +524,8 @@ int alcop_time(const alcop_problem* prob /* host */, const void* A, const void* 
 /* Static string for a status code. */
 /*
  * Optional: does now, on the current device, what the first call of each entry point would do
- * besides launching (opting every kernel in to its LDS size, looking up the device array of
- * alcop_gemm_splitk_static, reading the compute-unit count).  After it, a first call is as cheap
+ * besides launching (opting every kernel in to its LDS size, loading those of the unaligned entry
+ * points, looking up the device array of alcop_gemm_splitk_static, reading the compute-unit count).  After it, a first call is as cheap
  * as any other and may be recorded into a HIP graph without an eager call before the capture.
  * Launches nothing, allocates nothing.  Returns ALCOP_OK or ALCOP_ERR_LAUNCH (no usable device).
  */

@@ -1467,10 +1467,12 @@ int alcop_conv2d_igemm_fused(const void* x, const void* w, void* y, int N, int H
 
 int alcop_init(void)
 {
-  // everything a first call would do besides launching: the LDS opt-in of every kernel, the
-  // address of the allocation-free entry point's device array, the compute-unit count
+  // everything a first call would do besides launching: the LDS opt-in of every kernel, loading
+  // those of the unaligned entry points, the address of the allocation-free entry point's device
+  // array, the compute-unit count
   for (const KernelEntry& e : registry())
     if (e.prepare && e.prepare() != hipSuccess) return ALCOP_ERR_LAUNCH;
+  if (prepare_direct() != hipSuccess || prepare_copies() != hipSuccess) return ALCOP_ERR_LAUNCH;
   void* scratch = nullptr;
   size_t bytes = 0;
   if (splitk_scratch(&scratch, &bytes) != hipSuccess) return ALCOP_ERR_LAUNCH;

@@ -56,10 +56,14 @@ hipError_t launch_splitk_reduce(const ReduceParams& p, dim3 grid, hipStream_t st
 hipError_t launch_pack(const PackParams& p, unsigned blocks, hipStream_t st);
 // C from a dense image of it in the workspace.
 hipError_t launch_copy_out(const CopyOutParams& p, hipStream_t st);
+// Loads both kernels, so that alcop_init can do it ahead of time.
+hipError_t prepare_copies();
 
 // Product of operands at any element address (alcop_direct.hip.h); split: in place of a kernel whose waves
 // split K.
 hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, bool split, hipStream_t st);
+// Loads all of them.
+hipError_t prepare_direct();
 // ... with a launcher of one configuration, LAUNCH<DCfg>::go(args, blocks, stream).  Two k-tiles ahead
 // where there are no more (K <= 128: 235 x 3780 x 59 4.2 us, 4.5 with four, which load the last again), else
 // four (26 x 41 x 2500 22.7 us with two, 15.8 with four).
@@ -79,6 +83,19 @@ hipError_t dispatch_direct(const DirectArgs& a, int dt, bool transA, bool transB
     return transB ? depth(cdt, I1{}, I0{}) : depth(cdt, I0{}, I0{});
   };
   return dt ? layouts(I1{}) : layouts(I0{});
+}
+// LAUNCH<DCfg>::go for every configuration; the arguments are none of a call's.
+template <template <class> class LAUNCH>
+hipError_t every_direct()
+{
+  for (int i = 0; i < 32; i++) {
+    DirectArgs a = {};
+    a.M = a.N = 1;
+    a.K = i & 1 ? 256 : 128;
+    const hipError_t rc = dispatch_direct<LAUNCH>(a, (i >> 1) & 1, i & 4, i & 8, i & 16, nullptr);
+    if (rc != hipSuccess) return rc;
+  }
+  return hipSuccess;
 }
 
 // Device address and size of the library's own scratch array on the current device (set up on

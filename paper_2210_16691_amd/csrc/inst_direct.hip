@@ -12,11 +12,21 @@ struct Launch {
     return hipGetLastError();
   }
 };
+template <class C>
+struct Load {
+  static hipError_t go(const DirectArgs&, unsigned, hipStream_t)
+  {
+    hipFuncAttributes at;
+    return hipFuncGetAttributes(&at, (const void*)alcop_direct<C, Gfx950>);
+  }
+};
 }  // namespace
 
 hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, bool split, hipStream_t st)
 {
   return dispatch_direct<Launch>(a, dt, transA, transB, split, st);
 }
+
+hipError_t prepare_direct() { return every_direct<Load>(); }
 
 }  // namespace alcop

@@ -15,4 +15,11 @@ hipError_t launch_copy_out(const CopyOutParams& p, hipStream_t st)
   return hipGetLastError();
 }
 
+hipError_t prepare_copies()
+{
+  hipFuncAttributes at;
+  const hipError_t rc = hipFuncGetAttributes(&at, (const void*)alcop_pack<Gfx950>);
+  return rc != hipSuccess ? rc : hipFuncGetAttributes(&at, (const void*)alcop_copy_out<Gfx950>);
+}
+
 }  // namespace alcop

@@ -6,6 +6,8 @@
 // 8-wave blocks, one to four stages, single- and multi-level, fused and unfused.
 #include <hip/hip_runtime.h>
 
+#include <set>
+
 #include "emu_hw.h"
 #include "alcop_registry.h"
 
@@ -347,7 +349,25 @@ hipError_t launch_direct(const DirectArgs& a, int dt, bool transA, bool transB, 
 {
   return dispatch_direct<EmulatedDirect>(a, dt, transA, transB, split, st);
 }
+// kernels that alcop_init has loaded
+static std::set<const void*> g_loaded;
+template <class C>
+struct CountedDirect {
+  static hipError_t go(const DirectArgs&, unsigned, hipStream_t)
+  {
+    g_loaded.insert((const void*)&EmulatedDirect<C>::entry);
+    return hipSuccess;
+  }
+};
+hipError_t prepare_direct() { return every_direct<CountedDirect>(); }
 static void copy_out_entry(const void* p) { alcop_copy_out<emu::Emu>(*(const CopyOutParams*)p); }
+hipError_t prepare_copies()
+{
+  g_loaded.insert((const void*)&pack_entry);
+  g_loaded.insert((const void*)&copy_out_entry);
+  return hipSuccess;
+}
+extern "C" int emu_loaded() { return (int)g_loaded.size(); }
 hipError_t launch_copy_out(const CopyOutParams& p, hipStream_t)
 {
   emu::run_grid(&copy_out_entry, &p, PACK_THREADS, 0, copy_out_blocks(p), 1, 1);

@@ -135,6 +135,53 @@ def test_no_more_error_than_with_copies_on_the_gpu(dt, tA, tB):
     assert _no_more_error(dt, ROUTES, tA, tB, "cuda:0", lambda f, *a, **kw: f(*a, **kw), al.alcop_sched_auto) >= 4
 
 
+def test_init_loads_the_kernels_of_unaligned_calls():
+    L = emu.lib()
+    assert L.alcop_init() == al.OK
+    assert L.emu_loaded() == 32 + 2             # two types, four layouts, two depths, one or eight sums; the copies
+
+
+@pytest.mark.gpu
+def test_captured_after_alcop_init():
+    al.alcop_init()
+    small, odd = (142, 181, 229), (1021, 1531, 767)           # without copies, with them
+    make = lambda size, seed: (wl.uniform(size[::2], "bf16", seed).to("cuda:0"), wl.uniform(size[:0:-1], "bf16", seed + 1).to("cuda:0"))
+    ops = [make(small, 90), make(odd, 92)]
+    outs = [torch.empty(M, N, dtype=torch.bfloat16, device="cuda:0") for M, N, _ in (small, odd)]
+    ws = [torch.empty(al.alcop_unaligned_workspace_bytes(1, *s, al.BF16), dtype=torch.uint8, device="cuda:0")
+          for s in (small, odd)]
+    x, w = wl.uniform((2, 30, 31, 3), "bf16", 94).to("cuda:0"), wl.uniform((3, 3, 3, 21), "bf16", 95).to("cuda:0")
+    outs.append(torch.empty(2, 30, 31, 21, dtype=torch.bfloat16, device="cuda:0"))
+    ws.append(torch.empty(al.alcop_conv2d_unaligned_workspace_bytes(2, 30, 31, 3, 21, 3, 3, (1, 1), (1, 1), (1, 1), al.BF16),
+                          dtype=torch.uint8, device="cuda:0"))
+
+    def work(stream):
+        for (A, B), C, s in zip(ops, outs, ws):
+            al.alcop_bmm_unaligned(A, B, C, s, stream=stream)
+        al.alcop_conv2d_igemm_unaligned(x, w, outs[2], ws[2], (1, 1), (1, 1), stream=stream)
+
+    torch.cuda.synchronize()
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(graph, stream=side):
+            work(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    for rep in range(4):
+        for (A, B), size in zip(ops, (small, odd)):
+            for t, new in zip((A, B), make(size, 100 + rep)):
+                t.copy_(new)
+        x.copy_(wl.uniform((2, 30, 31, 3), "bf16", 110 + rep).to("cuda:0"))
+        work(torch.cuda.current_stream())
+        torch.cuda.synchronize()
+        want = [C.clone() for C in outs]
+        for C in outs:
+            C.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for C, ref in zip(outs, want):
+            assert torch.equal(C.view(torch.int16), ref.view(torch.int16)), rep
+
+
 @pytest.mark.parametrize("size,tA,tB", [((8, 7800001, 129), 0, 0), ((8, 7800001, 129), 1, 0), ((3000001, 20, 321), 1, 0)])
 def test_a_product_that_its_kernel_refuses_stays_refused(size, tA, tB):
     # padded, K rounded up to whole k-tiles reaches 2^31 bytes: refused before anything is launched,
