@@ -226,6 +226,7 @@ std::mutex g_cache_mu;
 struct CacheEntry {
   alcop_sched s;
   bool tuned;      // by alcop_tune or a cache file; else the library's pick
+  double us = 0;   // products of matrices: the estimated time of that pick
 };
 std::map<CacheKey, CacheEntry> g_cache;    // problem -> chosen schedule
 
@@ -338,24 +339,26 @@ bool tuned_sched(const alcop_problem& p, alcop_sched* out)
   return true;
 }
 
-// What a NULL / zero schedule resolves to: the tuning cache, else the library's pick (*picked).
-int auto_sched(const alcop_problem& p, alcop_sched* out, bool* picked = nullptr)
+// What a NULL / zero schedule resolves to: the tuning cache, else the library's pick, whose estimated time is
+// *us (negative where a schedule was tuned).
+int auto_sched(const alcop_problem& p, alcop_sched* out, double* us = nullptr)
 {
   load_env_cache();
-  if (picked) *picked = true;
   {
     std::lock_guard<std::mutex> lk(g_cache_mu);
     auto it = g_cache.find(key_of(p));
     if (it != g_cache.end()) {
       *out = it->second.s;
-      if (picked) *picked = !it->second.tuned;
+      if (us) *us = it->second.tuned ? -1.0 : it->second.us;
       return ALCOP_OK;
     }
   }
   const int rc = library_pick(p, out);
   if (rc) return rc;
+  const double est = measured_sched_us(p, *out);
+  if (us) *us = est;
   std::lock_guard<std::mutex> lk(g_cache_mu);
-  g_cache.emplace(key_of(p), CacheEntry{*out, false});
+  g_cache.emplace(key_of(p), CacheEntry{*out, false, est});
   return ALCOP_OK;
 }
 
@@ -722,7 +725,7 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
 struct Resolved {
   alcop_sched s;
   const KernelEntry* e = nullptr;
-  bool picked = false;         // products of matrices: by the library, without a tuned schedule
+  double us = -1.0;            // products of matrices: estimated time of the library's pick; negative if it is not that
 };
 int resolve(const Call& c, const alcop_sched* sched, Resolved* out)
 {
@@ -732,7 +735,7 @@ int resolve(const Call& c, const alcop_sched* sched, Resolved* out)
   alcop_sched& s = out->s;
   const bool automatic = !sched || sched->bm == 0;
   if (automatic) {
-    rc = c.op == ALCOP_OP_CONV2D ? auto_conv_sched(c, prob, &s) : auto_sched(prob, &s, &out->picked);
+    rc = c.op == ALCOP_OP_CONV2D ? auto_conv_sched(c, prob, &s) : auto_sched(prob, &s, &out->us);
     if (rc) return rc;
   } else {
     s = *sched;
@@ -1565,12 +1568,11 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
   // be paid back.  Rows hold eight elements and are less than 2^23 apart (32-bit offsets within a tile);
   // nothing that is read is overwritten by the result.
   const int min_row = std::min(transA ? M : K, transB ? K : N);
-  if (pk.p.nseg > 0 && batch == 1 && !far && r.picked && min_row >= 8 &&
+  if (pk.p.nseg > 0 && batch == 1 && !far && r.us >= 0.0 && min_row >= 8 &&
       std::max(lda, ldb) < (1L << 23) && !meets(A, bytes(2, lda, strideA, a_rows, a_cols), C, c_bytes) &&
       !meets(B, bytes(2, ldb, strideB, b_rows, b_cols), C, c_bytes) &&
       !(ep && ep->bias && meets(ep->bias, 4.0 * N, C, c_bytes))) {
-    const double us = measured_sched_us(problem_of(c), r.s);
-    if (direct_pays(M, N, K, us, pk.bytes())) {
+    if (direct_pays(M, N, K, r.us, pk.bytes())) {
       DirectArgs d;
       d.A = A;
       d.B = B;
@@ -1995,8 +1997,9 @@ int load_cache_file(const char* path)
     // own geometry
     const bool tuned = std::strstr(line, " auto") == nullptr;
     std::lock_guard<std::mutex> lk(g_cache_mu);
-    CacheEntry& entry = g_cache.emplace(key_of(p), CacheEntry{s, false}).first->second;
-    if (tuned || !entry.tuned) entry = CacheEntry{s, tuned};
+    const CacheEntry read{s, tuned, tuned ? 0.0 : measured_sched_us(p, s)};
+    CacheEntry& entry = g_cache.emplace(key_of(p), read).first->second;
+    if (tuned || !entry.tuned) entry = read;
     n++;
   }
   std::fclose(f);

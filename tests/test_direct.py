@@ -128,6 +128,16 @@ def test_no_more_error_than_with_copies_on_the_cpu_model(tA, tB):
     assert split >= (0 if tA and not tB else 4)      # the model holds no such kernel for this layout
 
 
+def test_a_pick_read_from_a_file_takes_the_same_route(tmp_path):
+    A, B, C, Cbuf, bias, ws, ref = _case("f16", "f32", (150, 181, 229), 0, 0, "cpu")
+    for step in ("picked", "read"):            # the entry that is read replaces the one that was picked
+        assert not emu.call(al.alcop_bmm_unaligned, A, B, C, ws, 0.5, bias, 1, reads=[A, B, bias], writes=[C, ws])
+        assert bool((ws == 255).all()), step
+        with emu._swapped():
+            assert al.alcop_cache_save(str(tmp_path / "picks")) >= 1
+            assert al.alcop_cache_load(str(tmp_path / "picks")) >= 1
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("dt", ["f16", "bf16"])
