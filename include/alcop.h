@@ -239,6 +239,15 @@ int alcop_conv2d_igemm_dilated(const void* x, const void* w, void* y, int N, int
  * extra k terms are exact zeros, so every valid element equals what an aligned call on the same
  * values returns) and store the valid M x N part straight to C; bytes of C outside the valid
  * elements (row padding) are not touched.  One small copy kernel besides the product.
+ *
+ * Without a schedule (NULL, none tuned), a single product (batch 1) of moderate size whose operands
+ * share no memory with C may instead run in one launch that loads the operands where they lie.  It
+ * leaves the workspace alone (which is asked for all the same).  Its elements are what an aligned call
+ * returns, bit for bit, unless that call is given a kernel whose waves split K (variant 3): then they
+ * are sums of the same products in another order, of no larger error.
+ *
+ * Of an operand, the memory between its rows may be read as well (up to 14 bytes behind a row's end, never
+ * behind the last row of a batch entry); what it holds does not matter.
  *   A, B, C: DEVICE pointers aligned to their element size; lda, ldb, ldc, strides in elements,
  *     any value allowed by the shape (lda >= K or M, ...); batch = 1 with strides 0 is a GEMM.
  *   ep: host, may be NULL; ep->bias: DEVICE pointer to N fp32 values, 4-byte aligned.
@@ -246,7 +255,7 @@ int alcop_conv2d_igemm_dilated(const void* x, const void* w, void* y, int N, int
  *     that problem, else the library's pick.
  *   workspace: DEVICE memory, 16-byte aligned, at least alcop_unaligned_workspace_bytes(batch, M, N,
  *     K, out) bytes (that function returns 0 for arguments no call accepts); owned by the caller,
- *     overwritten by the call.  Calls that share a workspace must be ordered on one stream.
+ *     overwritten by the call, if it copies.  Calls that share a workspace must be ordered on one stream.
  * Errors as for alcop_bmm; ALCOP_ERR_SIZE also if the workspace is too small.
  */
 size_t alcop_unaligned_workspace_bytes(int batch, int M, int N, int K, alcop_dtype out);

@@ -501,7 +501,8 @@ def alcop_bmm_unaligned(A, B, C, workspace, alpha=1.0, bias=None, act=0, sched=N
                         transB=False, stream=None):
     """C = act(alpha * A.B + bias[j]) for operands of any extent and element-aligned placement
     (2-D: a GEMM; 3-D: batched); they are padded into `workspace` (a CUDA byte tensor of at least
-    alcop_unaligned_workspace_bytes(...) bytes) and multiplied there."""
+    alcop_unaligned_workspace_bytes(...) bytes) and multiplied there, or, single products of moderate
+    size without a schedule, multiplied where they lie."""
     if _marshal_lib is _lib is not None:
         rc = _marshal.mm_any(A, B, C, workspace, alpha, bias, act, sched, transA, transB, stream)
         if rc is not None:

@@ -8,9 +8,12 @@
 //
 // Edges.  A chunk that would reach past the end of its row starts earlier, where the row's last eight
 // elements are, and is shifted down by what it starts early; zeros come in at the top.  A row past the
-// last k is the last one, shifted out whole.  So nothing is read that is not of the operand (rows hold
-// eight elements at least), the terms past K are zero times zero, and the shifts are behind a branch
-// that only blocks at an edge and the last k-tile take.
+// last k is the last one, shifted out whole.  So the terms past K are zero times zero, and the shifts are behind a
+// branch that only blocks at an edge and the last k-tile take (rows hold eight elements at least).
+//   Operands that run along m or n do so in the last k-tile only.  Before it, a chunk at the edge reads up to
+// seven elements past its row's end, what lies between two rows or the next row, which the operand has since the
+// row is not the last; whatever they hold goes into accumulators of rows >= M or columns >= N, and those are not
+// stored.  Nothing is read behind an operand's last row.
 //
 // What bounds it: misaligned loads, 24 bytes per clock and compute unit however many are in flight (aligned
 // direct-to-LDS loads 40 to 50): 0.3 us per k-tile of 16 KB, which is also what a block alone on its unit takes.
@@ -19,11 +22,11 @@
 // a pipelined kernel (bf16): 507 x 1611 x 23 4.2 us and 7.0, 142 x 1816 x 229 4.9 and 7.8, 435 x 386 x 385 6.1 and
 // 8.5; long reductions lose (direct_pays).
 //
-// Sums.  In place of a pipelined kernel (P = 1) the k order of an element is that kernel's: the same bits.  In
-// place of one whose waves split K, eight partial sums per element, as there are eight (or four) waves: one sum
-// over all of K had two to three times the error of the copies' route (fp16, fp32 result, 201 x 99 x 501 4.0e-7
-// against 1.4e-7).  Products that get such a kernel have at most one tile per compute unit (measured_applies), so
-// that the 112 registers more displace no block.
+// Sums.  In place of a pipelined kernel the k order of an element is that kernel's: the same bits.  In place of one
+// whose waves split K (PARTS), each k-tile is a sum of its own and D chains of them are added up at the end: one
+// sum over all of K had two to three times the error of the copies' route (fp16, fp32 result, 201 x 99 x 501 4.0e-7
+// against 1.4e-7), this has no more.  Eight accumulators per element instead, 112 registers more, cost 0.6 us
+// (cleared before the first loads, read and added after the last).
 #pragma once
 #include "alcop_kernel.hip.h"
 
@@ -42,11 +45,11 @@ struct DirectArgs {
 };
 static_assert(sizeof(DirectArgs) == 64, "one line");
 
-// D: k-tiles in registers or on their way there.  P: partial sums per element of C.
-template <int DT_, int D_, int BL_, int AL_, int P_>
+// D: k-tiles in registers or on their way there.  PARTS: a sum per k-tile.
+template <int DT_, int D_, int BL_, int AL_, int PARTS_>
 struct DCfg {
   static constexpr int DT = DT_, BM = 64, BN = 64, BK = 64, WM = BM / 2, WN = BN / 2, BL = BL_, AL = AL_;
-  static constexpr int NT = 256, D = D_, P = P_;
+  static constexpr int NT = 256, D = D_, PARTS = PARTS_;
   using OA = Opnd<AL ? LAY_MN : LAY_K, BM, WM, BK, NT>;
   using OB = Opnd<BL ? LAY_K : LAY_MN, BN, WN, BK, NT>;
   static constexpr int TM = WM / 32, TN = WN / 32;
@@ -54,7 +57,6 @@ struct DCfg {
   static constexpr int EPI_WAVE_BYTES = 32 * (WN * 4 + 16);
   static constexpr int LDS_BYTES = 2 * STAGE_BYTES > 4 * EPI_WAVE_BYTES ? 2 * STAGE_BYTES : 4 * EPI_WAVE_BYTES;
   static_assert(D % 2 == 0 && LDS_BYTES <= 64 * 1024, "stages");
-  static_assert(P == 1 || P == 8, "a k-tile has four steps, and an even and an odd stage");
 };
 
 // The upper elements of v moved down by n elements, zeros above; nothing is left from 8 on.
@@ -177,15 +179,16 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
   uint32_t rdA[OA::NRD], rdB[OB::NRD];
   setup_reader<OA, HW>(lane, wm, lds0, rdA);
   setup_reader<OB, HW>(lane, wn, lds0 + OA::BYTES, rdB);
-  f32x16 part[C::P][TN][TM];
+  constexpr int CHAINS = C::PARTS ? C::D : 1;
+  f32x16 sum[CHAINS][TN][TM], zero;
 #pragma unroll
-  for (int q = 0; q < C::P; q++)
+  for (int v = 0; v < 16; v++) zero[v] = 0.f;
+#pragma unroll
+  for (int q = 0; q < CHAINS; q++)
 #pragma unroll
     for (int i = 0; i < TN; i++)
 #pragma unroll
-      for (int j = 0; j < TM; j++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) part[q][i][j][v] = 0.f;
+      for (int j = 0; j < TM; j++) sum[q][i][j] = zero;
 
   constexpr int D = C::D;
   u32x4 ra[D][OA::NL], rb[D][OB::NL];
@@ -216,6 +219,7 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
     for (int i = 0; i < OA::NRD; i++) curA[i] = rdA[i] + (uint32_t)((set & 1) * C::STAGE_BYTES);
 #pragma unroll
     for (int i = 0; i < OB::NRD; i++) curB[i] = rdB[i] + (uint32_t)((set & 1) * C::STAGE_BYTES);
+    f32x16 part[TN][TM];
 #pragma unroll
     for (int ki = 0; ki < 4; ki++) {
       u32x4 fa[TM], fb[TN];
@@ -227,9 +231,17 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
       for (int i = 0; i < TN; i++)
 #pragma unroll
         for (int j = 0; j < TM; j++) {
-          f32x16& acc = part[(4 * set + ki) % C::P][i][j];
-          acc = HW::template mma<C::DT>(fb[i], fa[j], acc);
+          f32x16& acc = C::PARTS ? part[i][j] : sum[0][i][j];
+          acc = HW::template mma<C::DT>(fb[i], fa[j], C::PARTS && ki == 0 ? zero : acc);
         }
+    }
+    if constexpr (C::PARTS) {
+#pragma unroll
+      for (int i = 0; i < TN; i++)
+#pragma unroll
+        for (int j = 0; j < TM; j++)
+#pragma unroll
+          for (int v = 0; v < 16; v++) sum[set][i][j][v] += part[i][j][v];
     }
   };
   // No way out of this loop but its end: the compiler would wait for all loads at the loop's head.  The
@@ -256,7 +268,7 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
   }
 
 #pragma unroll
-  for (int d = C::P / 2; d > 0; d /= 2)
+  for (int d = CHAINS / 2; d > 0; d /= 2)
 #pragma unroll
     for (int q = 0; q < d; q++)
 #pragma unroll
@@ -264,7 +276,7 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
 #pragma unroll
         for (int j = 0; j < TM; j++)
 #pragma unroll
-          for (int v = 0; v < 16; v++) part[q][i][j][v] += part[q + d][i][j][v];
+          for (int v = 0; v < 16; v++) sum[q][i][j][v] += sum[q + d][i][j][v];
 
   // ---- epilogue: as in the pipelined loops; the bias one value at a time, from any address ----------
   const int m0 = tm * BM + wm * WM, n0 = tn * BN + wn * WN;
@@ -289,7 +301,7 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
     constexpr int OBY = sizeof(OT), RS = WN * OBY + 16, LPR = WN * OBY / 16, RPI = 64 / LPR;
 #pragma unroll
     for (int j = 0; j < TM; j++) {
-      park_band<OT, RS, HW>(p, part[0], j, mine, lane, fused, n0, bv);
+      park_band<OT, RS, HW>(p, sum[0], j, mine, lane, fused, n0, bv);
 #pragma unroll
       for (int t = 0; t < 32 / RPI; t++) {
         const int r = t * RPI + lane / LPR, c16 = lane % LPR;

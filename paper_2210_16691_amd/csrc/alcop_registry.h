@@ -75,8 +75,8 @@ hipError_t dispatch_direct(const DirectArgs& a, int dt, bool transA, bool transB
   using I1 = std::integral_constant<int, 1>;
   auto depth = [&](auto cdt, auto cbl, auto cal) {
     constexpr int DT = decltype(cdt)::value, BL = decltype(cbl)::value, AL = decltype(cal)::value;
-    if (split) return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 8>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 8>>::go(a, blocks, st);
-    return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 1>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 1>>::go(a, blocks, st);
+    if (split) return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 1>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 1>>::go(a, blocks, st);
+    return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 0>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 0>>::go(a, blocks, st);
   };
   auto layouts = [&](auto cdt) {
     if (transA) return transB ? depth(cdt, I1{}, I1{}) : depth(cdt, I0{}, I1{});

@@ -1,5 +1,5 @@
-// Products of operands at any element address: both types, every operand layout, two pipeline depths, one or eight
-// partial sums.
+// Products of operands at any element address: both types, every operand layout, two pipeline depths, one sum or
+// one per k-tile.
 #include "alcop_gfx950.hip.h"
 #include "alcop_registry.h"
 namespace alcop {
