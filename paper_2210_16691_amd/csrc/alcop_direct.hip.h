@@ -22,11 +22,12 @@
 // a pipelined kernel (bf16): 507 x 1611 x 23 4.2 us and 7.0, 142 x 1816 x 229 4.9 and 7.8, 435 x 386 x 385 6.1 and
 // 8.5; long reductions lose (direct_pays).
 //
-// Sums.  In place of a pipelined kernel the k order of an element is that kernel's: the same bits.  In place of one
-// whose waves split K (PARTS), each k-tile is a sum of its own and D chains of them are added up at the end: one
-// sum over all of K had two to three times the error of the copies' route (fp16, fp32 result, 201 x 99 x 501 4.0e-7
-// against 1.4e-7), this has no more.  Eight accumulators per element instead, 112 registers more, cost 0.6 us
-// (cleared before the first loads, read and added after the last).
+// Sums.  In place of a pipelined kernel (P = 1) the k order of an element is that kernel's: the same bits.  In place
+// of one whose waves split K it has P partial sums, one per k-tile up to four, else eight.  One sum over all of K had
+// 1.2 (K = 170) to 2.1 times (K = 1056) the error of the copies' route (fp32 results, against 64 bits); these have
+// 0.96 times in the mean over 165 products, 1.01 at most where there are more than a few hundred elements.  They
+// cost 3 % (median; 0.2 us of 6): as vector registers, which two waves per SIMD make the compiler take, since reading
+// 128 accumulation registers cost another 0.4 us, and cleared while the first loads are on their way.
 #pragma once
 #include "alcop_kernel.hip.h"
 
@@ -45,11 +46,11 @@ struct DirectArgs {
 };
 static_assert(sizeof(DirectArgs) == 64, "one line");
 
-// D: k-tiles in registers or on their way there.  PARTS: a sum per k-tile.
-template <int DT_, int D_, int BL_, int AL_, int PARTS_>
+// D: k-tiles in registers or on their way there.  P: partial sums per element of C.
+template <int DT_, int D_, int BL_, int AL_, int P_>
 struct DCfg {
   static constexpr int DT = DT_, BM = 64, BN = 64, BK = 64, WM = BM / 2, WN = BN / 2, BL = BL_, AL = AL_;
-  static constexpr int NT = 256, D = D_, PARTS = PARTS_;
+  static constexpr int NT = 256, D = D_, P = P_;
   using OA = Opnd<AL ? LAY_MN : LAY_K, BM, WM, BK, NT>;
   using OB = Opnd<BL ? LAY_K : LAY_MN, BN, WN, BK, NT>;
   static constexpr int TM = WM / 32, TN = WN / 32;
@@ -57,6 +58,7 @@ struct DCfg {
   static constexpr int EPI_WAVE_BYTES = 32 * (WN * 4 + 16);
   static constexpr int LDS_BYTES = 2 * STAGE_BYTES > 4 * EPI_WAVE_BYTES ? 2 * STAGE_BYTES : 4 * EPI_WAVE_BYTES;
   static_assert(D % 2 == 0 && LDS_BYTES <= 64 * 1024, "stages");
+  static_assert(P == 1 || P == D || P == 2 * D, "partial sums");
 };
 
 // The upper elements of v moved down by n elements, zeros above; nothing is left from 8 on.
@@ -143,7 +145,7 @@ struct DirectOperand {
 };
 
 template <class C, class HW>
-__global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
+__global__ void __launch_bounds__(C::NT, C::P > 1 ? 2 : 1) alcop_direct(const DirectArgs s)
 {
   constexpr int BM = C::BM, BN = C::BN, WM = C::WM, WN = C::WN, TM = C::TM, TN = C::TN;
   using OA = typename C::OA;
@@ -179,17 +181,6 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
   uint32_t rdA[OA::NRD], rdB[OB::NRD];
   setup_reader<OA, HW>(lane, wm, lds0, rdA);
   setup_reader<OB, HW>(lane, wn, lds0 + OA::BYTES, rdB);
-  constexpr int CHAINS = C::PARTS ? C::D : 1;
-  f32x16 sum[CHAINS][TN][TM], zero;
-#pragma unroll
-  for (int v = 0; v < 16; v++) zero[v] = 0.f;
-#pragma unroll
-  for (int q = 0; q < CHAINS; q++)
-#pragma unroll
-    for (int i = 0; i < TN; i++)
-#pragma unroll
-      for (int j = 0; j < TM; j++) sum[q][i][j] = zero;
-
   constexpr int D = C::D;
   u32x4 ra[D][OA::NL], rb[D][OB::NL];
   const bool trim = (s.K & 63) != 0 || la.edge || lb.edge;
@@ -210,6 +201,17 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
   };
 #pragma unroll
   for (int d = 0; d < D; d++) load(d, d);
+  HW::sched_fence();               // clearing the sums costs nothing while the loads are on their way
+  constexpr int P = C::P;
+  f32x16 sum[P][TN][TM];
+#pragma unroll
+  for (int q = 0; q < P; q++)
+#pragma unroll
+    for (int i = 0; i < TN; i++)
+#pragma unroll
+      for (int j = 0; j < TM; j++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) sum[q][i][j][v] = 0.f;
   store(0, 0, true);
   HW::wait_lds();
   HW::block_barrier();
@@ -219,9 +221,9 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
     for (int i = 0; i < OA::NRD; i++) curA[i] = rdA[i] + (uint32_t)((set & 1) * C::STAGE_BYTES);
 #pragma unroll
     for (int i = 0; i < OB::NRD; i++) curB[i] = rdB[i] + (uint32_t)((set & 1) * C::STAGE_BYTES);
-    f32x16 part[TN][TM];
 #pragma unroll
     for (int ki = 0; ki < 4; ki++) {
+      const int q = P == 1 ? 0 : P == D ? set : 2 * set + ki / 2;
       u32x4 fa[TM], fb[TN];
 #pragma unroll
       for (int i = 0; i < OA::NRI; i++) read_instr<OA, HW>(curA, ki, i, fa);
@@ -231,17 +233,9 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
       for (int i = 0; i < TN; i++)
 #pragma unroll
         for (int j = 0; j < TM; j++) {
-          f32x16& acc = C::PARTS ? part[i][j] : sum[0][i][j];
-          acc = HW::template mma<C::DT>(fb[i], fa[j], C::PARTS && ki == 0 ? zero : acc);
+          f32x16& acc = sum[q][i][j];
+          acc = HW::template mma<C::DT>(fb[i], fa[j], acc);
         }
-    }
-    if constexpr (C::PARTS) {
-#pragma unroll
-      for (int i = 0; i < TN; i++)
-#pragma unroll
-        for (int j = 0; j < TM; j++)
-#pragma unroll
-          for (int v = 0; v < 16; v++) sum[set][i][j][v] += part[i][j][v];
     }
   };
   // No way out of this loop but its end: the compiler would wait for all loads at the loop's head.  The
@@ -268,7 +262,7 @@ __global__ void __launch_bounds__(C::NT) alcop_direct(const DirectArgs s)
   }
 
 #pragma unroll
-  for (int d = CHAINS / 2; d > 0; d /= 2)
+  for (int d = P / 2; d > 0; d /= 2)
 #pragma unroll
     for (int q = 0; q < d; q++)
 #pragma unroll

@@ -222,7 +222,10 @@ inline double measured_sched_us(const alcop_problem& p, const alcop_sched& s)
 // saves the copy's launch (216 x 89 x 1766: 10.2 us with copies, 12.3 without; 142 x 1816 x 229: 7.8 and 4.9).
 // With the line at 0.85 the direct kernel is taken for 73 % of the products, 1.38 times faster in the mean over
 // all of them; one is slower by more than 1 % (26 x 30 x 567, one operand copied: 6.5 and 7.3), at 1.0 there
-// are eleven.
+// are eleven.  On 880 products drawn afterwards (8 to 4096, and 80 up to 40000; both types, results of 16 and 32
+// bits) it is taken for 660, 1.5 times faster in the mean (in place of a kernel whose waves split K, with partial
+// sums, 1.29); 9 of them are slower by more than 1 %, 8.5 % at most (13 x 19 x 534 6.3 and 6.9).  A line of its own at
+// 0.8 for products whose kernel splits K leaves three slower ones and loses eleven that gain up to 1.5 times.
 inline bool direct_pays(int M, int N, int K, double product_us, double copied)
 {
   const double tiles = (double)((M + 63) / 64) * ((N + 63) / 64), turns = (double)(((long)tiles + 255) / 256);

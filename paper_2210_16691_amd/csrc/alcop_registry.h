@@ -75,8 +75,10 @@ hipError_t dispatch_direct(const DirectArgs& a, int dt, bool transA, bool transB
   using I1 = std::integral_constant<int, 1>;
   auto depth = [&](auto cdt, auto cbl, auto cal) {
     constexpr int DT = decltype(cdt)::value, BL = decltype(cbl)::value, AL = decltype(cal)::value;
-    if (split) return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 1>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 1>>::go(a, blocks, st);
-    return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 0>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 0>>::go(a, blocks, st);
+    if (!split)
+      return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 1>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 1>>::go(a, blocks, st);
+    if (a.K > 256) return LAUNCH<DCfg<DT, 4, BL, AL, 8>>::go(a, blocks, st);
+    return a.K <= 128 ? LAUNCH<DCfg<DT, 2, BL, AL, 2>>::go(a, blocks, st) : LAUNCH<DCfg<DT, 4, BL, AL, 4>>::go(a, blocks, st);
   };
   auto layouts = [&](auto cdt) {
     if (transA) return transB ? depth(cdt, I1{}, I1{}) : depth(cdt, I0{}, I1{});
@@ -88,13 +90,14 @@ hipError_t dispatch_direct(const DirectArgs& a, int dt, bool transA, bool transB
 template <template <class> class LAUNCH>
 hipError_t every_direct()
 {
-  for (int i = 0; i < 32; i++) {
-    DirectArgs a = {};
-    a.M = a.N = 1;
-    a.K = i & 1 ? 256 : 128;
-    const hipError_t rc = dispatch_direct<LAUNCH>(a, (i >> 1) & 1, i & 4, i & 8, i & 16, nullptr);
-    if (rc != hipSuccess) return rc;
-  }
+  for (int i = 0; i < 16; i++)
+    for (int K : {128, 256, 512}) {
+      DirectArgs a = {};
+      a.M = a.N = 1;
+      a.K = K;
+      const hipError_t rc = dispatch_direct<LAUNCH>(a, i & 1, i & 2, i & 4, i & 8, nullptr);
+      if (rc != hipSuccess) return rc;
+    }
   return hipSuccess;
 }
 

@@ -1,5 +1,5 @@
-// Products of operands at any element address: both types, every operand layout, two pipeline depths, one sum or
-// one per k-tile.
+// Products of operands at any element address: both types, every operand layout, one, two, four or eight partial
+// sums.
 #include "alcop_gfx950.hip.h"
 #include "alcop_registry.h"
 namespace alcop {

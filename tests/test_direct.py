@@ -148,7 +148,7 @@ def test_no_more_error_than_with_copies_on_the_gpu(dt, tA, tB):
 def test_init_loads_the_kernels_of_unaligned_calls():
     L = emu.lib()
     assert L.alcop_init() == al.OK
-    assert L.emu_loaded() == 32 + 2             # two types, four layouts, two depths, two orders of the sum; the copies
+    assert L.emu_loaded() == 40 + 2             # two types, four layouts, two depths, and three of partial sums; the copies
 
 
 @pytest.mark.gpu
