@@ -96,6 +96,16 @@ struct Gfx950 {
     asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
   }
   __device__ static __forceinline__ void block_barrier() { __builtin_amdgcn_s_barrier(); }
+  // The distance from a matrix instruction (32x32x16: 8 passes) to the first use of its result, where that is behind
+  // a loop: the compiler, which keeps it within a block of code, can miss the shortest of several ways out.
+  // It passes through here in its registers, so that no copy of it comes before the wait.
+  template <int TN, int TM>
+  __device__ static __forceinline__ void wait_matrix(f32x16 (&acc)[TN][TM])
+  {
+    asm volatile("s_nop 11" : "+v"(acc[TN - 1][TM - 1]));
+#pragma unroll
+    for (int i = 0; i < TN * TM - 1; i++) asm volatile("" : "+v"(acc[i / TM][i % TM]));
+  }
   // nothing may be scheduled across this point
   __device__ static __forceinline__ void sched_fence() { __builtin_amdgcn_sched_barrier(0); }
 

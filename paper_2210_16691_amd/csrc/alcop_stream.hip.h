@@ -430,6 +430,7 @@ __global__ void __launch_bounds__(C::NT) alcop_stream(const Params p)
           }
         }
       }
+      HW::wait_matrix(acc);
       store_tile(acc, batch, tm, tn);
     }
     HW::wait_lds();

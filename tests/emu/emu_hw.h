@@ -402,6 +402,8 @@ struct Emu {
     if (cfg().mutation == 2) return;
     block_sync();
   }
+  template <class A>
+  static void wait_matrix(A&) {}
   static void sched_fence() {}
 
   template <int DT>
