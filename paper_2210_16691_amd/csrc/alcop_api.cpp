@@ -1111,11 +1111,8 @@ struct Packer {
     g.cols = cols;
     g.s_batch = s_batch;
     g.s_row = s_row;
-    g.total = (rows - 1) * s_row + cols;
-    if (s_batch == g.total) {
-      g.total *= batch;
-      g.s_total = s_batch;
-    }
+    const long entry = (rows - 1) * s_row + cols;
+    g.total = batch == 1 || s_batch == entry ? batch * entry : -entry;
   }
   double bytes() const
   {
@@ -1708,7 +1705,6 @@ int alcop_conv2d_igemm_unaligned(const void* x, const void* w, void* y, int N, i
       g.s_grp = (long)C * K;
       g.s_row = K;
       g.total = (long)R * S * C * K;
-      g.s_total = g.s_batch;
     }
   }
   rc = pk.launch(st);

@@ -39,8 +39,8 @@ struct PackSeg {
   FastDiv cpr, rows_d;    // chunks per destination row; destination rows per batch entry
   FastDiv rg;             // PACK_MAT: rows per group; PACK_WIN: chunks per window
   long s_batch, s_grp, s_row;   // source strides in elements: batch entry, row group, row
-  long total, s_total;    // 2-byte elements from the first of a batch entry up to its last, and what lies between: all
-                          // that may be read; up to the source's last where no gap follows an entry (s_total fewer each)
+  long total;             // elements from the source's first to its last, and what lies between: what may be read; where
+                          // gaps part the entries of a batch, minus those of one entry
   int nq, nm, cols;       // PACK_MAT: valid groups, rows of a group, columns
   int width, chans;       // PACK_PIX / PACK_WIN: pixels of a source row, channels
   int pad, cg, stride;    // ... zero pixels on the left; elements per pixel; columns per output
@@ -118,12 +118,12 @@ __global__ void __launch_bounds__(PACK_THREADS) alcop_pack(const PackParams p)
     const uint32_t m = r - q * g.rg.d;
     if ((int)q < g.nq && (int)m < g.nm) {
       const int c0 = (int)c * (16 / g.esize);
-      const char* mat = (const char*)g.src + (long)b * g.s_batch * g.esize;
-      const long off = (long)q * g.s_grp + (long)m * g.s_row + c0;
+      const long first = (long)b * g.s_batch;
+      const long off = first + (long)q * g.s_grp + (long)m * g.s_row + c0;
       if (g.esize == 2)
-        v = keep_elements(load_elements<HW>(mat, off, g.total - (long)b * g.s_total), 0, g.cols - c0);
+        v = keep_elements(load_elements<HW>(g.src, off, g.total < 0 ? first - g.total : g.total), 0, g.cols - c0);
       else
-        v = load_chunk<HW>(mat + off * 4, 4, 0, g.cols - c0);
+        v = load_chunk<HW>((const char*)g.src + off * 4, 4, 0, g.cols - c0);
     }
   } else if (g.kind == PACK_WIN) {
     const uint32_t q = g.rg.div(c);
