@@ -597,7 +597,7 @@ int launch_call(const Call& c, const alcop_sched& s, const KernelEntry* e, hipSt
   p.bias = (const float*)c.bias;
   p.act = c.act;
   p.group_m = std::min(8, p.ntm);
-  if (c.op != ALCOP_OP_CONV2D) p.keep = (short)(c.bias != nullptr || c.act);   // a layer's result (store_chunk)
+  if (c.op != ALCOP_OP_CONV2D) p.keep = (short)(c.bias != nullptr || c.act);   // the rule stands at store_chunk
   // sharers of a panel among the blocks one XCD runs side by side (32 CUs, blocks per CU by LDS)
   const int per_cu = std::max(1, std::min(2, (160 * 1024) / e->lds_bytes));
   // The touch addresses of an M/N-contiguous operand walk whole k-tiles; with a partial last
@@ -1569,7 +1569,8 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
       std::max(lda, ldb) < (1L << 23) && !meets(A, bytes(2, lda, strideA, a_rows, a_cols), C, c_bytes) &&
       !meets(B, bytes(2, ldb, strideB, b_rows, b_cols), C, c_bytes) &&
       !(ep && ep->bias && meets(ep->bias, 4.0 * N, C, c_bytes))) {
-    if (direct_pays(M, N, K, r.us, pk.bytes())) {
+    const bool split = r.s.variant == 3;
+    if (direct_pays(M, N, K, split, r.us, pk.bytes())) {
       DirectArgs d;
       d.A = A;
       d.B = B;
@@ -1583,7 +1584,6 @@ int alcop_bmm_unaligned(const void* A, const void* B, void* C, int batch, int M,
       d.ldc = (int)ldc;
       d.alpha = c.alpha;
       d.flags = (int)out | (c.act ? 4 : 0) | 8 | (c.c_any ? 16 : 0);
-      const bool split = r.s.variant == 3;
       return launch_direct(d, in == ALCOP_BF16, transA, transB, split, st) == hipSuccess ? ALCOP_OK : ALCOP_ERR_LAUNCH;
     }
   }

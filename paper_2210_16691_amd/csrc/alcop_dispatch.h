@@ -222,16 +222,17 @@ inline double measured_sched_us(const alcop_problem& p, const alcop_sched& s)
 // saves the copy's launch (216 x 89 x 1766: 10.2 us with copies, 12.3 without; 142 x 1816 x 229: 7.8 and 4.9).
 // With the line at 0.85 the direct kernel is taken for 73 % of the products, 1.38 times faster in the mean over
 // all of them; one is slower by more than 1 % (26 x 30 x 567, one operand copied: 6.5 and 7.3), at 1.0 there
-// are eleven.  On 880 products drawn afterwards (8 to 4096, and 80 up to 40000; both types, results of 16 and 32
-// bits) it is taken for 660, 1.5 times faster in the mean (in place of a kernel whose waves split K, with partial
-// sums, 1.29); 9 of them are slower by more than 1 %, 8.5 % at most (13 x 19 x 534 6.3 and 6.9).  A line of its own at
-// 0.8 for products whose kernel splits K leaves three slower ones and loses eleven that gain up to 1.5 times.
-inline bool direct_pays(int M, int N, int K, double product_us, double copied)
+// are eleven.  In place of a kernel whose waves split K (`split`), eight partial sums cost 0.17 us in the median;
+// 0.3 are counted.  Of 1796 products drawn afterwards (8 to 4096, and 120 up to 40000; both types, results of 16 and 32
+// bits) the line without them takes 1297, of which 22 are slower by more than 1 %, up to 1.17 times (25 x 1195 x 801
+// 8.5 us and 7.3); with them 1271, 13 slower, up to 1.06 times, and 16 that gain, up to 1.28 times, go back to the copies.
+// What is taken is 1.52 times faster in the mean, 1.27 in place of kernels that split K.
+inline bool direct_pays(int M, int N, int K, bool split, double product_us, double copied)
 {
   const double tiles = (double)((M + 63) / 64) * ((N + 63) / 64), turns = (double)(((long)tiles + 255) / 256);
   const double kt = (K + 63) / 64, bytes = 2.0 * ((double)M * K + (double)K * N + (double)M * N);
   const double with_copies = 2.38 + 1.41 * product_us + 1.64 * copied / 5.1e6;
-  const double direct = 3.12 + (0.033 + 0.282 * turns) * kt + 0.267 * turns + 0.68 * bytes / 5.1e6;
+  const double direct = (split && K > 256 ? 3.42 : 3.12) + (0.033 + 0.282 * turns) * kt + 0.267 * turns + 0.68 * bytes / 5.1e6;
   return direct < 0.85 * with_copies;
 }
 

@@ -97,8 +97,8 @@ struct Params {
   int cdh, cdw;                // dilation: filter tap (r, s) reads row ih0 + r * cdh, column iw0 + s * cdw
   // by Q, P * Q, C / 8 and S for every convolution; rWsDiv: the row length of a resident patch.  A division
   // by a value that is not constant is 35 vector instructions; a gather has two for each of a tile's
-  // loads, a patch one, and one for each of its stores (32 x 56 x 56 x 64 13.0 -> 12.5 us, 13 x 44 x 43 x 64
-  // 5.15 -> 4.75)
+  // loads, a patch one, and one for each of its stores (32 x 56 x 56 x 64 13.0 -> 12.5 us, on another card 12.2 ->
+  // 11.7; 13 x 44 x 43 x 64 5.15 -> 4.75)
   FastDiv rQ, rPQ, rWsDiv, rC8;
   unsigned a_span, b_span;     // conv: bytes of x; unused otherwise
   union {
@@ -607,11 +607,17 @@ __device__ __forceinline__ void store_elements(const Params& p, char* dst, int n
 }
 
 // KEEP: the store is written through and its line stays in the memory-side cache, where another XCD finds
-// it; otherwise the line is the first to be evicted (non-temporal).  The result of a layer with a bias or an
-// activation is what the next layer reads: the two layers of 4096 x 768 x 3072 took 55.0 us non-temporal, 49.0
-// so (a plain store 49 to 51: dirty lines are written back when the kernel ends).  Of 60 such pairs, 130 to 8000
-// tokens, one was slower (2 %) and the others 0 to 20 % faster.  A result that nothing asks for again takes the place of
-// operands: 3 to 14 % lost in the gradient products of 16 sizes of 60, up to 30 % in scores of 50 MB and more.
+// it; otherwise the line is the first to be evicted (non-temporal).
+//   The rule (Params::keep): products with a bias or an activation, as a layer's result is what the next layer
+// reads.  The two layers of 4096 x 768 x 3072 take 52.7 us non-temporal, 44.3 so (a plain store is 0 to 4 % behind: dirty
+// lines are written back when the kernel ends).  Of 60 such pairs, 130 to 8000 tokens, one was slower (2 %) and the others
+// 0 to 20 % faster.  What it costs where nothing reads the result: of 90 single layers (130 to 8192 rows, new buffers in
+// turn) 24 are 1 to 9 % slower, 23 as much as 4 % faster, the mean is 0.3 % slower.  Results without either are not kept:
+// 3 to 14 % were lost in the gradient products of 16 sizes of 60, up to 30 % in scores of 50 MB and more.
+//   What leaves it aside: kernels whose waves split K (at most 256 tiles of 64 x 64: results of a few MB), A stored
+// K x M (weight gradients, not layers), wave tiles of 128 x 128 (no register is free), and results in elements (c_any),
+// with them most of the products without copies.  Convolutions leave it aside too; whether their results
+// are better kept has not been measured.
 template <class OT, class HW, bool KEEP = false>
 __device__ __forceinline__ void store_chunk(const Params& p, char* dst, int n, u32x4 v)
 {
