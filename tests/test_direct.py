@@ -112,7 +112,7 @@ def _no_more_error(dt, sizes, tA, tB, dev, call, auto):
 
 
 # most of these get a kernel that splits K among four or eight waves, where copied; all get the direct kernel
-ROUTES = [(142, 181, 229), (100, 203, 449), (201, 99, 501), (260, 131, 395), (67, 66, 65), (435, 386, 385)]
+ROUTES = [(142, 181, 229), (201, 99, 401), (260, 131, 395), (330, 300, 501), (67, 66, 65), (90, 75, 121), (435, 386, 385)]
 
 
 @pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
