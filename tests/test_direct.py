@@ -77,6 +77,60 @@ def test_on_the_gpu(dt, out, tA, tB):
         assert _untouched(Cbuf, C) and bool((ws == 255).all()), size
 
 
+def _below_a_chunk(tA, tB):
+    """Rows of A, or of B stored N x K, may be fewer than a chunk has elements."""
+    return ([(1, 9, 70), (5, 130, 8)] if not tA else []) + ([(9, 1, 70), (130, 5, 8)] if tB else []) + \
+           ([(1, 1, 8), (3, 7, 300)] if tB and not tA else [])
+
+
+def _aligned_result(dt, out, size, tA, tB, alpha, dev):
+    """Whole aligned chunks of C, without a bias; A at any element."""
+    M, N, K = size
+    A0 = wl.small_ints((K, M) if tA else (M, K), dt, 52 + M)
+    B = wl.small_ints((N, K) if tB else (K, N), dt, 62 + N).to(dev)
+    ref = oracle.epilogue(oracle.gemm(wl.bits(A0), wl.bits(B.cpu()), ODT[dt], bool(tA), bool(tB)), alpha, None, 0)
+    buf = torch.full((A0.numel() + 16,), float("inf"), dtype=A0.dtype).to(dev)
+    A = buf[1:A0.numel() + 1].view(A0.shape)
+    A.copy_(A0)
+    Cbuf = torch.full((M + 2, N), float("nan"), dtype=TDT[out]).to(dev)
+    ws = torch.full((al.alcop_unaligned_workspace_bytes(1, M, N, K, ADT[out]),), 255, dtype=torch.uint8, device=dev)
+    return A, B, Cbuf, Cbuf[1:M + 1], ws, torch.from_numpy(ref).to(TDT[out]).double().numpy()
+
+
+WHOLE = [(65, 72, 67), (9, 8, 9), (130, 136, 200), (64, 64, 330)]
+
+
+def _edges(dt, out, tA, tB, dev, call):
+    for size in _below_a_chunk(tA, tB):
+        A, B, C, Cbuf, bias, ws, ref = _case(dt, out, size, tA, tB, dev)
+        call(A, B, C, ws, 0.5, bias, 1)
+        assert np.array_equal(C.double().cpu().numpy(), ref), size
+        assert _untouched(Cbuf, C) and bool((ws == 255).all()), size
+    for n, size in enumerate(WHOLE):
+        A, B, Cbuf, C, ws, ref = _aligned_result(dt, out, size, tA, tB, (1.0, 0.5)[n & 1], dev)
+        call(A, B, C, ws, (1.0, 0.5)[n & 1], None, 0)
+        assert np.array_equal(C.double().cpu().numpy(), ref), size
+        assert bool(torch.isnan(Cbuf[[0, -1]]).all()) and bool((ws == 255).all()), size
+
+
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dt,out", [("f16", "f16"), ("bf16", "f32")])
+def test_small_extents_and_aligned_results_on_the_cpu_model(dt, out, tA, tB):
+    def call(A, B, C, ws, alpha, bias, act):
+        errs = emu.call(al.alcop_bmm_unaligned, A, B, C, ws, alpha, bias, act, transA=bool(tA), transB=bool(tB),
+                        reads=[A, B] + ([] if bias is None else [bias]), writes=[C])
+        assert not errs, errs[:3]
+    _edges(dt, out, tA, tB, "cpu", call)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("tA,tB", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("dt,out", [("f16", "f16"), ("bf16", "f32")])
+def test_small_extents_and_aligned_results_on_the_gpu(dt, out, tA, tB):
+    _edges(dt, out, tA, tB, "cuda:0", lambda A, B, C, ws, alpha, bias, act: al.alcop_bmm_unaligned(
+        A, B, C, ws, alpha, bias, act, transA=bool(tA), transB=bool(tB)))
+
+
 def _both_routes(dt, size, tA, tB, dev, call, auto):
     """The product without copies and with them, each with its relative error against 64 bits, and whether the
     kernel of the copies' route splits K among its waves (fp32 results)."""
