@@ -244,7 +244,7 @@ int alcop_conv2d_igemm_dilated(const void* x, const void* w, void* y, int N, int
  * share no memory with C may instead run in one launch that loads the operands where they lie.  It
  * leaves the workspace alone (which is asked for all the same).  Its elements are what an aligned call
  * returns, bit for bit, unless that call is given a kernel whose waves split K (variant 3): then they
- * are sums of the same products in another order, of no larger error.
+ * are sums of the same products in another order, in the mean of no larger error.
  *
  * Of an operand, the memory between its rows may be read as well (up to 14 bytes behind a row's end, never
  * behind the last row of a batch entry); what it holds does not matter.
